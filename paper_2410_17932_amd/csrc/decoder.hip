@@ -629,40 +629,6 @@ __global__ void k_dec_pack(PackArgs<T> a) {
   }
 }
 
-// RGB head: F = W_o h_0 + b_o, one thread per output pixel of any crop.
-struct HeadArgs {
-  int n_crops, kp, K0;
-  int S[VRS_MAX_CROPS];
-  long long pix_base[VRS_MAX_CROPS + 1];
-  long long out_base[VRS_MAX_CROPS];
-  long long h_off[VRS_MAX_CROPS];
-};
-
-template <typename T>
-__global__ void k_dec_head(HeadArgs a, const T* __restrict__ h0, const float* __restrict__ wo,
-                           const float* __restrict__ bo, float* __restrict__ out) {
-  const long long npix = a.pix_base[a.n_crops];
-  for (long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x; p < npix;
-       p += (long long)gridDim.x * blockDim.x) {
-    int k = 0;
-    while (k + 1 < a.n_crops && p >= a.pix_base[k + 1]) ++k;
-    const long long q = p - a.pix_base[k];
-    const int S = a.S[k];
-    const T* h = h0 + a.h_off[k] + q * a.kp;
-    float a0 = bo[0], a1 = bo[1], a2 = bo[2];
-    for (int c = 0; c < a.K0; ++c) {
-      const float v = to_f(h[c]);
-      a0 += wo[c] * v;
-      a1 += wo[a.K0 + c] * v;
-      a2 += wo[2 * a.K0 + c] * v;
-    }
-    const long long plane = (long long)S * S;
-    out[a.out_base[k] + q] = a0;
-    out[a.out_base[k] + plane + q] = a1;
-    out[a.out_base[k] + 2 * plane + q] = a2;
-  }
-}
-
 // ------------------------------------------------------------ host side
 struct DecPlan {
   int nd, C, dtype;
@@ -671,11 +637,15 @@ struct DecPlan {
   size_t w_off[VRS_MAX_LEVELS], b_off[VRS_MAX_LEVELS];   // offsets into the float weights
   size_t head_w, head_b;
   // workspace (bytes)
-  size_t wp[VRS_MAX_LEVELS], bp[VRS_MAX_LEVELS], h[VRS_MAX_LEVELS], pre[VRS_MAX_LEVELS],
-      dh[VRS_MAX_LEVELS], total;
-  long long h_elems[VRS_MAX_LEVELS], pre_elems[VRS_MAX_LEVELS];
+  size_t wp[VRS_MAX_LEVELS], bp[VRS_MAX_LEVELS], h[VRS_MAX_LEVELS];
+  // the adjoint's weights, pre-activations and input gradient (one level at a time)
+  size_t wb[VRS_MAX_LEVELS], pre, dx, total;
+  long long h_elems[VRS_MAX_LEVELS];
   int n_crops;
-  long long head_pix;
+  // level l's weights in the adjoint's padded channel order
+  long long wb_elems(int l) const {
+    return (long long)2 * kp[l] * 9 * ((l + 1 < nd ? kp[l + 1] : 0) + 16);
+  }
 };
 
 static int round_up(int a, int b) { return (a + b - 1) / b * b; }
@@ -710,6 +680,7 @@ static bool dec_plan(const vrs_decoder_desc* dd, const vrs_crop* crops, int n_cr
   P->head_b = wo + 3 * P->K[0];
   const int unit = 1 << (P->nd - 1);
   Carver c;
+  long long pre = 0, dx = 0;
   for (int l = 0; l < P->nd; ++l) {
     long long he = 0;
     for (int k = 0; k < n_crops; ++k) {
@@ -718,13 +689,15 @@ static bool dec_plan(const vrs_decoder_desc* dd, const vrs_crop* crops, int n_cr
       he += s * s;
     }
     P->h_elems[l] = he * P->kp[l];
-    P->pre_elems[l] = he * 2 * P->kp[l];
     P->wp[l] = c.take((size_t)2 * P->kp[l] * P->kpad[l] * esz);
     P->bp[l] = c.take((size_t)2 * P->kp[l] * 4);
     P->h[l] = c.take((size_t)P->h_elems[l] * esz);
-    P->pre[l] = c.take((size_t)P->pre_elems[l] * 4);
-    P->dh[l] = c.take((size_t)P->h_elems[l] * 4);
+    P->wb[l] = c.take((size_t)P->wb_elems(l) * 4);
+    pre = std::max(pre, he * 2 * P->kp[l]);
+    if (l + 1 < P->nd) dx = std::max(dx, he * P->kp[l + 1]);
   }
+  P->pre = c.take((size_t)pre * 4);
+  P->dx = c.take((size_t)dx * 4);
   P->total = c.off;
   return true;
 }
@@ -831,7 +804,7 @@ template <typename T>
 static vrs_status decode_impl(const DecPlan& P, const float* pyramid, int levels,
                               const float* periph, const KViews& kv, const vrs_crop* crops,
                               int n_crops, const vrs_crop_place* place, const float* weights,
-                              float* out, void* ws, bool keep_pre, hipStream_t st) {
+                              float* out, void* ws, hipStream_t st) {
   {
     PackArgs<T> pa;
     pa.n = P.nd;
@@ -875,7 +848,7 @@ static vrs_status decode_impl(const DecPlan& P, const float* pyramid, int levels
     }
     VRS_HIP_CHECK(launch_conv<T>(d, 2 * P.kp[l] / 16, blocks, pyramid, periph, hn,
                                  at<T>(ws, P.wp[l]), at<float>(ws, P.bp[l]), at<T>(ws, P.h[l]),
-                                 keep_pre ? at<float>(ws, P.pre[l]) : nullptr, hf, st));
+                                 nullptr, hf, st));
   }
   return VRS_OK;
 }
@@ -935,10 +908,10 @@ vrs_status decode_impl_entry(const float* pyramid, int levels, const float* rgb_
   vrs_status r;
   if (P.dtype == VRS_BF16)
     r = decode_impl<__bf16>(P, pyramid, levels, rgb_periphery, kv, crops, n_crops, place,
-                            weights, fovea_rgb, ws, false, st);
+                            weights, fovea_rgb, ws, st);
   else
     r = decode_impl<float>(P, pyramid, levels, rgb_periphery, kv, crops, n_crops, place,
-                           weights, fovea_rgb, ws, false, st);
+                           weights, fovea_rgb, ws, st);
   trace_end(tr, VRS_TRACE_DECODER, st);
   return r;
 }
@@ -955,187 +928,464 @@ extern "C" vrs_status vrs_decode_fovea(const float* pyramid, int levels,
 }
 
 // ------------------------------------------------------------- backward
+// Per level, finest first: the pre-activations are recomputed, the gate's
+// adjoint turns them into their gradients, and the weight gradient and the
+// input gradient are matrix products on the FP32 matrix cores (operands and
+// sums stay in float32, as the pre-activations' gradients and the weights
+// are).  Four 512 crops, 16/32/64/64: 109 GFLOP, 0.73 ms at the 150 TFLOP/s a
+// large float32 product reaches; the products take 1.6 ms (0.65 input, 0.95
+// weights) where per-element loops took 15.9 (11.9 and 4.0), the whole adjoint
+// with the forward 2.07 ms instead of 16.7.
+//
+// Both products take the input channels in one padded order of 16-channel
+// tiles, [pyramid 4 | upsampled kpn | periphery 3 | 1 spare | zeros], so that
+// every group of four lanes' values has one destination.
 namespace vrs {
 
-// head: dh0 = W_o^T dF, dW_o += dF h0^T, db_o += sum dF (block sums, atomics)
-template <typename T>
-__global__ __launch_bounds__(256) void k_dec_head_bwd(HeadArgs a, const T* __restrict__ h0,
+// Input channel (of the weights) of padded channel n, or -1.
+__device__ inline int pad_to_orig(int n, int kn, int kpn, int has_p) {
+  if (n < 4) return n;
+  n -= 4;
+  if (n < kpn) return n < kn ? 4 + n : -1;
+  n -= kpn;
+  return has_p && n < 3 ? 4 + kn + n : -1;
+}
+
+// Weights as the input gradient's A operand, all levels in one launch:
+// [nout / 32][tap][2 groups of 16 k][N-tile][lane][4], lane (col, kq) holding
+// channel 16 j + col against pre-activations 16 g + 4 kq + s (s < 4): one
+// 16-byte load per lane feeds four matrix steps.
+struct PackBwdArgs {
+  int n;
+  int K[VRS_MAX_LEVELS], kn[VRS_MAX_LEVELS], kpn[VRS_MAX_LEVELS], cin[VRS_MAX_LEVELS];
+  long long start[VRS_MAX_LEVELS + 1];
+  const float* w[VRS_MAX_LEVELS];
+  float* wb[VRS_MAX_LEVELS];
+};
+
+__global__ void k_dec_pack_bwd(PackBwdArgs a) {
+  for (long long e0 = blockIdx.x * (long long)blockDim.x + threadIdx.x; e0 < a.start[a.n];
+       e0 += (long long)gridDim.x * blockDim.x) {
+    int l = 0;
+    while (l + 1 < a.n && e0 >= a.start[l + 1]) ++l;
+    const int e = (int)(e0 - a.start[l]);
+    const int nt = a.kpn[l] / 16 + 1;
+    const int s = e & 3, lane = (e >> 2) & 63;
+    int q = e >> 8;
+    const int j = q % nt;
+    q /= nt;
+    const int g = q & 1, tap = (q >> 1) % 9, c = (q >> 1) / 9;
+    const int ch = c * 16 + 4 * (lane >> 4) + s;      // feature (g = 0) or gate (g = 1) half
+    const int oc = pad_to_orig(j * 16 + (lane & 15), a.kn[l], a.kpn[l], l == 0);
+    float v = 0.0f;
+    if (ch < a.K[l] && oc >= 0)
+      v = a.w[l][((long long)(g ? a.K[l] + ch : ch) * 9 + tap) * a.cin[l] + oc];
+    a.wb[l][e] = v;
+  }
+}
+
+// Gate: h = ELU(f) sigmoid(g); the pre-activations are overwritten by their
+// gradients.  dh comes from the RGB head (HEAD, finest level: W_o^T dF, with
+// the head's weight gradients summed on the way) or is gathered from the
+// finer level's input gradient dx [pixel][kp]: the bilinear upsample's
+// adjoint, rows and columns 2m-1 .. 2m+2 with weights 1/4, 3/4, 3/4, 1/4 (1
+// for the pixel whose outer neighbour the clamp folds back).  A gather reads
+// each value four times from cache, where the scatter it replaces took four
+// device atomics per value.  HBM-bound: 16 B per pre-activation pair read
+// and written.  One thread per pixel and four channels; a thread keeps its
+// channels over its pixels.
+struct GateArgs {
+  int n_crops, kp, K;
+  int S[VRS_MAX_CROPS];
+  long long pix_base[VRS_MAX_CROPS + 1];
+  long long out_base[VRS_MAX_CROPS];
+};
+
+template <typename T, bool HEAD>
+__global__ __launch_bounds__(256) void k_dec_gate_bwd(GateArgs a, float* __restrict__ pre,
+                                                      const float* __restrict__ dx,
+                                                      const T* __restrict__ h0,
                                                       const float* __restrict__ wo,
                                                       const float* __restrict__ dF,
-                                                      float* __restrict__ dh0,
                                                       float* __restrict__ dwo,
                                                       float* __restrict__ dbo) {
   __shared__ float s_acc[3 * 64 + 3];
-  for (int e = threadIdx.x; e < 3 * a.K0 + 3; e += blockDim.x) s_acc[e] = 0.0f;
-  __syncthreads();
+  const int G = a.kp >> 2, per = 256 / G;      // channel groups; pixels per workgroup and round
+  const int g = threadIdx.x % G, slot = threadIdx.x / G, c0 = g * 4;
+  float w[3][4], aw[3][4], ab[3] = {0, 0, 0};
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w[r][i] = HEAD && c0 + i < a.K ? wo[r * a.K + c0 + i] : 0.0f;
+      aw[r][i] = 0.0f;
+    }
+  if (HEAD) {
+    for (int e = threadIdx.x; e < 3 * a.K + 3; e += 256) s_acc[e] = 0.0f;
+    __syncthreads();
+  }
   const long long npix = a.pix_base[a.n_crops];
-  const long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (p < npix) {
+  for (long long p = blockIdx.x * (long long)per + slot; slot < per && p < npix;
+       p += (long long)gridDim.x * per) {
     int k = 0;
     while (k + 1 < a.n_crops && p >= a.pix_base[k + 1]) ++k;
-    const long long q = p - a.pix_base[k];
-    const long long plane = (long long)a.S[k] * a.S[k];
-    const float g[3] = {dF[a.out_base[k] + q], dF[a.out_base[k] + plane + q],
-                        dF[a.out_base[k] + 2 * plane + q]};
-    const T* h = h0 + a.h_off[k] + q * a.kp;
-    float* dh = dh0 + a.h_off[k] + q * a.kp;
-    for (int c = 0; c < a.K0; ++c) {
-      const float hv = to_f(h[c]);
-      dh[c] += wo[c] * g[0] + wo[a.K0 + c] * g[1] + wo[2 * a.K0 + c] * g[2];
-      if (dwo) {
-        atomicAdd(&s_acc[c], g[0] * hv);
-        atomicAdd(&s_acc[a.K0 + c], g[1] * hv);
-        atomicAdd(&s_acc[2 * a.K0 + c], g[2] * hv);
+    const int S = a.S[k];
+    const int q = (int)(p - a.pix_base[k]);
+    float dh[4] = {0, 0, 0, 0};
+    if (HEAD) {
+      const long long plane = (long long)S * S;
+      float gr[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) gr[r] = dF[a.out_base[k] + r * plane + q];
+      float hv[4] = {0, 0, 0, 0};
+      if (dwo)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hv[i] = to_f(h0[p * a.kp + c0 + i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        dh[i] = w[0][i] * gr[0] + w[1][i] * gr[1] + w[2][i] * gr[2];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) aw[r][i] += gr[r] * hv[i];
+      }
+#pragma unroll
+      for (int r = 0; r < 3; ++r) ab[r] += gr[r];
+    } else {
+      const int y = q / S, x = q - y * S, Sf = 2 * S;
+      const float* src = dx + 4 * a.pix_base[k] * a.kp + c0;   // the finer layer has four times the pixels
+#pragma unroll
+      for (int iy = 0; iy < 4; ++iy) {
+        const int fy = 2 * y - 1 + iy;
+        if (fy < 0 || fy >= Sf) continue;
+        const float wy = fy == 0 || fy == Sf - 1 ? 1.0f : (iy == 0 || iy == 3 ? 0.25f : 0.75f);
+        float row[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int ix = 0; ix < 4; ++ix) {
+          const int fx = 2 * x - 1 + ix;
+          if (fx < 0 || fx >= Sf) continue;
+          const float wx = fx == 0 || fx == Sf - 1 ? 1.0f : (ix == 0 || ix == 3 ? 0.25f : 0.75f);
+          const float4 v =
+              *reinterpret_cast<const float4*>(src + ((long long)fy * Sf + fx) * a.kp);
+          row[0] = fmaf(wx, v.x, row[0]);
+          row[1] = fmaf(wx, v.y, row[1]);
+          row[2] = fmaf(wx, v.z, row[2]);
+          row[3] = fmaf(wx, v.w, row[3]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dh[i] = fmaf(wy, row[i], dh[i]);
       }
     }
-    if (dbo)
-      for (int ch = 0; ch < 3; ++ch) atomicAdd(&s_acc[3 * a.K0 + ch], g[ch]);
+    float* pf = pre + p * 2 * a.kp + (c0 >> 4) * 32 + (c0 & 15);
+    const float4 f4 = *reinterpret_cast<const float4*>(pf);
+    const float4 g4 = *reinterpret_cast<const float4*>(pf + 16);
+    const float fv[4] = {f4.x, f4.y, f4.z, f4.w}, gv[4] = {g4.x, g4.y, g4.z, g4.w};
+    float of[4], og[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float sg = 1.0f / (1.0f + expf(-gv[i]));
+      const float el = fv[i] > 0.0f ? fv[i] : expm1f(fv[i]);
+      const float del = fv[i] > 0.0f ? 1.0f : el + 1.0f;
+      const bool in = c0 + i < a.K;
+      of[i] = in ? dh[i] * sg * del : 0.0f;
+      og[i] = in ? dh[i] * el * sg * (1.0f - sg) : 0.0f;
+    }
+    *reinterpret_cast<float4*>(pf) = make_float4(of[0], of[1], of[2], of[3]);
+    *reinterpret_cast<float4*>(pf + 16) = make_float4(og[0], og[1], og[2], og[3]);
+  }
+  if (!HEAD || !dwo) return;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (slot < per && c0 + i < a.K) atomicAdd(&s_acc[r * a.K + c0 + i], aw[r][i]);
+    if (slot < per && g == 0) atomicAdd(&s_acc[3 * a.K + r], ab[r]);
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < 3 * a.K0 + 3; e += blockDim.x) {
-    if (e < 3 * a.K0 && dwo) atomicAdd(&dwo[e], s_acc[e]);
-    if (e >= 3 * a.K0 && dbo) atomicAdd(&dbo[e - 3 * a.K0], s_acc[e]);
-  }
+  for (int e = threadIdx.x; e < 3 * a.K + 3; e += 256)
+    atomicAdd(e < 3 * a.K ? &dwo[e] : &dbo[e - 3 * a.K], s_acc[e]);
 }
 
-// gate: h = ELU(f) sigmoid(g); pre-activations overwritten by their grads
-__global__ void k_dec_gate_bwd(float* __restrict__ pre, const float* __restrict__ dh,
-                               long long npix, int kp, int K) {
-  const long long total = npix * kp;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const long long p = e / kp;
-    const int ch = (int)(e - p * kp);
-    const int t = ch / 16, j = ch % 16;
-    float* pf = pre + p * 2 * kp + t * 32 + j;
-    float* pg = pf + 16;
-    if (ch >= K) { *pf = 0.0f; *pg = 0.0f; continue; }
-    const float f = *pf, g = *pg, d = dh[p * kp + ch];
-    const float sg = 1.0f / (1.0f + expf(-g));
-    const float el = f > 0.0f ? f : expm1f(f);
-    const float del = f > 0.0f ? 1.0f : el + 1.0f;
-    *pf = d * sg * del;
-    *pg = d * el * sg * (1.0f - sg);
-  }
-}
-
-// transposed convolution: gradient of level l's input, routed to its
-// sources (pyramid layer, upsampled coarser output, periphery crop)
-template <typename T>
+// Input gradient: a 3x3 convolution of the pre-activations' gradients with
+// the flipped weights.  One workgroup per tile of 4 RPW rows x 16 columns,
+// RPW rows per wave; the halo of 32 pre-activations at a time in LDS, weights
+// from L2 in operand order, one step ahead of their use.  Bound by the FP32
+// matrix rate (4 RPW NT steps of 32 cycles for RPW 16-byte LDS reads and NT
+// 16-byte global loads per lane).  The pixel stride of 36 floats spreads the
+// 16 columns of a read over all LDS banks.
+template <int NT, int RPW>
 __global__ __launch_bounds__(256) void k_dec_dgrad(DecLevel d, const float* __restrict__ dpre,
-                                                   const float* __restrict__ w, float* __restrict__ dpyr,
-                                                   float* __restrict__ dhn, float* __restrict__ dper) {
-  const int cin = d.cin;
-  // global pixel index over all crops of this level
-  long long pbase[VRS_MAX_CROPS + 1];
-  pbase[0] = 0;
-  for (int k = 0; k < d.n_crops; ++k) pbase[k + 1] = pbase[k] + (long long)d.S[k] * d.S[k];
-  const long long n_elem = pbase[d.n_crops] * cin;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n_elem;
-       e += (long long)gridDim.x * blockDim.x) {
-    const long long p = e / cin;
-    const int c = (int)(e - p * cin);
-    int k = 0;
-    while (k + 1 < d.n_crops && p >= pbase[k + 1]) ++k;
-    const int S = d.S[k];
-    const long long q = p - pbase[k];
-    const int y = (int)(q / S), x = (int)(q - (long long)y * S);
-    const float* dp = dpre + d.pre_off[k];
-    float acc = 0.0f;
-    for (int ky = 0; ky < 3; ++ky) {
-      const int oy = y - ky + 1;
-      if (oy < 0 || oy >= S) continue;
-      for (int kx = 0; kx < 3; ++kx) {
-        const int ox = x - kx + 1;
-        if (ox < 0 || ox >= S) continue;
-        const float* g = dp + ((long long)oy * S + ox) * d.nout;
-        const int tap = ky * 3 + kx;
-        for (int ch = 0; ch < d.width; ++ch) {
-          const int t = ch / 16, j = ch % 16;
-          acc += g[t * 32 + j] * w[((long long)ch * 9 + tap) * cin + c];
-          acc += g[t * 32 + 16 + j] * w[((long long)(d.width + ch) * 9 + tap) * cin + c];
+                                                   const float* __restrict__ wb,
+                                                   float* __restrict__ dpyr,
+                                                   float* __restrict__ dx,
+                                                   float* __restrict__ dper) {
+  constexpr int TH = 4 * RPW, NPIX = (TH + 2) * 18, PS = 36;
+  __shared__ __align__(16) float s_g[NPIX * PS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int k = 0;
+  while (k + 1 < d.n_crops && (int)blockIdx.x >= d.tile_base[k + 1]) ++k;
+  const int tl = blockIdx.x - d.tile_base[k], S = d.S[k];
+  const int oy = (tl / d.tiles_x[k]) * TH, ox = (tl % d.tiles_x[k]) * 16;
+  const int r0 = wave * RPW, col = lane & 15, kq = lane >> 4;
+  const float* src = dpre + d.pre_off[k];
+  v4f acc[RPW][NT];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[r][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  const int chunks = d.nout >> 5;
+  const v4f* wp = reinterpret_cast<const v4f*>(wb) + lane;
+  v4f b[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) b[j] = wp[j * 64];
+  for (int c = 0; c < chunks; ++c) {
+    if (c) __syncthreads();
+    for (int i = tid; i < NPIX * 8; i += 256) {
+      const int pix = i >> 3, q = i & 7;
+      const int y = oy + pix / 18 - 1, x = ox + pix % 18 - 1;
+      float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (y >= 0 && y < S && x >= 0 && x < S)
+        v = *reinterpret_cast<const float4*>(src + ((long long)y * S + x) * d.nout + c * 32 + q * 4);
+      *reinterpret_cast<float4*>(&s_g[pix * PS + q * 4]) = v;
+    }
+    __syncthreads();
+    for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          wp += NT * 64;
+          // the next step's weights (past the end: this step's again)
+          const bool end = c == chunks - 1 && ky == 2 && kx == 2 && g == 1;
+          v4f bn[NT];
+#pragma unroll
+          for (int j = 0; j < NT; ++j) bn[j] = wp[(end ? -NT * 64 : 0) + j * 64];
+          v4f av[RPW];
+#pragma unroll
+          for (int r = 0; r < RPW; ++r)
+            av[r] = *reinterpret_cast<const v4f*>(
+                &s_g[((r0 + r + 2 - ky) * 18 + col + 2 - kx) * PS + g * 16 + kq * 4]);
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+              for (int r = 0; r < RPW; ++r)
+                acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[j][s], av[r][s], acc[r][j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) b[j] = bn[j];
         }
+  }
+  // lane (col, kq) holds padded channels 16 j + 4 kq + i (i < 4) of pixel col
+  const int x = ox + col;
+  if (x >= S) return;
+  const long long pix0 = d.pre_off[k] / d.nout;
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    const int y = oy + r0 + r;
+    if (y >= S) continue;
+    const long long p = (long long)y * S + x;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int n0 = j * 16 + kq * 4 - 4;     // after the pyramid's four
+      if (n0 < 0) {
+        if (dpyr)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dpyr[d.pyr_off[k] + p * 4 + i] += acc[r][j][i];
+      } else if (n0 < d.kpn) {
+        *reinterpret_cast<v4f*>(dx + (pix0 + p) * d.kpn + n0) = acc[r][j];
+      } else if (n0 == d.kpn && d.has_p && dper) {
+        const long long plane = (long long)d.W * d.H;
+        float* o = dper + (long long)d.view[k] * 3 * plane +
+                   (long long)(dec_y0(d, k) + y) * d.W + (dec_x0(d, k) + x);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) atomicAdd(o + i * plane, acc[r][j][i]);
       }
     }
-    if (c < d.C) {
-      if (dpyr) dpyr[d.pyr_off[k] + q * d.C + c] += acc;
-    } else if (c < d.C + d.kn) {
-      const int cc = c - d.C;
-      const int Sn = S >> 1;
-      const float sx = 0.5f * (float)x - 0.25f, sy = 0.5f * (float)y - 0.25f;
-      const float fx0 = floorf(sx), fy0 = floorf(sy);
-      const float fx = sx - fx0, fy = sy - fy0;
-      int xa = (int)fx0, ya = (int)fy0, xb = xa + 1, yb = ya + 1;
-      xa = xa < 0 ? 0 : (xa > Sn - 1 ? Sn - 1 : xa);
-      xb = xb < 0 ? 0 : (xb > Sn - 1 ? Sn - 1 : xb);
-      ya = ya < 0 ? 0 : (ya > Sn - 1 ? Sn - 1 : ya);
-      yb = yb < 0 ? 0 : (yb > Sn - 1 ? Sn - 1 : yb);
-      float* h = dhn + d.hn_off[k];
-      atomicAdd(&h[((long long)ya * Sn + xa) * d.kpn + cc], acc * (1.0f - fy) * (1.0f - fx));
-      atomicAdd(&h[((long long)ya * Sn + xb) * d.kpn + cc], acc * (1.0f - fy) * fx);
-      atomicAdd(&h[((long long)yb * Sn + xa) * d.kpn + cc], acc * fy * (1.0f - fx));
-      atomicAdd(&h[((long long)yb * Sn + xb) * d.kpn + cc], acc * fy * fx);
-    } else if (d.has_p && dper) {
-      const int cc = c - d.C - d.kn;
-      const long long plane = (long long)d.W * d.H;
-      atomicAdd(&dper[(long long)d.view[k] * 3 * plane + cc * plane +
-                      (long long)(dec_y0(d, k) + y) * d.W + (dec_x0(d, k) + x)],
-                acc);
-    }
   }
 }
 
-// weight gradient over 8x8 output tiles: dW[row][tap][c] += sum_p dpre[p][row] x[p+tap][c]
-template <typename T>
+// Weight gradient dW[row][tap][c] = sum over pixels of dpre[p][row]
+// x[p + tap][c], and db from a channel of ones (the spare one): a matrix
+// product with the pixels as its depth.  A workgroup takes 32 rows (blockIdx.y)
+// and keeps their 2 x 9 NT output tiles in registers, a quarter per wave, over
+// its share of the 8 x 16 pixel tiles, so that each sum reaches memory once
+// per workgroup.  Bound by the FP32 matrix rate: 2 + 9 NT / 4 LDS reads for
+// 9 NT / 2 steps of 32 cycles.  The pixel strides put a read's four pixels in
+// different banks.
+template <int NT>
+constexpr int wg_stride() { return NT % 2 ? 16 * NT : 16 * NT + 16; }
+constexpr int kWgRows = 36;   // dpre pixel stride in LDS (32 rows)
+template <int NT>
+constexpr size_t wg_smem() { return (size_t)(180 * wg_stride<NT>() + 128 * kWgRows) * 4; }
+
+template <typename T, int NT>
 __global__ __launch_bounds__(256) void k_dec_wgrad(DecLevel d, const float* __restrict__ pyr,
                                                    const float* __restrict__ periph,
                                                    const T* __restrict__ hnext,
                                                    const float* __restrict__ dpre,
                                                    float* __restrict__ dw, float* __restrict__ db) {
+  constexpr int NQ = (9 * NT + 3) / 4, CS = wg_stride<NT>();
   extern __shared__ __align__(16) char smem[];
-  const int cin = d.cin, K = d.width;
-  float* sx = reinterpret_cast<float*>(smem);          // [10*10][cin]
-  float* sg = sx + 100 * cin;                          // [64][2K]
-  int b = blockIdx.x, k = 0;
-  while (k + 1 < d.n_crops && b >= d.tile_base[k + 1]) ++k;
-  const int S = d.S[k];
-  const int tl = b - d.tile_base[k], tpr = (S + 7) / 8;
-  const int oy = (tl / tpr) * 8, ox = (tl % tpr) * 8;
-  for (int e = threadIdx.x; e < 100 * cin; e += blockDim.x) {
-    const int pix = e / cin, c = e - pix * cin;
-    const int y = oy + pix / 10 - 1, x = ox + pix % 10 - 1;
-    float v = 0.0f;
-    if (y >= 0 && y < S && x >= 0 && x < S) v = dec_input<T>(d, k, S, y, x, c, pyr, periph, hnext);
-    sx[e] = v;
+  float* s_x = reinterpret_cast<float*>(smem);    // [10][18] pixels, padded channels
+  float* s_g = s_x + 180 * CS;                    // [8][16] pixels, 32 rows
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 15, kq = lane >> 4, rg = blockIdx.y;
+  v4f acc[2][NQ];
+  int off[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    acc[0][i] = acc[1][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    const int q = wave + 4 * i < 9 * NT ? wave + 4 * i : 0;
+    const int tap = q / NT;
+    off[i] = ((tap / 3) * 18 + tap % 3) * CS + (q - tap * NT) * 16;
   }
-  for (int e = threadIdx.x; e < 64 * 2 * K; e += blockDim.x) {
-    const int pix = e / (2 * K), r = e - pix * 2 * K;
-    const int y = oy + pix / 8, x = ox + pix % 8;
-    float v = 0.0f;
-    if (y < S && x < S) {
-      const int ch = r < K ? r : r - K, half = r < K ? 0 : 1;
-      v = dpre[d.pre_off[k] + ((long long)y * S + x) * d.nout + (ch / 16) * 32 + half * 16 + ch % 16];
+  // the last channel tile's zeros, which no pixel tile overwrites
+  for (int e = tid; e < 180 * 8; e += 256) s_x[(e >> 3) * CS + 16 * NT - 8 + (e & 7)] = 0.0f;
+  const int tiles = d.tile_base[d.n_crops];
+  const long long plane = (long long)d.W * d.H;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    int k = 0;
+    while (k + 1 < d.n_crops && tile >= d.tile_base[k + 1]) ++k;
+    const int S = d.S[k], tl = tile - d.tile_base[k];
+    const int oy = (tl / d.tiles_x[k]) * 8, ox = (tl % d.tiles_x[k]) * 16;
+    __syncthreads();
+    // upsampled channels, four per item: loads without branches (clamped
+    // places, the weights of pixels outside the layer zero), so that several
+    // items' loads are in flight
+    constexpr int KG = 4 * (NT - 1);
+    if (KG > 0) {
+      const int Sn = S >> 1;
+      const T* h = hnext + d.hn_off[k];
+#pragma unroll 3
+      for (int e = tid; e < 180 * KG; e += 256) {
+        const int pix = e / (KG > 0 ? KG : 1), n = (e - pix * KG) * 4;
+        const int y = oy + pix / 18 - 1, x = ox + pix % 18 - 1;
+        const bool in = y >= 0 && y < S && x >= 0 && x < S;
+        const int ya = (y - 1) >> 1, xa = (x - 1) >> 1;    // floor((y - 1/2) / 2)
+        const float fy = y & 1 ? 0.25f : 0.75f, fx = x & 1 ? 0.25f : 0.75f;
+        const int y0 = min(max(ya, 0), Sn - 1), y1 = min(max(ya + 1, 0), Sn - 1);
+        const int x0 = min(max(xa, 0), Sn - 1), x1 = min(max(xa + 1, 0), Sn - 1);
+        typedef T v4t __attribute__((ext_vector_type(4)));
+        const v4t a00 = *reinterpret_cast<const v4t*>(h + (y0 * Sn + x0) * (KG * 4) + n);
+        const v4t a01 = *reinterpret_cast<const v4t*>(h + (y0 * Sn + x1) * (KG * 4) + n);
+        const v4t a10 = *reinterpret_cast<const v4t*>(h + (y1 * Sn + x0) * (KG * 4) + n);
+        const v4t a11 = *reinterpret_cast<const v4t*>(h + (y1 * Sn + x1) * (KG * 4) + n);
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          v[i] = (1.0f - fy) * ((1.0f - fx) * to_f(a00[i]) + fx * to_f(a01[i])) +
+                 fy * ((1.0f - fx) * to_f(a10[i]) + fx * to_f(a11[i]));
+          v[i] = in ? v[i] : 0.0f;
+        }
+        *reinterpret_cast<float4*>(&s_x[pix * CS + 4 + n]) = make_float4(v[0], v[1], v[2], v[3]);
+      }
     }
-    sg[e] = v;
-  }
-  __syncthreads();
-  const int nw = 2 * K * 9 * cin;
-  for (int e = threadIdx.x; e < nw; e += blockDim.x) {
-    const int row = e / (9 * cin), rem = e - row * 9 * cin;
-    const int tap = rem / cin, c = rem - tap * cin;
-    const int ky = tap / 3, kx = tap - ky * 3;
-    float acc = 0.0f;
-    for (int pix = 0; pix < 64; ++pix) {
-      const int py = pix / 8, px = pix % 8;
-      acc += sg[pix * 2 * K + row] * sx[((py + ky) * 10 + px + kx) * cin + c];
+    // pyramid layer, periphery crop and the channel of ones
+    if (tid < 180) {
+      const int y = oy + tid / 18 - 1, x = ox + tid % 18 - 1;
+      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f}, w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (y >= 0 && y < S && x >= 0 && x < S) {
+        const float* p = pyr + d.pyr_off[k] + ((long long)y * S + x) * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = p[i];
+        if (d.has_p) {
+          const float* q = periph + (long long)d.view[k] * 3 * plane +
+                           (long long)(dec_y0(d, k) + y) * d.W + (dec_x0(d, k) + x);
+#pragma unroll
+          for (int i = 0; i < 3; ++i) w[i] = q[i * plane];
+        }
+        w[3] = 1.0f;
+      }
+      *reinterpret_cast<float4*>(&s_x[tid * CS]) = make_float4(v[0], v[1], v[2], v[3]);
+      *reinterpret_cast<float4*>(&s_x[tid * CS + 4 + KG * 4]) = make_float4(w[0], w[1], w[2], w[3]);
     }
-    if (acc != 0.0f) atomicAdd(&dw[e], acc);
+#pragma unroll
+    for (int e = tid; e < 128 * 8; e += 256) {
+      const int pix = e >> 3, q = e & 7;
+      const int y = oy + (pix >> 4), x = ox + (pix & 15);
+      float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (y < S && x < S)
+        v = *reinterpret_cast<const float4*>(dpre + d.pre_off[k] +
+                                             ((long long)y * S + x) * d.nout + rg * 32 + q * 4);
+      *reinterpret_cast<float4*>(&s_g[pix * kWgRows + q * 4]) = v;
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int ks = 0; ks < 32; ++ks) {
+      const float a0 = s_g[(ks * 4 + kq) * kWgRows + col];
+      const float a1 = s_g[(ks * 4 + kq) * kWgRows + 16 + col];
+      const float* xb = &s_x[((ks >> 2) * 18 + (ks & 3) * 4 + kq) * CS + col];
+      float bv[NQ];
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) bv[i] = xb[off[i]];
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        acc[0][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, bv[i], acc[0][i], 0, 0, 0);
+        acc[1][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, bv[i], acc[1][i], 0, 0, 0);
+      }
+    }
   }
-  for (int r = threadIdx.x; r < 2 * K; r += blockDim.x) {
-    float acc = 0.0f;
-    for (int pix = 0; pix < 64; ++pix) acc += sg[pix * 2 * K + r];
-    if (acc != 0.0f) atomicAdd(&db[r], acc);
+  // lane (col, kq) holds rows 4 kq + r of padded channel 16 ct + col
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const int q = wave + 4 * i;
+    if (q >= 9 * NT) break;
+    const int tap = q / NT, n = (q - tap * NT) * 16 + col;
+    const int oc = pad_to_orig(n, d.kn, d.kpn, d.has_p);
+    const bool ones = tap == 4 && n == 4 + d.kpn + 3;
+    if (oc < 0 && !ones) continue;
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ch = rg * 16 + 4 * kq + r;
+        if (ch >= d.width) continue;
+        const int row = m ? d.width + ch : ch;
+        atomicAdd(ones ? &db[row] : &dw[((long long)row * 9 + tap) * d.cin + oc], acc[m][i][r]);
+      }
   }
+}
+
+// The level's tiles of TH rows x 16 columns.
+static int level_tiles(DecLevel* d, int TH) {
+  int tb = 0;
+  for (int k = 0; k < d->n_crops; ++k) {
+    d->tile_base[k] = tb;
+    d->tiles_x[k] = (d->S[k] + 15) / 16;
+    tb += d->tiles_x[k] * ((d->S[k] + TH - 1) / TH);
+  }
+  d->tile_base[d->n_crops] = tb;
+  return tb;
+}
+
+// 16-row tiles where they still give every compute unit four workgroups,
+// 8-row tiles below (a level of 64 tiles would leave most of the chip idle).
+template <int NT>
+static hipError_t launch_dgrad(DecLevel d, const float* dpre, const float* wb, float* dpyr,
+                               float* dx, float* dper, hipStream_t st) {
+  int tiles = level_tiles(&d, 16);
+  if (tiles >= 4 * device_cus()) {
+    hipLaunchKernelGGL((k_dec_dgrad<NT, 4>), dim3(tiles), dim3(256), 0, st, d, dpre, wb, dpyr, dx,
+                       dper);
+  } else {
+    tiles = level_tiles(&d, 8);
+    hipLaunchKernelGGL((k_dec_dgrad<NT, 2>), dim3(tiles), dim3(256), 0, st, d, dpre, wb, dpyr, dx,
+                       dper);
+  }
+  return hipGetLastError();
+}
+
+// As many workgroups per compute unit as the LDS holds (three up to three
+// channel tiles, two above), so that one's loads run under another's matrix
+// steps; fewer where there are not that many pixel tiles.
+template <typename T, int NT>
+static hipError_t launch_wgrad(DecLevel d, const float* pyr, const float* periph, const T* hn,
+                               const float* dpre, float* dw, float* db, hipStream_t st) {
+  const int tiles = level_tiles(&d, 8), groups = d.nout / 32;
+  const int blocks = std::max(1, std::min(tiles, (NT <= 3 ? 3 : 2) * device_cus() / groups));
+  hipLaunchKernelGGL((k_dec_wgrad<T, NT>), dim3(blocks, groups), dim3(256), wg_smem<NT>(), st, d,
+                     pyr, periph, hn, dpre, dw, db);
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -1145,71 +1395,78 @@ static vrs_status decode_bwd_impl(const DecPlan& P, const float* pyramid, int le
                                   const float* weights, const float* d_fovea,
                                   float* d_pyr, float* d_per, float* d_w, void* ws,
                                   hipStream_t st) {
-  // recompute every level's pre-activations (the forward's h_l stay valid)
-  for (int l = P.nd - 1; l >= 0; --l) {
-    DecLevel d;
-    int blocks = 0;
-    level_args(P, l, crops, n_crops, kv, levels, place, &d, &blocks);
-    const T* hn = l + 1 < P.nd ? at<T>(ws, P.h[l + 1]) : nullptr;
-    VRS_HIP_CHECK(launch_conv<T>(d, 2 * P.kp[l] / 16, blocks, pyramid, periph, hn,
-                                 at<T>(ws, P.wp[l]), at<float>(ws, P.bp[l]), at<T>(ws, P.h[l]),
-                                 at<float>(ws, P.pre[l]), HeadFuse{}, st));
-    VRS_HIP_CHECK(fill_u32(at<uint32_t>(ws, P.dh[l]), 0u, P.h_elems[l], st));
-  }
-  // head
   {
-    HeadArgs ha;
-    ha.n_crops = n_crops;
-    ha.kp = P.kp[0];
-    ha.K0 = P.K[0];
-    long long p = 0, o = 0;
-    DecLevel d0;
-    int b0 = 0;
-    level_args(P, 0, crops, n_crops, kv, levels, place, &d0, &b0);
-    for (int k = 0; k < n_crops; ++k) {
-      ha.S[k] = crops[k].size;
-      ha.pix_base[k] = p;
-      ha.out_base[k] = o;
-      ha.h_off[k] = d0.h_off[k];
-      p += (long long)crops[k].size * crops[k].size;
-      o += 3LL * crops[k].size * crops[k].size;
+    PackBwdArgs pa;
+    pa.n = P.nd;
+    long long s = 0;
+    for (int l = 0; l < P.nd; ++l) {
+      pa.K[l] = P.K[l];
+      pa.kn[l] = l + 1 < P.nd ? P.K[l + 1] : 0;
+      pa.kpn[l] = l + 1 < P.nd ? P.kp[l + 1] : 0;
+      pa.cin[l] = P.cin[l];
+      pa.w[l] = weights + P.w_off[l];
+      pa.wb[l] = at<float>(ws, P.wb[l]);
+      pa.start[l] = s;
+      s += P.wb_elems(l);
     }
-    ha.pix_base[n_crops] = p;
-    hipLaunchKernelGGL(k_dec_head_bwd<T>, dim3((unsigned)((p + 255) / 256)), dim3(256), 0, st, ha,
-                       at<T>(ws, P.h[0]), weights + P.head_w, d_fovea, at<float>(ws, P.dh[0]),
-                       d_w ? d_w + P.head_w : nullptr, d_w ? d_w + P.head_b : nullptr);
+    pa.start[P.nd] = s;
+    hipLaunchKernelGGL(k_dec_pack_bwd, dim3((unsigned)std::min<long long>(1024, (s + 255) / 256)),
+                       dim3(256), 0, st, pa);
     VRS_LAUNCH_CHECK();
   }
+  float *dpre = at<float>(ws, P.pre), *dx = at<float>(ws, P.dx);
   for (int l = 0; l < P.nd; ++l) {
     DecLevel d;
     int blocks = 0;
     level_args(P, l, crops, n_crops, kv, levels, place, &d, &blocks);
-    long long npix = 0;
-    for (int k = 0; k < n_crops; ++k) npix += (long long)d.S[k] * d.S[k];
-    const int gb = (int)std::min<long long>(16384, (npix * P.kp[l] + 255) / 256);
-    hipLaunchKernelGGL(k_dec_gate_bwd, dim3(gb), dim3(256), 0, st, at<float>(ws, P.pre[l]),
-                       at<float>(ws, P.dh[l]), npix, P.kp[l], P.K[l]);
+    // the level's pre-activations again (the forward's h_l stay valid)
+    const T* hn = l + 1 < P.nd ? at<T>(ws, P.h[l + 1]) : nullptr;
+    VRS_HIP_CHECK(launch_conv<T>(d, 2 * P.kp[l] / 16, blocks, pyramid, periph, hn,
+                                 at<T>(ws, P.wp[l]), at<float>(ws, P.bp[l]), at<T>(ws, P.h[l]),
+                                 dpre, HeadFuse{}, st));
+    GateArgs ga;
+    ga.n_crops = n_crops;
+    ga.kp = P.kp[l];
+    ga.K = P.K[l];
+    long long p = 0, o = 0;
+    for (int k = 0; k < n_crops; ++k) {
+      ga.S[k] = d.S[k];
+      ga.pix_base[k] = p;
+      ga.out_base[k] = o;
+      p += (long long)d.S[k] * d.S[k];
+      o += 3LL * d.S[k] * d.S[k];
+    }
+    ga.pix_base[n_crops] = p;
+    const int per = 256 / (ga.kp / 4);
+    if (l == 0) {
+      // few workgroups: each ends with an atomic per head weight
+      const int gb = (int)std::min<long long>(8 * device_cus(), (p + per - 1) / per);
+      hipLaunchKernelGGL((k_dec_gate_bwd<T, true>), dim3(gb), dim3(256), 0, st, ga, dpre, nullptr,
+                         at<T>(ws, P.h[0]), weights + P.head_w, d_fovea,
+                         d_w ? d_w + P.head_w : nullptr, d_w ? d_w + P.head_b : nullptr);
+    } else {
+      const int gb = (int)std::min<long long>(16384, (p + per - 1) / per);
+      hipLaunchKernelGGL((k_dec_gate_bwd<T, false>), dim3(gb), dim3(256), 0, st, ga, dpre, dx,
+                         (const T*)nullptr, nullptr, nullptr, nullptr, nullptr);
+    }
     VRS_LAUNCH_CHECK();
-    const int dbk = (int)std::min<long long>(16384, (npix * P.cin[l] + 255) / 256);
-    hipLaunchKernelGGL(k_dec_dgrad<T>, dim3(dbk), dim3(256), 0, st, d, at<float>(ws, P.pre[l]),
-                       weights + P.w_off[l], d_pyr,
-                       l + 1 < P.nd ? at<float>(ws, P.dh[l + 1]) : nullptr, d_per);
-    VRS_LAUNCH_CHECK();
-    if (d_w) {
-      DecLevel dw8 = d;
-      int tb = 0;
-      for (int k = 0; k < n_crops; ++k) {
-        dw8.tile_base[k] = tb;
-        const int t = (d.S[k] + 7) / 8;
-        tb += t * t;
+    const float* wb = at<float>(ws, P.wb[l]);
+    float* dw = d_w ? d_w + P.w_off[l] : nullptr;
+    float* db = d_w ? d_w + P.b_off[l] : nullptr;
+    auto level = [&](auto nt) -> hipError_t {
+      constexpr int NT = decltype(nt)::value;
+      if (dw) {
+        const hipError_t e = launch_wgrad<T, NT>(d, pyramid, periph, hn, dpre, dw, db, st);
+        if (e != hipSuccess) return e;
       }
-      dw8.tile_base[n_crops] = tb;
-      const size_t smem = (size_t)(100 * P.cin[l] + 64 * 2 * P.K[l]) * 4;
-      if (smem > 64 * 1024) return VRS_EUNSUPPORTED;
-      const T* hn = l + 1 < P.nd ? at<T>(ws, P.h[l + 1]) : nullptr;
-      hipLaunchKernelGGL(k_dec_wgrad<T>, dim3(tb), dim3(256), smem, st, dw8, pyramid, periph, hn,
-                         at<float>(ws, P.pre[l]), d_w + P.w_off[l], d_w + P.b_off[l]);
-      VRS_LAUNCH_CHECK();
+      return launch_dgrad<NT>(d, dpre, wb, d_pyr, dx, d_per, st);
+    };
+    switch (d.kpn / 16 + 1) {
+      case 1: VRS_HIP_CHECK(level(std::integral_constant<int, 1>{})); break;
+      case 2: VRS_HIP_CHECK(level(std::integral_constant<int, 2>{})); break;
+      case 3: VRS_HIP_CHECK(level(std::integral_constant<int, 3>{})); break;
+      case 4: VRS_HIP_CHECK(level(std::integral_constant<int, 4>{})); break;
+      default: VRS_HIP_CHECK(level(std::integral_constant<int, 5>{})); break;
     }
   }
   return VRS_OK;
