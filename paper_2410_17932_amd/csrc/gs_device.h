@@ -189,6 +189,34 @@ __device__ inline float gs_alpha(const float4& a, const float4& b, float xc, flo
   return fminf(b.y * e, aclamp);
 }
 
+// A lane flag as the wave's mask (bit l = lane l) and back: the mask lives
+// in scalar registers and every combination of flags is a scalar operation.
+__device__ inline uint64_t wave_mask(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ inline bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Lower bound of G(d) = ga dx^2 + gb dx dy + gc dy^2 (positive definite)
+// over the box dx in [X0, X1], dy in [Y0, Y1]: 0 if the box holds the
+// origin, else the least of the four edge minima (the minimiser of a convex
+// quadratic over a box lies on its boundary; on an edge it is the clamped
+// stationary point).  ia, ic = 1 / (2 ga), 1 / (2 gc): a stationary point off
+// by a relative rounding error changes the edge minimum by its square, far
+// inside the caller's margin.
+__device__ inline float box_min_quadratic(float ga, float gb, float gc, float ia, float ic,
+                                          float X0, float X1, float Y0, float Y1) {
+  if (X0 <= 0.0f && X1 >= 0.0f && Y0 <= 0.0f && Y1 >= 0.0f) return 0.0f;
+  float m = 3.0e38f;
+  float Xe[2] = {X0, X1}, Ye[2] = {Y0, Y1};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float X = Xe[i];
+    const float dy = fminf(fmaxf(-gb * X * ic, Y0), Y1);
+    m = fminf(m, ga * X * X + gb * X * dy + gc * dy * dy);
+    const float Y = Ye[i];
+    const float dx = fminf(fmaxf(-gb * Y * ia, X0), X1);
+    m = fminf(m, ga * dx * dx + gb * dx * Y + gc * Y * Y);
+  }
+  return m;
+}
+
 // Packed rectangle: low 16 bits x, high 16 bits y.
 __device__ inline uint32_t pack_xy(int x, int y) { return (uint32_t)x | ((uint32_t)y << 16); }
 
