@@ -657,11 +657,13 @@ __global__ __launch_bounds__(kEmitBlock) void k_pt_emit(
 
 // Each fragment's record (point index, depth key, weight, pixel) to its
 // segment place (checked against the segment, so an unresolved place can
-// never write outside it).
+// never write outside it).  The place replaces the fragment's slot and, once
+// the fragment is ranked, its final place the record's pixel: the adjoint's
+// way from a point's fragments to the sorted lists.
 __global__ __launch_bounds__(256) void k_pt_scatter(const uint32_t* __restrict__ fkey,
                                                     const uint64_t* __restrict__ fval,
                                                     const uint32_t* __restrict__ fdep,
-                                                    const uint32_t* __restrict__ fslot,
+                                                    uint32_t* __restrict__ fslot,
                                                     const uint32_t* __restrict__ poff,
                                                     const uint32_t* __restrict__ total_p,
                                                     int64_t max_frags, uint4* __restrict__ seg) {
@@ -673,8 +675,12 @@ __global__ __launch_bounds__(256) void k_pt_scatter(const uint32_t* __restrict__
     const uint64_t v = fval[i];
     const uint32_t at = poff[px] + fslot[i];
     if (at < poff[px + 1]) seg[at] = make_uint4((uint32_t)v, fdep[i], (uint32_t)(v >> 32), px);
+    fslot[i] = at;
   }
 }
+
+// Fragments per layer pixel above which k_pt_resolve ranks and blends.
+constexpr int64_t kRsDense = 12;
 
 // One thread per segment place: the record's final place is its segment's
 // offset plus the number of the segment's records before it in (depth key,
@@ -685,7 +691,7 @@ __global__ __launch_bounds__(256) void k_pt_scatter(const uint32_t* __restrict__
 // Consecutive places share segments, so the lanes of a segment read the
 // same records; places go in reverse, so that the long segments of each
 // crop's coarse layers start early.
-__global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
+__global__ __launch_bounds__(256) void k_pt_rank(uint4* seg,
                                                  const uint32_t* __restrict__ poff,
                                                  const uint32_t* __restrict__ total_p,
                                                  int64_t max_frags, int64_t pix_total,
@@ -693,7 +699,7 @@ __global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
                                                  uint32_t* __restrict__ okey,
                                                  uint64_t* __restrict__ oval) {
   const int64_t total = *total_p;
-  if (total > max_frags) return;
+  if (total > max_frags || total > kRsDense * pix_total) return;
   const uint64_t* key = reinterpret_cast<const uint64_t*>(seg);   // depth key << 32 | index
   for (int64_t sr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; sr < total;
        sr += (int64_t)gridDim.x * blockDim.x) {
@@ -734,6 +740,7 @@ __global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
     }
     okey[start + rank] = rec.w;
     oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
+    seg[total - 1 - sr].w = start + rank;   // read by this thread alone
   }
 }
 
@@ -749,6 +756,8 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
                                                   const uint16_t* __restrict__ feat,
                                                   const float* __restrict__ opacity, int64_t np,
                                                   int64_t pix_total, float4* __restrict__ pyr) {
+  // dense lists are k_pt_resolve's (launched wherever the capacity allows them)
+  if (min((int64_t)*total_p, max_frags) > kRsDense * pix_total) return;
   const bool over = (int64_t)*total_p > max_frags;
   for (int64_t kr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; kr < pix_total;
        kr += (int64_t)gridDim.x * blockDim.x) {
@@ -804,15 +813,16 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
 // list order, a channel per lane (the same operations in the same order as
 // k_pt_blend, so the results are the same to the bit): 0.93 ms.
 //
-// Chosen where the capacity is over kRsDense fragments per layer pixel: one
-// 512 crop, whole splat, this kernel against the two: 435 us against 325 at
-// 6.6 fragments per pixel, 622 against 704 at 13, 3.2 ms against 11.8 at 77
-// (a wave per pixel idles on short lists).
-constexpr int64_t kRsDense = 12;
+// It takes the splats that counted over kRsDense fragments per layer pixel;
+// the count is on the device, so where the capacity allows that many all three
+// kernels are launched and those not meant leave at once.  One 512 crop,
+// whole splat, this kernel against the two: 435 us against 325 at 6.6
+// fragments per pixel, 622 against 704 at 13, 3.2 ms against 11.8 at 77 (a
+// wave per pixel idles on short lists).
 constexpr int kRsCap = 4096, kRsBuckets = 1024, kRsPix = 4;   // pixels per workgroup, one wave each
 
 __global__ __launch_bounds__(256) void k_pt_resolve(
-    const uint4* __restrict__ seg, const uint32_t* __restrict__ poff,
+    uint4* seg, const uint32_t* __restrict__ poff,
     const uint32_t* __restrict__ total_p, int64_t max_frags, int64_t pix_total,
     const uint32_t* __restrict__ ids, const uint16_t* __restrict__ feat,
     const float* __restrict__ opacity, int64_t np, uint32_t* __restrict__ okey,
@@ -821,207 +831,214 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
   __shared__ uint32_t s_cur[kRsBuckets];   // bucket starts, advanced to their ends by the placing
   __shared__ uint32_t s_n[kRsPix], s_w[4], s_v[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t total = *total_p;
+  if (total <= kRsDense * pix_total) return;
+  const bool over = total > max_frags;
   // pixels in reverse: the coarse layers' long lists start early
-  const int64_t k0 = pix_total - kRsPix * ((int64_t)blockIdx.x + 1);
-  const bool over = (int64_t)*total_p > max_frags;
-  const int64_t kw = k0 + wave;   // the wave's pixel
-  uint32_t start_w = 0, nw = 0;
-  if (kw >= 0 && !over) {
-    start_w = poff[kw];
-    nw = poff[kw + 1] - start_w;
-  }
-  if (lane == 0) s_n[wave] = nw;
-  if (nw <= 64 && lane < (int)nw) {
-    // one fragment per lane, ranked against each other in registers
-    const uint4 rec = seg[start_w + lane];
-    uint32_t rank = 0, same = 0;
-    for (uint32_t j = 0; j < nw; ++j) {
-      const uint32_t d = __builtin_amdgcn_readlane(rec.y, j);
-      rank += d < rec.y ? 1u : 0u;
-      same += d == rec.y ? 1u : 0u;
+  for (int64_t k0 = pix_total - kRsPix * ((int64_t)blockIdx.x + 1); k0 > -kRsPix;
+       k0 -= kRsPix * (int64_t)gridDim.x) {
+    const int64_t kw = k0 + wave;   // the wave's pixel
+    uint32_t start_w = 0, nw = 0;
+    if (kw >= 0 && !over) {
+      start_w = poff[kw];
+      nw = poff[kw + 1] - start_w;
     }
-    if (__ballot(same > 1)) {   // equal depths: the points' own order
-      const uint32_t own = ids ? ids[rec.x] : rec.x;
-      for (uint32_t j = 0; j < nw; ++j)
-        rank += (uint32_t)__builtin_amdgcn_readlane(rec.y, j) == rec.y &&
-                        (uint32_t)__builtin_amdgcn_readlane(own, j) < own
-                    ? 1u : 0u;
-    }
-    okey[start_w + rank] = (uint32_t)kw;
-    oval[start_w + rank] = ((uint64_t)rec.z << 32) | rec.x;
-  }
-  __syncthreads();
-  for (int w = 0; w < kRsPix; ++w) {
-    const uint32_t n = s_n[w];
-    if (n <= 64) continue;   // uniform over the workgroup
-    const int64_t k = k0 + w;
-    const uint32_t start = poff[k];
-    const uint4* sg = seg + start;
-    // range of the depth keys
-    uint32_t lo = ~0u, hi = 0u;
-    for (uint32_t i = tid; i < n; i += 256) {
-      const uint32_t d = sg[i].y;
-      lo = min(lo, d);
-      hi = max(hi, d);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
-      hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
-    }
-    if (lane == 0) {
-      s_w[wave] = lo;
-      s_v[wave] = hi;
-    }
-    for (int b = tid; b < kRsBuckets; b += 256) s_cur[b] = 0;
-    __syncthreads();
-    lo = min(min(s_w[0], s_w[1]), min(s_w[2], s_w[3]));
-    hi = max(max(s_v[0], s_v[1]), max(s_v[2], s_v[3]));
-    // bucket of a key: every step is monotone, so buckets are in key order
-    const float scale = (float)kRsBuckets / ((float)(hi - lo) + 1.0f);
-    auto bucket = [&](uint32_t d) {
-      return min((int)((float)(d - lo) * scale), kRsBuckets - 1);
-    };
-    for (uint32_t i = tid; i < n; i += 256) atomicAdd(&s_cur[bucket(sg[i].y)], 1u);
-    __syncthreads();
-    // exclusive scan of the counts, four buckets per thread
-    {
-      uint32_t c[4], sum = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        c[q] = s_cur[tid * 4 + q];
-        sum += c[q];
+    if (lane == 0) s_n[wave] = nw;
+    if (nw <= 64 && lane < (int)nw) {
+      // one fragment per lane, ranked against each other in registers
+      const uint4 rec = seg[start_w + lane];
+      uint32_t rank = 0, same = 0;
+      for (uint32_t j = 0; j < nw; ++j) {
+        const uint32_t d = __builtin_amdgcn_readlane(rec.y, j);
+        rank += d < rec.y ? 1u : 0u;
+        same += d == rec.y ? 1u : 0u;
       }
-      uint32_t inc = sum;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
-        if (lane >= o) inc += t;
+      if (__ballot(same > 1)) {   // equal depths: the points' own order
+        const uint32_t own = ids ? ids[rec.x] : rec.x;
+        for (uint32_t j = 0; j < nw; ++j)
+          rank += (uint32_t)__builtin_amdgcn_readlane(rec.y, j) == rec.y &&
+                          (uint32_t)__builtin_amdgcn_readlane(own, j) < own
+                      ? 1u : 0u;
       }
-      __syncthreads();   // s_w is read above
-      if (lane == 63) s_w[wave] = inc;
+      okey[start_w + rank] = (uint32_t)kw;
+      oval[start_w + rank] = ((uint64_t)rec.z << 32) | rec.x;
+      seg[start_w + lane].w = start_w + rank;
+    }
+    __syncthreads();
+    for (int w = 0; w < kRsPix; ++w) {
+      const uint32_t n = s_n[w];
+      if (n <= 64) continue;   // uniform over the workgroup
+      const int64_t k = k0 + w;
+      const uint32_t start = poff[k];
+      uint4* sg = seg + start;
+      // range of the depth keys
+      uint32_t lo = ~0u, hi = 0u;
+      for (uint32_t i = tid; i < n; i += 256) {
+        const uint32_t d = sg[i].y;
+        lo = min(lo, d);
+        hi = max(hi, d);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+      }
+      if (lane == 0) {
+        s_w[wave] = lo;
+        s_v[wave] = hi;
+      }
+      for (int b = tid; b < kRsBuckets; b += 256) s_cur[b] = 0;
       __syncthreads();
-      uint32_t base = inc - sum;
-      for (int q = 0; q < wave; ++q) base += s_w[q];
+      lo = min(min(s_w[0], s_w[1]), min(s_w[2], s_w[3]));
+      hi = max(max(s_v[0], s_v[1]), max(s_v[2], s_v[3]));
+      // bucket of a key: every step is monotone, so buckets are in key order
+      const float scale = (float)kRsBuckets / ((float)(hi - lo) + 1.0f);
+      auto bucket = [&](uint32_t d) {
+        return min((int)((float)(d - lo) * scale), kRsBuckets - 1);
+      };
+      for (uint32_t i = tid; i < n; i += 256) atomicAdd(&s_cur[bucket(sg[i].y)], 1u);
+      __syncthreads();
+      // exclusive scan of the counts, four buckets per thread
+      {
+        uint32_t c[4], sum = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        s_cur[tid * 4 + q] = base;
-        base += c[q];
-      }
-    }
-    __syncthreads();
-    // buckets [b0, b1) whose fragments fit the LDS at a time: all of them
-    // for segments up to kRsCap
-    uint32_t done = 0;   // fragments of the buckets before b0
-    for (int b0 = 0; b0 < kRsBuckets && done < n;) {
-      int b1 = kRsBuckets;
-      if (n - done > kRsCap) {
-        int most = b0 + 1;
-        for (int b = tid * 4; b < tid * 4 + 4; ++b)
-          if (b > b0 && s_cur[b] - done <= kRsCap) most = max(most, b);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
-        __syncthreads();
-        if (lane == 0) s_w[wave] = (uint32_t)most;
-        __syncthreads();
-        b1 = (int)max(max(s_w[0], s_w[1]), max(s_w[2], s_w[3]));
-      }
-      const uint32_t cnt = (b1 < kRsBuckets ? s_cur[b1] : n) - done;
-      __syncthreads();   // b1's start is read before any placing moves a cursor
-      if (cnt <= kRsCap) {
-        for (uint32_t i = tid; i < n; i += 256) {
-          const uint32_t d = sg[i].y;
-          const int b = bucket(d);
-          if (b >= b0 && b < b1)
-            s_key[atomicAdd(&s_cur[b], 1u) - done] = ((uint64_t)d << 32) | i;
+        for (int q = 0; q < 4; ++q) {
+          c[q] = s_cur[tid * 4 + q];
+          sum += c[q];
         }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
+          if (lane >= o) inc += t;
+        }
+        __syncthreads();   // s_w is read above
+        if (lane == 63) s_w[wave] = inc;
         __syncthreads();
-        for (uint32_t p = tid; p < cnt; p += 256) {
-          const uint64_t e = s_key[p];
-          const uint32_t d = (uint32_t)(e >> 32);
-          const int b = bucket(d);
-          const uint32_t first = b == b0 ? 0u : s_cur[b - 1] - done, last = s_cur[b] - done;
-          const uint4 rec = sg[(uint32_t)e];
-          uint32_t rank = done + first;
-          for (uint32_t q = first; q < last; ++q) {
-            const uint64_t f = s_key[q];
-            const uint32_t df = (uint32_t)(f >> 32);
-            rank += df < d ? 1u : 0u;
-            if (df == d && q != p) {   // equal depths: the points' own order
-              const uint32_t x = sg[(uint32_t)f].x;
-              rank += (ids ? ids[x] : x) < (ids ? ids[rec.x] : rec.x) ? 1u : 0u;
+        uint32_t base = inc - sum;
+        for (int q = 0; q < wave; ++q) base += s_w[q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          s_cur[tid * 4 + q] = base;
+          base += c[q];
+        }
+      }
+      __syncthreads();
+      // buckets [b0, b1) whose fragments fit the LDS at a time: all of them
+      // for segments up to kRsCap
+      uint32_t done = 0;   // fragments of the buckets before b0
+      for (int b0 = 0; b0 < kRsBuckets && done < n;) {
+        int b1 = kRsBuckets;
+        if (n - done > kRsCap) {
+          int most = b0 + 1;
+          for (int b = tid * 4; b < tid * 4 + 4; ++b)
+            if (b > b0 && s_cur[b] - done <= kRsCap) most = max(most, b);
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+          __syncthreads();
+          if (lane == 0) s_w[wave] = (uint32_t)most;
+          __syncthreads();
+          b1 = (int)max(max(s_w[0], s_w[1]), max(s_w[2], s_w[3]));
+        }
+        const uint32_t cnt = (b1 < kRsBuckets ? s_cur[b1] : n) - done;
+        __syncthreads();   // b1's start is read before any placing moves a cursor
+        if (cnt <= kRsCap) {
+          for (uint32_t i = tid; i < n; i += 256) {
+            const uint32_t d = sg[i].y;
+            const int b = bucket(d);
+            if (b >= b0 && b < b1)
+              s_key[atomicAdd(&s_cur[b], 1u) - done] = ((uint64_t)d << 32) | i;
+          }
+          __syncthreads();
+          for (uint32_t p = tid; p < cnt; p += 256) {
+            const uint64_t e = s_key[p];
+            const uint32_t d = (uint32_t)(e >> 32);
+            const int b = bucket(d);
+            const uint32_t first = b == b0 ? 0u : s_cur[b - 1] - done, last = s_cur[b] - done;
+            const uint4 rec = sg[(uint32_t)e];
+            uint32_t rank = done + first;
+            for (uint32_t q = first; q < last; ++q) {
+              const uint64_t f = s_key[q];
+              const uint32_t df = (uint32_t)(f >> 32);
+              rank += df < d ? 1u : 0u;
+              if (df == d && q != p) {   // equal depths: the points' own order
+                const uint32_t x = sg[(uint32_t)f].x;
+                rank += (ids ? ids[x] : x) < (ids ? ids[rec.x] : rec.x) ? 1u : 0u;
+              }
             }
+            okey[start + rank] = (uint32_t)k;
+            oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
+            sg[(uint32_t)e].w = start + rank;
           }
-          okey[start + rank] = (uint32_t)k;
-          oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
-        }
-      } else {
-        // one bucket beyond the LDS (thousands of nearly equal depths)
-        for (uint32_t i = tid; i < n; i += 256) {
-          const uint4 rec = sg[i];
-          if (bucket(rec.y) != b0) continue;
-          uint32_t rank = done;
-          for (uint32_t j = 0; j < n; ++j) {
-            const uint4 o = sg[j];
-            if (o.y > rec.y || bucket(o.y) != b0 || j == i) continue;
-            rank += o.y < rec.y || (ids ? ids[o.x] : o.x) < (ids ? ids[rec.x] : rec.x) ? 1u : 0u;
+        } else {
+          // one bucket beyond the LDS (thousands of nearly equal depths)
+          for (uint32_t i = tid; i < n; i += 256) {
+            const uint4 rec = sg[i];
+            if (bucket(rec.y) != b0) continue;
+            uint32_t rank = done;
+            for (uint32_t j = 0; j < n; ++j) {
+              const uint4 o = sg[j];
+              if (o.y > rec.y || bucket(o.y) != b0 || j == i) continue;
+              rank += o.y < rec.y || (ids ? ids[o.x] : o.x) < (ids ? ids[rec.x] : rec.x) ? 1u : 0u;
+            }
+            okey[start + rank] = (uint32_t)k;
+            oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
+            sg[i].w = start + rank;
           }
-          okey[start + rank] = (uint32_t)k;
-          oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
         }
+        __syncthreads();
+        done += cnt;
+        b0 = b1;
       }
-      __syncthreads();
-      done += cnt;
-      b0 = b1;
     }
-  }
-  __syncthreads();   // the sorted lists are written, s_key is free
-  if (kw < 0) return;
-  // weights, 1 - weights and four features of 64 fragments, per wave
-  float* st = reinterpret_cast<float*>(s_key) + wave * (6 * 64);
-  const uint64_t* list = oval + start_w;
-  const int ch = lane & 3;
-  float F = 0.0f, T = 1.0f;
-  uint64_t v = lane < (int)nw ? list[lane] : ~0ull;
-  for (uint32_t j0 = 0; j0 < nw; j0 += 64) {
-    const uint32_t id = (uint32_t)v;
-    const bool ok = id < (uint64_t)np;
-    const float w = __uint_as_float((uint32_t)(v >> 32));
-    float al = 0.0f;
-    uint2 hb = make_uint2(0, 0);
-    if (ok) {
-      al = opacity ? w * opacity[id] : w;
-      hb = *reinterpret_cast<const uint2*>(feat + (int64_t)id * 4);
-    }
-    v = j0 + 64 + lane < nw ? list[j0 + 64 + lane] : ~0ull;
-    st[lane] = al;
-    st[64 + lane] = 1.0f - al;
-    st[128 + lane] = h2f((uint16_t)(hb.x & 0xffffu));
-    st[192 + lane] = h2f((uint16_t)(hb.x >> 16));
-    st[256 + lane] = h2f((uint16_t)(hb.y & 0xffffu));
-    st[320 + lane] = h2f((uint16_t)(hb.y >> 16));
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // (lanes past the list hold weight 0 and leave both sums as they are)
-    const int cnt = (int)min(nw - j0, 64u);
+    __syncthreads();   // the sorted lists are written, s_key is free
+    // weights, 1 - weights and four features of 64 fragments, per wave
+    float* st = reinterpret_cast<float*>(s_key) + wave * (6 * 64);
+    const uint64_t* list = oval + start_w;
+    const int ch = lane & 3;
+    float F = 0.0f, T = 1.0f;
+    uint64_t v = lane < (int)nw ? list[lane] : ~0ull;
+    for (uint32_t j0 = 0; j0 < nw; j0 += 64) {
+      const uint32_t id = (uint32_t)v;
+      const bool ok = id < (uint64_t)np;
+      const float w = __uint_as_float((uint32_t)(v >> 32));
+      float al = 0.0f;
+      uint2 hb = make_uint2(0, 0);
+      if (ok) {
+        al = opacity ? w * opacity[id] : w;
+        hb = *reinterpret_cast<const uint2*>(feat + (int64_t)id * 4);
+      }
+      v = j0 + 64 + lane < nw ? list[j0 + 64 + lane] : ~0ull;
+      st[lane] = al;
+      st[64 + lane] = 1.0f - al;
+      st[128 + lane] = h2f((uint16_t)(hb.x & 0xffffu));
+      st[192 + lane] = h2f((uint16_t)(hb.x >> 16));
+      st[256 + lane] = h2f((uint16_t)(hb.y & 0xffffu));
+      st[320 + lane] = h2f((uint16_t)(hb.y >> 16));
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // (lanes past the list hold weight 0 and leave both sums as they are)
+      const int cnt = (int)min(nw - j0, 64u);
 #pragma unroll 4
-    for (int i = 0; i < cnt; i += 4) {
-      const float4 a4 = *reinterpret_cast<const float4*>(st + i);
-      const float4 o4 = *reinterpret_cast<const float4*>(st + 64 + i);
-      const float4 h4 = *reinterpret_cast<const float4*>(st + 128 + ch * 64 + i);
-      const float a[4] = {a4.x, a4.y, a4.z, a4.w}, o[4] = {o4.x, o4.y, o4.z, o4.w};
-      const float h[4] = {h4.x, h4.y, h4.z, h4.w};
+      for (int i = 0; i < cnt; i += 4) {
+        const float4 a4 = *reinterpret_cast<const float4*>(st + i);
+        const float4 o4 = *reinterpret_cast<const float4*>(st + 64 + i);
+        const float4 h4 = *reinterpret_cast<const float4*>(st + 128 + ch * 64 + i);
+        const float a[4] = {a4.x, a4.y, a4.z, a4.w}, o[4] = {o4.x, o4.y, o4.z, o4.w};
+        const float h[4] = {h4.x, h4.y, h4.z, h4.w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float aT = a[q] * T;
-        F += h[q] * aT;
-        T = T * o[q];
+        for (int q = 0; q < 4; ++q) {
+          const float aT = a[q] * T;
+          F += h[q] * aT;
+          T = T * o[q];
+        }
       }
+      __builtin_amdgcn_wave_barrier();   // read before the next batch's stores
     }
-    __builtin_amdgcn_wave_barrier();   // read before the next batch's stores
+    if (lane < 4 && kw >= 0) reinterpret_cast<float*>(pyr + kw)[lane] = F;
+    __syncthreads();   // the shared words are reused by the next pixels
   }
-  if (lane < 4) reinterpret_cast<float*>(pyr + kw)[lane] = F;
 }
 
 __global__ void k_zero4(float4* p, int64_t n) {
@@ -1158,16 +1175,15 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
                      at<uint32_t>(ws, L.fslot), poff, frag_count, max_frags,
                      at<uint4>(ws, L.seg));
   VRS_LAUNCH_CHECK();
-  // long lists are ranked and blended together, short ones by a thread per
-  // fragment and per pixel
+  // long lists are ranked and blended together (four workgroups per compute
+  // unit, what the LDS holds), short ones by a thread per fragment and pixel
   if (max_frags > kRsDense * L.pix_total) {
-    hipLaunchKernelGGL(k_pt_resolve, dim3((unsigned)div_up(L.pix_total, kRsPix)), dim3(256), 0, st,
-                       at<uint4>(ws, L.seg), poff, frag_count, max_frags, L.pix_total, point_ids,
-                       feat, opacity, np, at<uint32_t>(ws, L.fkey1), at<uint64_t>(ws, L.fval1),
+    const unsigned rb = (unsigned)std::min<int64_t>(4 * device_cus(), div_up(L.pix_total, kRsPix));
+    hipLaunchKernelGGL(k_pt_resolve, dim3(rb), dim3(256), 0, st, at<uint4>(ws, L.seg), poff,
+                       frag_count, max_frags, L.pix_total, point_ids, feat, opacity, np,
+                       at<uint32_t>(ws, L.fkey1), at<uint64_t>(ws, L.fval1),
                        reinterpret_cast<float4*>(pyramid));
     VRS_LAUNCH_CHECK();
-    trace_end(tr, VRS_TRACE_SPLAT, st);
-    return VRS_OK;
   }
   hipLaunchKernelGGL(k_pt_rank, dim3(fb), dim3(256), 0, st, at<uint4>(ws, L.seg), poff,
                      frag_count, max_frags, L.pix_total, point_ids, at<uint32_t>(ws, L.fkey1),
@@ -1200,126 +1216,228 @@ extern "C" vrs_status vrs_splat_points(const float* pos, const float* radius,
 // ------------------------------------------------------------- backward
 namespace vrs {
 
-// Segment heads replay their pixel's list: a forward walk finds the final
-// transmittance (and the first fully opaque fragment, after which nothing is
-// visible), then a backward walk recovers T before each fragment as
-// T / (1 - alpha) and accumulates
-//   dfeat = alpha T dF,  dalpha = T (feat - acc) . dF,  acc = feat alpha + (1 - alpha) acc
-// Fragment weights are recomputed from the point to carry dalpha into the
-// position and radius (trilinear weight = layer weight x bilinear weight).
-__global__ __launch_bounds__(256) void k_pt_blend_bwd(
-    const uint32_t* __restrict__ fkey, const uint64_t* __restrict__ fval,
-    const uint32_t* __restrict__ total_p, int64_t max_frags, const float* __restrict__ pos,
-    const float* __restrict__ radius, const uint16_t* __restrict__ feat,
-    const float* __restrict__ opacity, int64_t np, KViews views, KCrops crops, PtArgs a,
-    int64_t pix_total, const float4* __restrict__ dpyr, float* __restrict__ d_feat,
-    float* __restrict__ d_pos, float* __restrict__ d_radius, float* __restrict__ d_opacity) {
-  const int64_t cnt = std::min<int64_t>(*total_p, max_frags);
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < cnt;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t key = fkey[i];
-    if (i > 0 && fkey[i - 1] == key) continue;
-    if (key >= (uint64_t)pix_total) continue;
-    const float4 g = dpyr[key];
-    // locate crop, layer and pixel of this key
-    int k = 0;
-    while (k + 1 < crops.n && (int)key >= crops.c[k + 1].pix_base) ++k;
-    const KCrop& c = crops.c[k];
-    int l = 0, lb = c.pix_base;
-    while (l + 1 < a.levels && (int)key >= lb + (c.size >> l) * (c.size >> l)) {
-      lb += (c.size >> l) * (c.size >> l);
-      ++l;
-    }
-    const int Sl = c.size >> l;
-    const int xx = ((int)key - lb) % Sl, yy = ((int)key - lb) / Sl;
-    // forward walk
-    int64_t j = i, jend = i;
-    float T = 1.0f;
-    while (jend < cnt && fkey[jend] == key) {
-      const uint64_t vv = fval[jend];
-      const uint32_t id = (uint32_t)vv;
-      const float w = __uint_as_float((uint32_t)(vv >> 32));
-      const float al = opacity && id < (uint64_t)np ? w * opacity[id] : w;
-      ++jend;
-      if (al >= 1.0f) { T = 0.0f; break; }   // fully opaque: nothing behind is visible
-      T = T * (1.0f - al);
-    }
-    // backward walk over [i, jend)
-    float acc[4] = {0, 0, 0, 0};
-    bool opaque_end = T == 0.0f;
-    for (j = jend - 1; j >= i; --j) {
-      const uint64_t vv = fval[j];
-      const uint32_t id = (uint32_t)vv;
-      if (id >= (uint64_t)np) continue;
-      const float w = __uint_as_float((uint32_t)(vv >> 32));
-      const float o = opacity ? opacity[id] : 1.0f;
-      const float al = w * o;
-      float Tb;
-      if ((opaque_end && j == jend - 1) || !(1.0f - al >= 0.5f)) {
-        // T before an opaque or nearly opaque fragment: the product of the
-        // ones in front (dividing by a small 1 - alpha would amplify error)
-        Tb = 1.0f;
-        for (int64_t q = i; q < j; ++q) {
-          const uint64_t u = fval[q];
-          const uint32_t iq = (uint32_t)u;
-          const float wq = __uint_as_float((uint32_t)(u >> 32));
-          Tb *= 1.0f - (opacity && iq < (uint64_t)np ? wq * opacity[iq] : wq);
-        }
-      } else {
-        Tb = T / (1.0f - al);
-      }
-      const uint2 hb = *reinterpret_cast<const uint2*>(feat + (int64_t)id * 4);
-      const float f[4] = {h2f((uint16_t)(hb.x & 0xffffu)), h2f((uint16_t)(hb.x >> 16)),
-                          h2f((uint16_t)(hb.y & 0xffffu)), h2f((uint16_t)(hb.y >> 16))};
-      const float gg[4] = {g.x, g.y, g.z, g.w};
-      float dal = 0.0f;
+// The adjoint in two kernels.  With G = feat . dF and A the same product for
+// the colour behind a fragment, a fragment's feature gradient is alpha T dF and
+// its alpha's is T (G - A), T the transmittance before it.  T is a prefix
+// product of 1 - alpha over the pixel's list and A a suffix composition of
+// A -> alpha G + (1 - alpha) A, so 16 lanes take a pixel and scan 16 fragments
+// at a time (row shifts); a fully opaque fragment (alpha >= 1) cuts both.  The
+// second kernel gathers a point's fragments and carries them into the point.
+// Both are latency-bound.  Fitting workload (2M points, four 512 crops): one
+// thread walking each list took 864 us, the two take 165.
+constexpr int kPbLanes = 16;
+
+template <int CTRL>
+__device__ inline float row_shift(float v, float edge) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), CTRL,
+                                                    0xf, 0xf, false));
+}
+
+__global__ __launch_bounds__(256) void k_pt_scan_bwd(
+    const uint64_t* __restrict__ fval, const uint32_t* __restrict__ poff,
+    const uint32_t* __restrict__ total_p, int64_t max_frags, const uint16_t* __restrict__ feat,
+    const float* __restrict__ opacity, int64_t np, int64_t pix_total,
+    const float4* __restrict__ dpyr, float2* res) {
+  if ((int64_t)*total_p > max_frags) return;
+  const int lane = threadIdx.x & 63, li = lane % kPbLanes, row = lane / kPbLanes;
+  // a wave looks at 64 pixels, one per lane, and takes those that hold
+  // fragments four at a time, one per row of lanes (most pixels hold none)
+  for (int64_t p0 = (blockIdx.x * (int64_t)256 + threadIdx.x - lane); p0 < pix_total;
+       p0 += (int64_t)gridDim.x * 256) {
+    const uint32_t start_l = p0 + lane < pix_total ? poff[p0 + lane] : 0u;
+    const uint32_t n_l = p0 + lane < pix_total ? poff[p0 + lane + 1] - start_l : 0u;
+    for (uint64_t m = __ballot(n_l > 0); m;) {
+      int at = -1;
 #pragma unroll
-      for (int ch = 0; ch < 4; ++ch) {
-        if (d_feat) atomicAdd(&d_feat[(int64_t)id * 4 + ch], al * Tb * gg[ch]);
-        dal += Tb * (f[ch] - acc[ch]) * gg[ch];
-        acc[ch] = f[ch] * al + (1.0f - al) * acc[ch];
+      for (int r = 0; r < 64 / kPbLanes; ++r) {
+        if (row == r && m) at = __builtin_ctzll(m);
+        m &= m - 1;   // (stays 0 once empty)
       }
-      T = Tb;
-      if (d_opacity && opacity) atomicAdd(&d_opacity[id], dal * w);
-      const float dw = dal * o;
-      if ((d_pos || d_radius) && dw != 0.0f) {
-        const KView& cv = views.v[c.view];
-        PtGeom pg;
-        if (!pt_geom32(cv, pos[id], pos[np + id], pos[2 * np + id], radius[id], a.levels, pg))
-          continue;
+      const uint32_t start = (uint32_t)__shfl((int)start_l, at, 64);
+      const int n_at = __shfl((int)n_l, at, 64);   // by every lane: the source is any of them
+      const int n = at < 0 ? 0 : n_at;
+      const int64_t p = p0 + at;
+      if (n == 0) continue;
+      const float4 g = dpyr[p];
+      const int last = (n - 1) / kPbLanes;
+      // alpha, 1 - alpha (0 from an opaque one on) and T of the lane's fragment
+      // in chunk c; T0: before the chunk, advanced past it
+      float al = 0.0f, om = 1.0f, G = 0.0f, Tb = 0.0f, T0 = 1.0f;
+      auto load = [&](int c) {
+        const int j = c * kPbLanes + li;
+        al = 0.0f;
+        om = 1.0f;
+        G = 0.0f;
+        if (j < n) {
+          const uint64_t v = fval[start + j];
+          const uint32_t id = (uint32_t)v;
+          if (id < (uint64_t)np) {
+            const float w = __uint_as_float((uint32_t)(v >> 32));
+            al = opacity ? w * opacity[id] : w;
+            om = al >= 1.0f ? 0.0f : 1.0f - al;
+            const uint2 hb = *reinterpret_cast<const uint2*>(feat + (int64_t)id * 4);
+            G = h2f((uint16_t)(hb.x & 0xffffu)) * g.x + h2f((uint16_t)(hb.x >> 16)) * g.y +
+                h2f((uint16_t)(hb.y & 0xffffu)) * g.z + h2f((uint16_t)(hb.y >> 16)) * g.w;
+          }
+        }
+      };
+      auto scan_T = [&]() {
+        float q = om;   // inclusive products over the row: row_shr 1, 2, 4, 8
+        q *= row_shift<0x111>(q, 1.0f);
+        q *= row_shift<0x112>(q, 1.0f);
+        q *= row_shift<0x114>(q, 1.0f);
+        q *= row_shift<0x118>(q, 1.0f);
+        Tb = T0 * row_shift<0x111>(q, 1.0f);
+        T0 *= __shfl(q, kPbLanes - 1, kPbLanes);
+      };
+      // the chunks before the last leave T for the walk back
+      for (int c = 0; c <= last; ++c) {
+        load(c);
+        scan_T();
+        if (c < last) res[start + c * kPbLanes + li].x = Tb;
+      }
+      float Aend = 0.0f;   // A behind the chunk
+      for (int c = last; c >= 0; --c) {
+        if (c < last) {
+          load(c);
+          Tb = res[start + c * kPbLanes + li].x;
+        }
+        // suffix compositions of A -> b + a A over the row: row_shl 1, 2, 4, 8
+        float a = om, b = al * G;
+        b = fmaf(a, row_shift<0x101>(b, 0.0f), b);
+        a *= row_shift<0x101>(a, 1.0f);
+        b = fmaf(a, row_shift<0x102>(b, 0.0f), b);
+        a *= row_shift<0x102>(a, 1.0f);
+        b = fmaf(a, row_shift<0x104>(b, 0.0f), b);
+        a *= row_shift<0x104>(a, 1.0f);
+        b = fmaf(a, row_shift<0x108>(b, 0.0f), b);
+        a *= row_shift<0x108>(a, 1.0f);
+        const float here = fmaf(a, Aend, b);   // A before the lane's fragment
+        const float A = row_shift<0x101>(here, Aend);
+        Aend = __shfl(here, 0, kPbLanes);
+        const int j = c * kPbLanes + li;
+        if (j < n) res[start + j] = make_float2(al * Tb, Tb * (G - A));
+      }
+    }
+  }
+}
+
+// A quad of lanes per survivor walks its crops and layers as the emission
+// did, a lane per footprint target, so that the target's fragment is the next
+// of the survivor's in emission order; its place in the sorted lists is
+// fslot -> seg.w.  The quad's sums go out once per survivor (two atomic
+// instructions) instead of eight scattered atomics per fragment, which bound
+// the per-fragment form (726 us against 91).
+// res: each sorted fragment's alpha T and alpha gradient.
+template <int CTRL>
+__device__ inline float quad_add(float v) {
+  return v + __int_as_float(
+                 __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ inline float quad_sum(float v) { return quad_add<0x4E>(quad_add<0xB1>(v)); }
+
+__global__ __launch_bounds__(256) void k_pt_blend_bwd(
+    const uint4* __restrict__ surv, const uint32_t* __restrict__ live_p,
+    const uint32_t* __restrict__ total_p, int64_t max_frags, const uint32_t* __restrict__ fslot,
+    const uint4* __restrict__ seg, const float* __restrict__ pos,
+    const float* __restrict__ radius, const float* __restrict__ opacity, int64_t np, KViews views,
+    KCrops crops, PtArgs a, const uint32_t* __restrict__ grid, int gx, int gy,
+    const float4* __restrict__ dpyr, const float2* __restrict__ res, float* __restrict__ d_feat,
+    float* __restrict__ d_pos, float* __restrict__ d_radius, float* __restrict__ d_opacity) {
+  __shared__ int s_cx0[VRS_MAX_CROPS], s_cy0[VRS_MAX_CROPS], s_cs[VRS_MAX_CROPS],
+      s_pb[VRS_MAX_CROPS];
+  if (threadIdx.x < crops.n) {
+    s_cx0[threadIdx.x] = crop_x0(crops, threadIdx.x);
+    s_cy0[threadIdx.x] = crop_y0(crops, threadIdx.x);
+    s_cs[threadIdx.x] = crops.c[threadIdx.x].size;
+    s_pb[threadIdx.x] = crops.c[threadIdx.x].pix_base;
+  }
+  __syncthreads();
+  const int64_t total = *total_p, live = *live_p;
+  if (total > max_frags) return;
+  const int q = threadIdx.x & 3, dx = q & 1, dy = q >> 1;
+  for (int64_t j = (blockIdx.x * (int64_t)256 + threadIdx.x) >> 2; j < live;
+       j += (int64_t)gridDim.x * 64) {
+    const uint4 sv = surv[j];
+    const int v = (int)(sv.x / np);
+    const int64_t i = sv.x - (int64_t)v * np;
+    const KView& cv = views.v[v];
+    const float x = pos[i], y = pos[np + i], z = pos[2 * np + i];
+    PtGeom g;
+    if (!pt_geom32(cv, x, y, z, radius[i], a.levels, g)) continue;
+    const float o = opacity ? opacity[i] : 1.0f;
+    float f = 0.0f;
+    if (g.two) f = log2f(g.s) - (float)g.l0;
+    FF ux, uy;
+    pt_plane_ff(cv, x, y, z, ux, uy);
+    // the lane's sums: features, the point's opacity, pixel position, size
+    float df[4] = {0, 0, 0, 0}, dop = 0.0f, dpx = 0.0f, dpy = 0.0f, ds = 0.0f;
+    int64_t at = sv.z;   // the survivor's next fragment
+    for (uint32_t cand = pt_candidates(cv, v, crops.n, grid, gx, gy, x, y, z); cand;
+         cand &= cand - 1) {
+      const int k = __builtin_ctz(cand);
+      const int cx0 = s_cx0[k], cy0 = s_cy0[k], size = s_cs[k];
+      int lb = s_pb[k];
+      int l = 0;
+      for (; l < g.l0; ++l) lb += (size >> l) * (size >> l);
+      for (int li = 0; li < (g.two ? 2 : 1); ++li, ++l) {
+        const int Sl = size >> l;
         float xl, yl;
         int ix, iy;
-        const int cx0 = crop_x0(crops, k), cy0 = crop_y0(crops, k);
-        if (!pt_layer32(pg, cx0, cy0, l, Sl, xl, yl, ix, iy)) continue;
-        FF ux, uy;
-        pt_plane_ff(cv, pos[id], pos[np + id], pos[2 * np + id], ux, uy);
-        const float bx = pt_frac_ff(cv.fx, ux, cv.cx, cx0, l, ix);
-        const float by = pt_frac_ff(cv.fy, uy, cv.cy, cy0, l, iy);
-        const int dx = xx - ix, dy = yy - iy;
-        const float wx = dx ? bx : 1.0f - bx, wy = dy ? by : 1.0f - by;
-        float f2 = 0.0f, wl = 1.0f;
-        if (pg.two) {
-          f2 = log2f(pg.s) - (float)pg.l0;
-          wl = l == pg.l0 ? 1.0f - f2 : f2;
+        if (pt_layer32(g, cx0, cy0, l, Sl, xl, yl, ix, iy)) {
+          const bool x0 = ix >= 0, x1 = ix + 1 < Sl, y0 = iy >= 0, y1 = iy + 1 < Sl;
+          const int nx = (x0 ? 1 : 0) + (x1 ? 1 : 0);
+          if ((dx ? x1 : x0) && (dy ? y1 : y0)) {
+            const int64_t e = at + (dy && y0 ? nx : 0) + (dx && x0 ? 1 : 0);
+            const uint32_t place = e < total ? fslot[e] : ~0u;
+            const uint32_t fin = place < total ? seg[place].w : ~0u;
+            if (fin < total) {
+              const float2 r = res[fin];
+              const float4 gp = dpyr[lb + (iy + dy) * Sl + ix + dx];
+              df[0] = fmaf(r.x, gp.x, df[0]);
+              df[1] = fmaf(r.x, gp.y, df[1]);
+              df[2] = fmaf(r.x, gp.z, df[2]);
+              df[3] = fmaf(r.x, gp.w, df[3]);
+              const float bx = pt_frac_ff(cv.fx, ux, cv.cx, cx0, l, ix);
+              const float by = pt_frac_ff(cv.fy, uy, cv.cy, cy0, l, iy);
+              const float wx = dx ? bx : 1.0f - bx, wy = dy ? by : 1.0f - by;
+              const float wl = g.two ? (li == 0 ? 1.0f - f : f) : 1.0f;
+              const float dw = r.y * o;
+              dop = fmaf(r.y, wl * (wx * wy), dop);
+              // trilinear weight: layer weight x bilinear weight
+              const float sc = ldexpf(1.0f, -l);
+              dpx += dw * wl * wy * (dx ? sc : -sc);
+              dpy += dw * wl * wx * (dy ? sc : -sc);
+              if (g.two) ds += (li == 0 ? -dw : dw) * wx * wy / (g.s * 0.69314718055994531f);
+            }
+          }
+          at += nx * ((y0 ? 1 : 0) + (y1 ? 1 : 0));
         }
-        const float dwl = dw * wx * wy;
-        const float sc = ldexpf(1.0f, -l);
-        const float dpx = dw * wl * wy * (dx ? 1.0f : -1.0f) * sc;
-        const float dpy = dw * wl * wx * (dy ? 1.0f : -1.0f) * sc;
-        float ds = 0.0f;
-        if (pg.two) ds = (l == pg.l0 ? -dwl : dwl) / (pg.s * 0.69314718055994531f);
-        const float tz = pg.t[2];
-        const float dr = ds * 2.0f * cv.fx / tz;
-        float dt0 = dpx * cv.fx / tz, dt1 = dpy * cv.fy / tz;
-        float dt2 = -dpx * cv.fx * pg.t[0] / (tz * tz) - dpy * cv.fy * pg.t[1] / (tz * tz) -
-                    ds * pg.s / tz;
-        if (d_radius) atomicAdd(&d_radius[id], dr);
-        if (d_pos)
-#pragma unroll
-          for (int q = 0; q < 3; ++q)
-            atomicAdd(&d_pos[q * np + id], cv.R[q] * dt0 + cv.R[3 + q] * dt1 + cv.R[6 + q] * dt2);
+        lb += Sl * Sl;
       }
     }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) df[c] = quad_sum(df[c]);
+    dop = quad_sum(dop);
+    dpx = quad_sum(dpx);
+    dpy = quad_sum(dpy);
+    ds = quad_sum(ds);
+    // lane q: feature q, position q (q < 3) or the radius
+    if (d_feat) {
+      const float m = q == 0 ? df[0] : (q == 1 ? df[1] : (q == 2 ? df[2] : df[3]));
+      if (m != 0.0f) atomicAdd(&d_feat[i * 4 + q], m);
+    }
+    const float tz = g.t[2];
+    const float dt0 = dpx * cv.fx / tz, dt1 = dpy * cv.fy / tz;
+    const float dt2 = -dpx * cv.fx * g.t[0] / (tz * tz) - dpy * cv.fy * g.t[1] / (tz * tz) -
+                      ds * g.s / tz;
+    const int qr = q < 3 ? q : 0;
+    const float m = q < 3 ? cv.R[qr] * dt0 + cv.R[3 + qr] * dt1 + cv.R[6 + qr] * dt2
+                          : ds * 2.0f * cv.fx / tz;
+    float* to = q < 3 ? (d_pos ? d_pos + q * np + i : nullptr)
+                      : (d_radius ? d_radius + i : nullptr);
+    if (to && m != 0.0f) atomicAdd(to, m);
+    if (d_opacity && opacity && q == 0) atomicAdd(&d_opacity[i], dop);
   }
 }
 
@@ -1353,12 +1471,22 @@ extern "C" vrs_status vrs_splat_points_backward(const float* pos, const float* r
   a.view_mask = 0;
   for (int k = 0; k < n_crops; ++k) a.view_mask |= 1u << crops[k].view;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int bb = (int)std::min<int64_t>(8192, std::max(1, div_up(max_frags, 256)));
-  hipLaunchKernelGGL(k_pt_blend_bwd, dim3(bb), dim3(256), 0, st,
-                     at<uint32_t>(ws, L.fkey1), at<uint64_t>(ws, L.fval1),
-                     at<uint32_t>(ws, L.frag_count), max_frags, pos, radius, feat, opacity, np, kv,
-                     kc, a, L.pix_total, reinterpret_cast<const float4*>(d_pyramid), d_feat, d_pos,
-                     d_radius, d_opacity);
+  // the emission's weights are free: two numbers per fragment there
+  float2* res = at<float2>(ws, L.fval0);
+  const int sb = (int)std::min<int64_t>(16384, div_up(L.pix_total, 256));
+  hipLaunchKernelGGL(k_pt_scan_bwd, dim3(sb), dim3(256), 0, st, at<uint64_t>(ws, L.fval1),
+                     at<uint32_t>(ws, L.poff), at<uint32_t>(ws, L.frag_count), max_frags, feat,
+                     opacity, np, L.pix_total, reinterpret_cast<const float4*>(d_pyramid), res);
+  VRS_LAUNCH_CHECK();
+  // no more survivors than fragments or (view, point) pairs
+  const int bb = (int)std::min<int64_t>(
+      8192, std::max(1, div_up(std::min<int64_t>(max_frags, L.vn), 64)));
+  hipLaunchKernelGGL(k_pt_blend_bwd, dim3(bb), dim3(256), 0, st, at<uint4>(ws, L.surv),
+                     at<uint32_t>(ws, L.live), at<uint32_t>(ws, L.frag_count), max_frags,
+                     at<uint32_t>(ws, L.fslot), at<uint4>(ws, L.seg), pos, radius, opacity, np, kv,
+                     kc, a, at<uint32_t>(ws, L.grid), L.gx, L.gy,
+                     reinterpret_cast<const float4*>(d_pyramid), res, d_feat, d_pos, d_radius,
+                     d_opacity);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
 }
