@@ -13,6 +13,10 @@ constexpr int kSuper = 8;
 // the bucket cursors.
 constexpr int kSchedHist = 0, kSchedDone = 256, kSchedCursor = 320, kSchedWords = 576;
 
+// Per-pixel order: 16-byte words per (view, Gaussian) of key coefficients
+// (three used: each entry is one 64-byte line, fetched by four lanes).
+constexpr int kPcStride = 4;
+
 struct RenderWs {
   size_t rec, rect, dkey0, dval0, dkey1, dval1, nsup, nsorted, soffs, psum, pair_count, super_count,
       skey0, sval0, skey1, sval1,   // (super-tile, Gaussian) pairs
@@ -106,7 +110,7 @@ inline bool render_layout(int64_t n, int nv, const vrs_view* views, int tile, in
     // the tile lists' bound words (64-bit): the pair sort's value buffer,
     // free once the binning has scattered it
     L->tkey = L->sval0;
-    L->pcoef = c.take((size_t)vn * 48);
+    L->pcoef = c.take((size_t)vn * kPcStride * 16);
     L->fix_list = c.take((size_t)std::max<int64_t>(L->npix, 1) * 4);
     L->fix_count = c.take(4);
   }
