@@ -233,126 +233,257 @@ __global__ __launch_bounds__(256) void k_composite4_inplace(CompArgs a, float* i
   comp_quad(a, io, F, io, v, y, x, pl, near);
 }
 
-// Adjoint.  Per pixel the crop chain is replayed forward to recover the
-// intermediate images, then walked backwards:
+// Adjoint.  With g the gradient of the image after crop k's blend,
 //   dF_k += c_k g,  dc_k = <g, F_k - out_{k-1}>,  g <- (1 - c_k) g,  dP += g.
-// In PAPER mode dc_k also flows into F_k through the Sobel edge term
-// (scattered to the 3x3 neighbourhood with atomics).
-__global__ __launch_bounds__(256) void k_composite_bwd(CompArgs a, const float* __restrict__ P,
-                                                       const float* __restrict__ F,
-                                                       const float* __restrict__ dout,
-                                                       float* __restrict__ dP,
-                                                       float* __restrict__ dF) {
-  const long long plane = (long long)a.W * a.H;
-  const long long total = plane * a.nv;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int v = (int)(i / plane);
-    const long long pi = i - v * plane;
-    const int y = (int)(pi / a.W), x = (int)(pi - (long long)y * a.W);
-    const long long base = (long long)v * 3 * plane + pi;
-    int ks[VRS_MAX_CROPS];
-    int nk = 0;
+// In PAPER mode dc_k also flows into F_k through the Sobel edge term.  Two
+// kernels: the periphery's gradient per view pixel, and each crop's per crop
+// pixel (one thread owns each gradient element, so nothing is atomic).  A
+// pixel under several crops walks those, and recomputes their masks, in both.
+// Four 1024 x 1024 views with a 512 crop each, with the edge term: 48 us and 28
+// us (together 155 with per-pixel chains in scratch memory and 27 atomics per
+// edge pixel).
+
+// The crops of view v over pixel (x, y), as bits (of those in `cand`).
+__device__ inline uint32_t comp_over(const CompArgs& a, int v, int x, int y, uint32_t cand) {
+  uint32_t m = 0;
+  for (; cand; cand &= cand - 1) {
+    const int k = __builtin_ctz(cand);
+    if (a.view[k] != v) continue;
+    const int lx = x - cx0(a, k), ly = y - cy0(a, k);
+    if (lx >= 0 && ly >= 0 && lx < a.S[k] && ly < a.S[k]) m |= 1u << k;
+  }
+  return m;
+}
+// Whether the mask may be non-zero at distance r from the gaze: inside the
+// inscribed circle, where the edge term can only raise S2's argument.
+__device__ inline bool comp_inside(const CompArgs& a, int k, float r) {
+  return r < 0.5f * (float)a.S[k] || (a.mode == VRS_BLEND_PAPER && a.gamma < 0.0f);
+}
+// Blend mask of crop k at view pixel (x, y); no Sobel work where it is 0.
+__device__ inline float comp_mask(const CompArgs& a, int k, const float* __restrict__ F, int x,
+                                  int y) {
+  const float dx = (float)x + 0.5f - cgx(a, k), dy = (float)y + 0.5f - cgy(a, k);
+  if (!comp_inside(a, k, sqrtf(dx * dx + dy * dy))) return 0.0f;
+  float u, gx, gy;
+  return blend_mask(a, k, F + a.fbase[k], x - cx0(a, k), y - cy0(a, k), u, gx, gy, a.place);
+}
+
+// VEC pixels of a row per thread (4 where rows and pointers allow).
+template <int VEC>
+__global__ __launch_bounds__(256) void k_composite_bwd_p(CompArgs a, const float* __restrict__ F,
+                                                         const float* __restrict__ dout,
+                                                         float* __restrict__ dP) {
+  const long long plane = (long long)a.W * a.H, per = plane / VEC;
+  const uint32_t all = a.n_crops >= 32 ? ~0u : (1u << a.n_crops) - 1u;
+  const int v = blockIdx.y;
+  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < per; i += (long long)gridDim.x * 256) {
+    const long long pi = i * VEC;
+    const int y = plane >> 32 ? (int)(pi / a.W) : (int)((uint32_t)pi / (uint32_t)a.W);
+    const int x = (int)(pi - (long long)y * a.W);
+    // the crops over any of the pixels
+    uint32_t near = 0;
     for (int k = 0; k < a.n_crops; ++k) {
       if (a.view[k] != v) continue;
       const int lx = x - cx0(a, k), ly = y - cy0(a, k);
-      if (lx < 0 || ly < 0 || lx >= a.S[k] || ly >= a.S[k]) continue;
-      ks[nk++] = k;
+      if (ly >= 0 && ly < a.S[k] && lx + VEC > 0 && lx < a.S[k]) near |= 1u << k;
     }
-    float g0 = dout[base], g1 = dout[base + plane], g2 = dout[base + 2 * plane];
-    if (nk > 0) {
-      // forward replay: o_j = image after crop j
-      float o[VRS_MAX_CROPS + 1][3];
-      float cs[VRS_MAX_CROPS], us[VRS_MAX_CROPS], gxs[VRS_MAX_CROPS], gys[VRS_MAX_CROPS];
-      o[0][0] = P[base]; o[0][1] = P[base + plane]; o[0][2] = P[base + 2 * plane];
-      for (int j = 0; j < nk; ++j) {
-        const int k = ks[j], S = a.S[k];
-        const int lx = x - cx0(a, k), ly = y - cy0(a, k);
-        const float* Fk = F + a.fbase[k];
-        cs[j] = blend_mask(a, k, Fk, lx, ly, us[j], gxs[j], gys[j], a.place);
-        const long long fp = (long long)S * S, fo = (long long)ly * S + lx;
-        for (int ch = 0; ch < 3; ++ch)
-          o[j + 1][ch] = (1.0f - cs[j]) * o[j][ch] + cs[j] * Fk[ch * fp + fo];
-      }
-      for (int j = nk - 1; j >= 0; --j) {
-        const int k = ks[j], S = a.S[k];
-        const int lx = x - cx0(a, k), ly = y - cy0(a, k);
-        const float* Fk = F + a.fbase[k];
-        const long long fp = (long long)S * S, fo = (long long)ly * S + lx;
-        const float c = cs[j];
-        const float f0 = Fk[fo], f1 = Fk[fp + fo], f2 = Fk[2 * fp + fo];
-        const float dc = g0 * (f0 - o[j][0]) + g1 * (f1 - o[j][1]) + g2 * (f2 - o[j][2]);
-        if (dF) {
-          float* dFk = dF + a.fbase[k];
-          if (a.mode == VRS_BLEND_PAPER) {
-            // neighbours scatter into this crop pixel too (edge term)
-            atomicAdd(&dFk[fo], c * g0);
-            atomicAdd(&dFk[fp + fo], c * g1);
-            atomicAdd(&dFk[2 * fp + fo], c * g2);
-          } else {
-            dFk[fo] += c * g0;
-            dFk[fp + fo] += c * g1;
-            dFk[2 * fp + fo] += c * g2;
-          }
-          const float u = us[j];
-          if (a.mode == VRS_BLEND_PAPER && u > 0.0f && u < 1.0f) {
-            // c = 1 - S2(u), u = fp + gamma |grad|/4
-            const float mag = sqrtf(gxs[j] * gxs[j] + gys[j] * gys[j]);
-            if (mag > 0.0f) {
-              const float dfe = -smootherstep_d(u) * a.gamma * dc;
-              const float s = dfe * 0.25f / mag / 3.0f;  // d|g|/dg = g/|g|; gray = mean/3
-              const float wx = s * gxs[j], wy = s * gys[j];
-              // Sobel taps: gx weights (+1,+2,+1 on x+1; -1,-2,-1 on x-1),
-              // gy weights (+1,+2,+1 on y+1; -1,-2,-1 on y-1)
-              for (int oy = -1; oy <= 1; ++oy)
-                for (int ox = -1; ox <= 1; ++ox) {
-                  const float kx = (float)ox * (oy == 0 ? 2.0f : 1.0f);
-                  const float ky = (float)oy * (ox == 0 ? 2.0f : 1.0f);
-                  const float wgt = kx * wx + ky * wy;
-                  if (wgt == 0.0f) continue;
-                  int sx = lx + ox, sy = ly + oy;
-                  sx = sx < 0 ? 0 : (sx > S - 1 ? S - 1 : sx);
-                  sy = sy < 0 ? 0 : (sy > S - 1 ? S - 1 : sy);
-                  const long long so = (long long)sy * S + sx;
-                  atomicAdd(&dFk[so], wgt);
-                  atomicAdd(&dFk[fp + so], wgt);
-                  atomicAdd(&dFk[2 * fp + so], wgt);
-                }
-            }
-          }
+    near &= all;
+    float f[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+      f[j] = 1.0f;
+      if (near)
+        for (uint32_t m = comp_over(a, v, x + j, y, near); m;) {   // last crop first
+          const int k = 31 - __builtin_clz(m);
+          m &= ~(1u << k);
+          f[j] *= 1.0f - comp_mask(a, k, F, x + j, y);
         }
-        g0 *= 1.0f - c;
-        g1 *= 1.0f - c;
-        g2 *= 1.0f - c;
-      }
     }
-    if (dP) {
-      dP[base] += g0;
-      dP[base + plane] += g1;
-      dP[base + 2 * plane] += g2;
+    const long long base = (long long)v * 3 * plane + pi;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float* o = dP + base + c * plane;
+      const float* g = dout + base + c * plane;
+      if constexpr (VEC == 4) {
+        const float4 d = *reinterpret_cast<const float4*>(o), e = *reinterpret_cast<const float4*>(g);
+        *reinterpret_cast<float4*>(o) = make_float4(fmaf(f[0], e.x, d.x), fmaf(f[1], e.y, d.y),
+                                                    fmaf(f[2], e.z, d.z), fmaf(f[3], e.w, d.w));
+      } else {
+        *o = fmaf(f[0], *g, *o);
+      }
     }
   }
 }
 
+// One 16 x 16 tile of crop blockIdx.y.  EDGE (PAPER mode with gamma): the
+// tile's grey values with two pixels around, the edge term's gradient in the
+// Sobel sums of every pixel with one around, gathered by the pixels it flows
+// into: tap (ox, oy) of pixel p lands on the pixel at p + o clamped into the
+// crop, so a border pixel also takes its own outward taps.
+template <bool EDGE>
+__global__ __launch_bounds__(256) void k_composite_bwd_f(CompArgs a, const float* __restrict__ P,
+                                                         const float* __restrict__ F,
+                                                         const float* __restrict__ dout,
+                                                         float* __restrict__ dF) {
+  constexpr int N = EDGE ? 18 : 16, OFF = EDGE ? 1 : 0;
+  __shared__ float s_gray[EDGE ? 20 : 1][21];
+  __shared__ float s_wx[EDGE ? 18 : 1][19], s_wy[EDGE ? 18 : 1][19];
+  __shared__ float s_d[3][16][17];
+  const int k = blockIdx.y, S = a.S[k], v = a.view[k];
+  const int nt = (S + 15) / 16;
+  if ((int)blockIdx.x >= nt * nt) return;
+  const int X0 = (int)blockIdx.x % nt * 16, Y0 = (int)blockIdx.x / nt * 16;
+  const int tid = threadIdx.x, ox0 = cx0(a, k), oy0 = cy0(a, k);
+  const long long plane = (long long)a.W * a.H, fp = (long long)S * S;
+  const float* Fk = F + a.fbase[k];
+  if constexpr (EDGE) {
+    for (int i = tid; i < 400; i += 256) s_gray[i / 20][i % 20] = gray_at(Fk, S, X0 + i % 20 - 2, Y0 + i / 20 - 2);
+    __syncthreads();
+  }
+  const uint32_t all = a.n_crops >= 32 ? ~0u : (1u << a.n_crops) - 1u;
+  for (int i = tid; i < N * N; i += 256) {
+    const int hx = i % N, hy = i / N;
+    const int lx = X0 + hx - OFF, ly = Y0 + hy - OFF;
+    float wx = 0.0f, wy = 0.0f, d[3] = {0, 0, 0};
+    if (lx >= 0 && ly >= 0 && lx < S && ly < S) {
+      const int x = ox0 + lx, y = oy0 + ly;
+      const long long base = (long long)v * 3 * plane + (long long)y * a.W + x;
+      float g[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) g[c] = dout[base + c * plane];
+      const uint32_t over = comp_over(a, v, x, y, all);
+      for (uint32_t m = over & ~((2u << k) - 1u); m;) {   // the later crops, last first
+        const int q = 31 - __builtin_clz(m);
+        m &= ~(1u << q);
+        const float f = 1.0f - comp_mask(a, q, F, x, y);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) g[c] *= f;
+      }
+      const long long fo = (long long)ly * S + lx;
+      if constexpr (!EDGE) {
+        const float c = comp_mask(a, k, F, x, y);
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) d[ch] = c * g[ch];
+      } else {
+        const float dx = (float)x + 0.5f - cgx(a, k), dy = (float)y + 0.5f - cgy(a, k);
+        const float r = sqrtf(dx * dx + dy * dy), df = 0.5f * (float)S;
+        if (comp_inside(a, k, r)) {
+          auto gr = [&](int ex, int ey) { return s_gray[hy + 1 + ey][hx + 1 + ex]; };
+          const float gx = (gr(1, -1) + 2.0f * gr(1, 0) + gr(1, 1)) -
+                           (gr(-1, -1) + 2.0f * gr(-1, 0) + gr(-1, 1));
+          const float gy = (gr(-1, 1) + 2.0f * gr(0, 1) + gr(1, 1)) -
+                           (gr(-1, -1) + 2.0f * gr(0, -1) + gr(1, -1));
+          const float mag = sqrtf(gx * gx + gy * gy);
+          const float u = (clamp01(r / df) - a.m) / (1.0f - a.m) + a.gamma * (0.25f * mag);
+          const float c = 1.0f - smootherstep(clamp01(u));
+#pragma unroll
+          for (int ch = 0; ch < 3; ++ch) d[ch] = c * g[ch];
+          if (u > 0.0f && u < 1.0f && mag > 0.0f) {
+            // the image before crop k
+            float o[3];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) o[ch] = P[base + ch * plane];
+            for (uint32_t m = over & ((1u << k) - 1u); m; m &= m - 1) {
+              const int q = __builtin_ctz(m), Sq = a.S[q];
+              const float cq = comp_mask(a, q, F, x, y);
+              const float* Fq = F + a.fbase[q];
+              const long long qo = (long long)(y - cy0(a, q)) * Sq + (x - cx0(a, q));
+#pragma unroll
+              for (int ch = 0; ch < 3; ++ch)
+                o[ch] = (1.0f - cq) * o[ch] + cq * Fq[ch * (long long)Sq * Sq + qo];
+            }
+            const float dc = g[0] * (Fk[fo] - o[0]) + g[1] * (Fk[fp + fo] - o[1]) +
+                             g[2] * (Fk[2 * fp + fo] - o[2]);
+            // c = 1 - S2(u), u = fp + gamma |grad| / 4; d|g|/dg = g/|g|; grey = mean / 3
+            const float s = -smootherstep_d(u) * a.gamma * dc * 0.25f / mag / 3.0f;
+            wx = s * gx;
+            wy = s * gy;
+          }
+        }
+      }
+    }
+    if constexpr (EDGE) {
+      s_wx[hy][hx] = wx;
+      s_wy[hy][hx] = wy;
+    }
+    const int cx = hx - OFF, cy = hy - OFF;
+    if (cx >= 0 && cy >= 0 && cx < 16 && cy < 16)
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) s_d[ch][cy][cx] = d[ch];
+  }
+  __syncthreads();
+  const int cx = tid & 15, cy = tid >> 4, lx = X0 + cx, ly = Y0 + cy;
+  if (lx >= S || ly >= S) return;
+  float e = 0.0f;
+  if constexpr (EDGE) {
+    // Sobel factors of the taps that land here from the pixel at offset d on
+    // one axis: the derivative's (-1, 0, 1) and the smoothing's (1, 2, 1)
+    auto deriv = [&](int d, int t) {
+      return d ? (float)-d : (t == S - 1 ? 1.0f : 0.0f) - (t == 0 ? 1.0f : 0.0f);
+    };
+    auto smooth = [&](int d, int t) {
+      return d ? 1.0f : 2.0f + (t == S - 1 ? 1.0f : 0.0f) + (t == 0 ? 1.0f : 0.0f);
+    };
+#pragma unroll
+    for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+      for (int dx = -1; dx <= 1; ++dx)   // (pixels outside the crop hold zeros)
+        e += deriv(dx, lx) * smooth(dy, ly) * s_wx[cy + 1 + dy][cx + 1 + dx] +
+             smooth(dx, lx) * deriv(dy, ly) * s_wy[cy + 1 + dy][cx + 1 + dx];
+  }
+  float* o = dF + a.fbase[k] + (long long)ly * S + lx;
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) o[ch * fp] += s_d[ch][cy][cx] + e;
+}
+
 // L1: block partial sums of |pred - target| atomically added to loss[0]
 // (zeroed by the preceding fill), gradient scale*sign(pred - target)/n.
+// HBM-bound; two workgroups per compute unit, since every one ends with an
+// atomic on the same word (about 11 ns each: 12.6M elements in 4096
+// workgroups took 65 us, 35 now).
+template <int VEC>
 __global__ __launch_bounds__(256) void k_l1(const float* __restrict__ pred,
                                             const float* __restrict__ target, long long n,
                                             float* loss, float* __restrict__ dpred, float scale) {
-  __shared__ float s_part[4];
-  float acc = 0.0f;
-  const float inv = 1.0f / (float)n;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const float d = pred[i] - target[i];
-    acc += fabsf(d);
-    if (dpred) dpred[i] += d > 0.0f ? scale * inv : (d < 0.0f ? -scale * inv : 0.0f);
+  __shared__ double s_part[4];
+  double acc = 0.0;
+  const float inv = 1.0f / (float)n, step = scale * inv;
+  const long long vn = n / VEC;
+  auto one = [&](float p, float t, float& g) {
+    const float d = p - t;
+    g = d > 0.0f ? step : (d < 0.0f ? -step : 0.0f);
+    return fabsf(d);
+  };
+  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < vn; i += (long long)gridDim.x * 256) {
+    if constexpr (VEC == 4) {
+      const float4 p = reinterpret_cast<const float4*>(pred)[i];
+      const float4 t = reinterpret_cast<const float4*>(target)[i];
+      float4 g;
+      acc += (double)((one(p.x, t.x, g.x) + one(p.y, t.y, g.y)) +
+                      (one(p.z, t.z, g.z) + one(p.w, t.w, g.w)));
+      if (dpred) {
+        float4 o = reinterpret_cast<float4*>(dpred)[i];
+        o.x += g.x; o.y += g.y; o.z += g.z; o.w += g.w;
+        reinterpret_cast<float4*>(dpred)[i] = o;
+      }
+    } else {
+      float g;
+      acc += (double)one(pred[i], target[i], g);
+      if (dpred) dpred[i] += g;
+    }
+  }
+  const long long tail = vn * VEC + blockIdx.x * 256LL + threadIdx.x;
+  if (tail < n) {   // fewer than VEC elements
+    float g;
+    acc += (double)one(pred[tail], target[tail], g);
+    if (dpred) dpred[tail] += g;
   }
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) s_part[wave] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(loss, (s_part[0] + s_part[1] + s_part[2] + s_part[3]) * inv);
+  if (threadIdx.x == 0)
+    atomicAdd(loss, (float)((s_part[0] + s_part[1] + s_part[2] + s_part[3]) / (double)n));
 }
 
 __global__ void k_zero1(float* p) { *p = 0.0f; }
@@ -457,12 +588,32 @@ extern "C" vrs_status vrs_composite_frame_backward(const float* rgb_periphery, i
   if (!comp_args(n_views, width, height, crops, n_crops, mode, ring, m, gamma, place, &a))
     return VRS_EINVAL;
   if (!rgb_periphery || !d_out || (n_crops > 0 && !fovea_rgb)) return VRS_EINVAL;
-  const long long total = (long long)width * height * n_views;
-  const int blocks = (int)std::min<long long>(16384, (total + 255) / 256);
-  hipLaunchKernelGGL(k_composite_bwd, dim3(blocks), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), a, rgb_periphery, fovea_rgb, d_out,
-                     d_rgb_periphery, d_fovea);
-  VRS_LAUNCH_CHECK();
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (d_rgb_periphery) {
+    const bool vec4 = width % 4 == 0 && ((reinterpret_cast<uintptr_t>(d_out) |
+                                          reinterpret_cast<uintptr_t>(d_rgb_periphery)) & 15) == 0;
+    const long long per = (long long)width * height / (vec4 ? 4 : 1);
+    const dim3 grid((unsigned)std::min<long long>(8192, (per + 255) / 256), n_views);
+    if (vec4)
+      hipLaunchKernelGGL(k_composite_bwd_p<4>, grid, dim3(256), 0, st, a, fovea_rgb, d_out,
+                         d_rgb_periphery);
+    else
+      hipLaunchKernelGGL(k_composite_bwd_p<1>, grid, dim3(256), 0, st, a, fovea_rgb, d_out,
+                         d_rgb_periphery);
+    VRS_LAUNCH_CHECK();
+  }
+  if (d_fovea && n_crops > 0) {
+    int most = 0;
+    for (int k = 0; k < n_crops; ++k) most = std::max(most, (crops[k].size + 15) / 16);
+    const dim3 grid((unsigned)(most * most), n_crops);
+    if (mode == VRS_BLEND_PAPER && gamma != 0.0f)
+      hipLaunchKernelGGL(k_composite_bwd_f<true>, grid, dim3(256), 0, st, a, rgb_periphery,
+                         fovea_rgb, d_out, d_fovea);
+    else
+      hipLaunchKernelGGL(k_composite_bwd_f<false>, grid, dim3(256), 0, st, a, rgb_periphery,
+                         fovea_rgb, d_out, d_fovea);
+    VRS_LAUNCH_CHECK();
+  }
   return VRS_OK;
 }
 
@@ -471,9 +622,16 @@ extern "C" vrs_status vrs_l1_loss(const float* pred, const float* target, int64_
   if (!pred || !target || !loss || n < 1) return VRS_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipLaunchKernelGGL(k_zero1, dim3(1), dim3(1), 0, st, loss);
-  const int blocks = (int)std::min<int64_t>(4096, (n + 255) / 256);
-  hipLaunchKernelGGL(k_l1, dim3(blocks), dim3(256), 0, st, pred, target, (long long)n, loss,
-                     d_pred, scale);
+  const bool vec4 = ((reinterpret_cast<uintptr_t>(pred) | reinterpret_cast<uintptr_t>(target) |
+                      reinterpret_cast<uintptr_t>(d_pred)) & 15) == 0;
+  const int blocks =
+      (int)std::min<int64_t>(2 * device_cus(), ((vec4 ? (n + 3) / 4 : n) + 255) / 256);
+  if (vec4)
+    hipLaunchKernelGGL(k_l1<4>, dim3(blocks), dim3(256), 0, st, pred, target, (long long)n, loss,
+                       d_pred, scale);
+  else
+    hipLaunchKernelGGL(k_l1<1>, dim3(blocks), dim3(256), 0, st, pred, target, (long long)n, loss,
+                       d_pred, scale);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
 }

@@ -15,7 +15,7 @@ namespace {
 
 // ------------------------------------------------------------ tone mapping
 constexpr int kTmFixed = 7, kTmMaxResp = 256;
-constexpr int kTmBlock = 256, kTmBlocksPerView = 1024;
+constexpr int kTmBlock = 256, kTmBlocksPerView = 1024, kTmBwdBlocks = 512;
 
 struct TmView {
   float cx, cy, inv_d2;   // principal point, rounded 1 / half-diagonal^2
@@ -108,49 +108,123 @@ __global__ __launch_bounds__(kTmBlock) void k_tonemap(const float* __restrict__ 
   }
 }
 
+// Row and column of element p of a W-wide plane (32-bit division wherever
+// the plane allows it).
+__device__ inline void tm_xy(int64_t p, int64_t plane, int W, int& x, int& y) {
+  if (plane >> 32) {
+    y = (int)(p / W);
+  } else {
+    y = (int)((uint32_t)p / (uint32_t)W);
+  }
+  x = (int)(p - (int64_t)y * W);
+}
+
 // Adjoint: d_in written; per block partial sums of the parameters'
-// gradients, [view][block][7 + n].
+// gradients, [view][block][7 + n].  HBM-bound (12 B per element) once the
+// response's gradient leaves the LDS atomics: those run at about one lane per
+// four clocks, however the samples are spread, and held the kernel at 148 us
+// for four 1024 x 1024 views.  Up to kTmLaneSamples samples every lane has a
+// column of its own instead and adds to it by plain reads and writes
+// (39 us); longer responses, whose columns would leave few waves in
+// flight, keep atomics on one copy.
+constexpr int kTmLaneSamples = 48;   // 12 KB of LDS per wave
+__host__ __device__ constexpr bool tm_lanes(int n) { return n <= kTmLaneSamples; }
+__host__ constexpr int tm_lds(int n) {
+  return (tm_lanes(n) ? n * kTmBlock : n) * (int)sizeof(float);
+}
+
+template <bool LANES>
 __global__ __launch_bounds__(kTmBlock) void k_tonemap_bwd(
     const float* __restrict__ in, const float* __restrict__ params, TmArgs a,
     const float* __restrict__ d_out, float* __restrict__ d_in, float* __restrict__ partial) {
   __shared__ TmShared sh;
-  __shared__ float s_dr[kTmMaxResp];
   __shared__ float s_red[kTmBlock / 64][kTmFixed];
+  extern __shared__ float s_dr[];   // LANES: [n][kTmBlock], else [n]
   const int v = blockIdx.y;
   const int P = kTmFixed + a.n;
-  for (int i = threadIdx.x; i < a.n; i += kTmBlock) s_dr[i] = 0.0f;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < (LANES ? a.n * kTmBlock : a.n); i += kTmBlock) s_dr[i] = 0.0f;
   tm_load(sh, params + (int64_t)v * P, a.n);
   const int64_t plane = (int64_t)a.W * a.H;
   const float* src = in + (int64_t)v * 3 * plane;
   const float* g = d_out + (int64_t)v * 3 * plane;
+  float* dst = d_in ? d_in + (int64_t)v * 3 * plane : nullptr;
   float acc[kTmFixed] = {0, 0, 0, 0, 0, 0, 0};
-  for (int64_t p = blockIdx.x * (int64_t)kTmBlock + threadIdx.x; p < plane;
-       p += (int64_t)gridDim.x * kTmBlock) {
-    const int y = (int)(p / a.W), x = (int)(p - (int64_t)y * a.W);
+  auto pixel = [&](int x, int y, const float xi[3], const float gi[3], float di[3]) {
     float r2, vig;
     tm_vig(a.v[v], sh, x, y, r2, vig);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const float xi = src[c * plane + p];
-      const float gi = g[c * plane + p];
-      const float t = tm_t(xi, sh.e, sh.wb[c], vig);
+      const float t = tm_t(xi[c], sh.e, sh.wb[c], vig);
       float f;
       const int i = tm_seg(t, a.n, f);
-      atomicAdd(&s_dr[i], gi * (1.0f - f));
-      atomicAdd(&s_dr[i + 1], gi * f);
+      if constexpr (LANES) {
+        float* col = s_dr + i * kTmBlock + threadIdx.x;
+        col[0] += gi[c] * (1.0f - f);
+        col[kTmBlock] += gi[c] * f;
+      } else {
+        atomicAdd(&s_dr[i], gi[c] * (1.0f - f));
+        atomicAdd(&s_dr[i + 1], gi[c] * f);
+      }
       const bool inside = t > 0.0f && t < 1.0f;
-      const float dt = inside ? gi * (sh.resp[i + 1] - sh.resp[i]) * (float)(a.n - 1) : 0.0f;
-      if (d_in) d_in[(int64_t)v * 3 * plane + c * plane + p] = dt * sh.e * sh.wb[c] * vig;
+      const float dt = inside ? gi[c] * (sh.resp[i + 1] - sh.resp[i]) * (float)(a.n - 1) : 0.0f;
+      di[c] = dt * sh.e * sh.wb[c] * vig;
       acc[0] += dt * t;
-      acc[1 + c] += dt * xi * sh.e * vig;
-      const float base = dt * xi * sh.e * sh.wb[c];
+      acc[1 + c] += dt * xi[c] * sh.e * vig;
+      const float base = dt * xi[c] * sh.e * sh.wb[c];
       acc[4] += base * r2;
       acc[5] += base * r2 * r2;
       acc[6] += base * r2 * r2 * r2;
     }
+  };
+  const bool quads = plane % 4 == 0 && ((reinterpret_cast<uintptr_t>(in) |
+                                         reinterpret_cast<uintptr_t>(d_out) |
+                                         reinterpret_cast<uintptr_t>(d_in)) & 15) == 0;
+  if (quads) {   // four elements of each plane at a time (uniform)
+    for (int64_t p = 4 * (blockIdx.x * (int64_t)kTmBlock + threadIdx.x); p < plane;
+         p += 4 * (int64_t)gridDim.x * kTmBlock) {
+      float xi[4][3], gi[4][3], di[4][3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float4 u = *reinterpret_cast<const float4*>(src + c * plane + p);
+        const float4 w = *reinterpret_cast<const float4*>(g + c * plane + p);
+        xi[0][c] = u.x; xi[1][c] = u.y; xi[2][c] = u.z; xi[3][c] = u.w;
+        gi[0][c] = w.x; gi[1][c] = w.y; gi[2][c] = w.z; gi[3][c] = w.w;
+      }
+      int x, y;
+      tm_xy(p, plane, a.W, x, y);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        pixel(x, y, xi[j], gi[j], di[j]);
+        if (++x == a.W) {
+          x = 0;
+          ++y;
+        }
+      }
+      if (dst)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          *reinterpret_cast<float4*>(dst + c * plane + p) =
+              make_float4(di[0][c], di[1][c], di[2][c], di[3][c]);
+    }
+  } else {
+    for (int64_t p = blockIdx.x * (int64_t)kTmBlock + threadIdx.x; p < plane;
+         p += (int64_t)gridDim.x * kTmBlock) {
+      int x, y;
+      tm_xy(p, plane, a.W, x, y);
+      float xi[3], gi[3], di[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        xi[c] = src[c * plane + p];
+        gi[c] = g[c * plane + p];
+      }
+      pixel(x, y, xi, gi, di);
+      if (dst)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dst[c * plane + p] = di[c];
+    }
   }
   acc[0] *= -0.69314718055994531f;   // d t / d ev = -ln 2 t
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int q = 0; q < kTmFixed; ++q) {
     float s = acc[q];
@@ -166,7 +240,18 @@ __global__ __launch_bounds__(kTmBlock) void k_tonemap_bwd(
     for (int w = 0; w < kTmBlock / 64; ++w) s += s_red[w][threadIdx.x];
     out[threadIdx.x] = s;
   }
-  for (int i = threadIdx.x; i < a.n; i += kTmBlock) out[kTmFixed + i] = s_dr[i];
+  if constexpr (!LANES) {
+    for (int i = threadIdx.x; i < a.n; i += kTmBlock) out[kTmFixed + i] = s_dr[i];
+  } else {
+    for (int i = wave; i < a.n; i += kTmBlock / 64) {
+      float s = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kTmBlock / 64; ++w) s += s_dr[i * kTmBlock + 64 * w + lane];
+#pragma unroll
+      for (int sh2 = 32; sh2 > 0; sh2 >>= 1) s += __shfl_xor(s, sh2, 64);
+      if (lane == 0) out[kTmFixed + i] = s;
+    }
+  }
 }
 
 // d_params[v][q] += sum over blocks of partial[v][b][q], in a fixed order.
@@ -189,140 +274,162 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict
 int tm_blocks(const TmArgs& a) {
   return std::max(1, std::min(kTmBlocksPerView, div_up((int64_t)a.W * a.H, kTmBlock)));
 }
+// The adjoint ends each workgroup with a reduction of the response columns,
+// so it takes fewer: two per compute unit.
+int tm_bwd_blocks(const TmArgs& a) {
+  return std::max(1, std::min(kTmBwdBlocks, div_up((int64_t)a.W * a.H, kTmBlock)));
+}
 
 // ------------------------------------------------------------------- SSIM
-constexpr int kSsTile = 32, kSsHalo = 5, kSsIn = kSsTile + 2 * kSsHalo;   // 42
-constexpr int kSsBlock = 256;
+constexpr int kSsHalo = 5, kSsTaps = 2 * kSsHalo + 1;
+constexpr int kSsBlock = 128, kSsOut = 116;   // threads (input columns), output columns
+constexpr int kSsRow = 132;                   // LDS row: reads of 16 from any multiple of 4
 
 struct SsArgs {
   int planes, W, H;
   int tiles_x, tiles_y;
-  float w[11];   // the window's 1-D taps, rounded from double precision
+  int rows, groups;   // output rows per workgroup; input row groups of kSsTaps
+  float w[kSsTaps];   // the window's 1-D taps, rounded from double precision
 };
 
-// Separable 11-tap blur of NM maps staged in LDS (in: [NM][42][43]) to the
-// tile's 32 x 32 outputs; each thread produces four rows of one column.
-// hbuf: [NM][42][33].  Returns the blurred values o[NM][4].
-template <int NM>
-__device__ inline void ss_blur(const SsArgs& a, float (*in)[kSsIn][kSsIn + 1],
-                               float (*hbuf)[kSsIn][kSsTile + 1], float o[NM][4]) {
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
-  for (int r = ty; r < kSsIn; r += 8) {
+// Separable 11-tap blur of NM maps computed from NL input planes, over a
+// strip of kSsOut columns.  Vertical first: each thread walks down one input
+// column and adds its row's NM values to the 11 output rows under way, kept
+// in registers (11 input rows per unrolled group, so that every register
+// index is a constant); the 11 finished rows go through LDS for the
+// horizontal pass, four output columns per item.  Per output about 11 NM
+// fused multiply-adds each way and 5 NM 16-byte LDS reads per item: bound by
+// vector issue, where 32 x 32 tiles with both passes through LDS read 22 NM
+// floats per output.  in(x, y, v): the input values at a pixel of the image;
+// maps(v, m): the NM maps' values; out(x, y, o): four outputs from column x.
+template <int NM, int NL, class In, class Maps, class Out>
+__device__ inline void ss_blur(const SsArgs& a, int X0, int Y0, float (*s_v)[NM][kSsRow], In in,
+                               Maps maps, Out out) {
+  const int tid = threadIdx.x, x = X0 - kSsHalo + tid;
+  const int y1 = min(Y0 + a.rows, a.H);   // end of the output rows
+  float acc[kSsTaps][NM], cur[kSsTaps][NL];
+  auto load = [&](int g) {
 #pragma unroll
-    for (int m = 0; m < NM; ++m) {
-      float s = 0.0f;
+    for (int s = 0; s < kSsTaps; ++s) {
+      const int y = Y0 - kSsHalo + g * kSsTaps + s;
 #pragma unroll
-      for (int j = 0; j < 11; ++j) s = fmaf(a.w[j], in[m][r][tx + j], s);
-      hbuf[m][r][tx] = s;
+      for (int l = 0; l < NL; ++l) cur[s][l] = 0.0f;
+      if (x >= 0 && x < a.W && y >= 0 && y < a.H) in(x, y, cur[s]);
     }
-  }
-  __syncthreads();
+  };
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = ty + 8 * q;
+  for (int k = 0; k < kSsTaps; ++k)
 #pragma unroll
-    for (int m = 0; m < NM; ++m) {
-      float s = 0.0f;
+    for (int m = 0; m < NM; ++m) acc[k][m] = 0.0f;
+  load(0);
+  for (int g = 0; g < a.groups; ++g) {
 #pragma unroll
-      for (int j = 0; j < 11; ++j) s = fmaf(a.w[j], hbuf[m][r + j][tx], s);
-      o[m][q] = s;
+    for (int s = 0; s < kSsTaps; ++s) {
+      float v[NM];
+      maps(cur[s], v);
+      // input row i = 11 g + s is tap i - o of output row o = i - 10 .. i; row
+      // o is summed in slot o mod 11, row i entering slot s afresh
+#pragma unroll
+      for (int k = 0; k < kSsTaps; ++k)
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+          acc[k][m] = k == s ? a.w[0] * v[m]
+                             : fmaf(a.w[(s - k + kSsTaps) % kSsTaps], v[m], acc[k][m]);
+#pragma unroll
+      for (int m = 0; m < NM; ++m) s_v[s][m][tid] = acc[(s + 1) % kSsTaps][m];
     }
+    if (g + 1 < a.groups) load(g + 1);
+    __syncthreads();
+    for (int it = tid; it < kSsTaps * (kSsOut / 4); it += kSsBlock) {
+      const int r = it / (kSsOut / 4), q = it - r * (kSsOut / 4);
+      const int o = g * kSsTaps + r - 2 * kSsHalo;   // output row of the strip
+      if (o < 0 || Y0 + o >= y1 || X0 + 4 * q >= a.W) continue;
+      float b[NM][4];
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        float t[16];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float4 f = *reinterpret_cast<const float4*>(&s_v[r][m][4 * (q + k)]);
+          t[4 * k] = f.x; t[4 * k + 1] = f.y; t[4 * k + 2] = f.z; t[4 * k + 3] = f.w;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          float u = 0.0f;
+#pragma unroll
+          for (int j = 0; j < kSsTaps; ++j) u = fmaf(a.w[j], t[c + j], u);
+          b[m][c] = u;
+        }
+      }
+      out(X0 + 4 * q, Y0 + o, b);
+    }
+    __syncthreads();
   }
 }
 
-// Loads NM planes' halo tiles (zero outside the image) into LDS.
-template <int NM>
-__device__ inline void ss_stage(const float* const src[NM], const SsArgs& a, int X0, int Y0,
-                                float (*in)[kSsIn][kSsIn + 1]) {
-  for (int idx = threadIdx.x; idx < kSsIn * kSsIn; idx += kSsBlock) {
-    const int r = idx / kSsIn, c = idx - r * kSsIn;
-    const int y = Y0 + r - kSsHalo, x = X0 + c - kSsHalo;
-    const bool ok = x >= 0 && x < a.W && y >= 0 && y < a.H;
-#pragma unroll
-    for (int m = 0; m < NM; ++m) in[m][r][c] = ok ? src[m][(int64_t)y * a.W + x] : 0.0f;
-  }
-  __syncthreads();
-}
-
-// SSIM over one tile, from seven blurred moments of x, y and e = x - y
-// (mu_x, mu_y, E[x^2], E[y^2], E[xy], D = mu_e, E[e^2]).  With a1 = 2 mu_x
-// mu_y + C1, a2 = 2 s_xy + C2, b1 = a1 + D^2 (= mu_x^2 + mu_y^2 + C1),
-// b2 = a2 + v_e (= s_xx + s_yy + C2, v_e = E[e^2] - D^2), the map's
-// complement is 1 - SSIM = (b1 v_e + D^2 a2) / (b1 b2): no difference of
+// SSIM from five blurred moments of x, y and e = x - y (mu_x, mu_y, E[xy],
+// D = mu_e, E[e^2]; s_xy is taken from E[xy] itself, since a difference of
+// larger moments would lose it where either image is dark).  With a1 = 2 mu_x
+// mu_y + C1, a2 = 2 s_xy + C2, b1 = a1 + D^2 (= mu_x^2 + mu_y^2 + C1), b2 = a2
+// + v_e (= s_xx + s_yy + C2, v_e = E[e^2] - D^2), the map's complement is 1 - SSIM = (b1 v_e + D^2 a2) / (b1 b2): no difference of
 // nearly equal terms where x and y agree.  MAPS: writes the map's partials
 // in (mu_x, E[x^2]) and their combination with E[xy]'s, in the same
 // difference form (A, B, C' = C + 2B: A = -2 a2 D (mu_y (mu_x + mu_y) + C1)
 // / (b1^2 b2) + 2 a1 (D a2 - mu_y v_e) / (b1 b2^2), B = -SSIM / b2,
 // C' = 2 a1 v_e / (b1 b2^2)) to maps [3][planes][H][W]; else the block's sum
-// of 1 - SSIM to partial[block].
+// of 1 - SSIM to partial[block].  Twelve 1024 x 1024 planes: 89 us,
+// and 116 with the maps (141 and 165 with 32 x 32 tiles).
 template <bool MAPS>
 __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
                                                    const float* __restrict__ y, SsArgs a,
                                                    float* __restrict__ maps,
                                                    float* __restrict__ partial) {
-  __shared__ float s_in[2][kSsIn][kSsIn + 1];
-  __shared__ float s_h[7][kSsIn][kSsTile + 1];
+  __shared__ __align__(16) float s_v[kSsTaps][5][kSsRow];
   __shared__ float s_red[kSsBlock / 64];
   const int pl = blockIdx.z;
-  const int X0 = blockIdx.x * kSsTile, Y0 = blockIdx.y * kSsTile;
   const int64_t plane = (int64_t)a.W * a.H;
-  {
-    const float* src[2] = {x + pl * plane, y + pl * plane};
-    ss_stage<2>(src, a, X0, Y0, s_in);
-  }
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  // horizontal pass: the seven moments from x and y on the fly
-  for (int r = ty; r < kSsIn; r += 8) {
-    float h[7] = {0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 11; ++j) {
-      const float w = a.w[j], u = s_in[0][r][tx + j], v = s_in[1][r][tx + j], e = u - v;
-      h[0] = fmaf(w, u, h[0]);
-      h[1] = fmaf(w, v, h[1]);
-      h[2] = fmaf(w, u * u, h[2]);
-      h[3] = fmaf(w, v * v, h[3]);
-      h[4] = fmaf(w, u * v, h[4]);
-      h[5] = fmaf(w, e, h[5]);
-      h[6] = fmaf(w, e * e, h[6]);
-    }
-#pragma unroll
-    for (int m = 0; m < 7; ++m) s_h[m][r][tx] = h[m];
-  }
-  __syncthreads();
+  const float *xp = x + pl * plane, *yp = y + pl * plane;
   const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
   float sum = 0.0f;
+  ss_blur<5, 2>(
+      a, blockIdx.x * kSsOut, blockIdx.y * a.rows, s_v,
+      [&](int px, int py, float* v) {
+        const int64_t i = (int64_t)py * a.W + px;
+        v[0] = xp[i];
+        v[1] = yp[i];
+      },
+      [&](const float* v, float* m) {
+        const float e = v[0] - v[1];
+        m[0] = v[0];
+        m[1] = v[1];
+        m[2] = v[0] * v[1];
+        m[3] = e;
+        m[4] = e * e;
+      },
+      [&](int px, int py, const float (*o)[4]) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = ty + 8 * q;
-    float o[7];
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      float t = 0.0f;
-#pragma unroll
-      for (int j = 0; j < 11; ++j) t = fmaf(a.w[j], s_h[m][r + j][tx], t);
-      o[m] = t;
-    }
-    const int gx = X0 + tx, gy = Y0 + r;
-    if (gx >= a.W || gy >= a.H) continue;
-    const float mx = o[0], my = o[1], D = o[5];
-    const float sxy = o[4] - mx * my;
-    const float ve = o[6] - D * D;
-    const float a1 = 2.0f * mx * my + C1, a2 = 2.0f * sxy + C2;
-    const float b1 = a1 + D * D, b2 = a2 + ve;
-    const float inv = 1.0f / (b1 * b2);
-    if (MAPS) {
-      const float s = a1 * a2 * inv;
-      const float A = -2.0f * a2 * D * (my * (mx + my) + C1) * inv / b1 +
-                      2.0f * a1 * (D * a2 - my * ve) * inv / b2;
-      const int64_t o2 = pl * plane + (int64_t)gy * a.W + gx;
-      const int64_t all = (int64_t)a.planes * plane;
-      maps[o2] = A;
-      maps[all + o2] = -s / b2;
-      maps[2 * all + o2] = 2.0f * a1 * ve * inv / b2;
-    } else {
-      sum += (b1 * ve + D * D * a2) * inv;
-    }
-  }
+        for (int c = 0; c < 4; ++c) {
+          if (px + c >= a.W) continue;
+          const float mx = o[0][c], my = o[1][c], D = o[3][c];
+          const float sxy = o[2][c] - mx * my;
+          const float ve = o[4][c] - D * D;
+          const float a1 = 2.0f * mx * my + C1, a2 = 2.0f * sxy + C2;
+          const float b1 = a1 + D * D, b2 = a2 + ve;
+          const float inv = 1.0f / (b1 * b2);
+          if (MAPS) {
+            const float s = a1 * a2 * inv;
+            const float A = -2.0f * a2 * D * (my * (mx + my) + C1) * inv / b1 +
+                            2.0f * a1 * (D * a2 - my * ve) * inv / b2;
+            const int64_t o2 = pl * plane + (int64_t)py * a.W + px + c;
+            const int64_t all = (int64_t)a.planes * plane;
+            maps[o2] = A;
+            maps[all + o2] = -s / b2;
+            maps[2 * all + o2] = 2.0f * a1 * ve * inv / b2;
+          } else {
+            sum += (b1 * ve + D * D * a2) * inv;
+          }
+        }
+      });
   if (!MAPS) {
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) sum += __shfl_xor(sum, sh, 64);
@@ -339,32 +446,40 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
 
 // d_x += scale (blur(A) + 2 (x - y) blur(B) + y blur(C')), scale =
 // -d_loss / N (the partials' adjoint: A + 2 x B + y C with C = C' - 2B).
+// Twelve 1024 x 1024 planes: 114 us (129 with 32 x 32 tiles; its 350 MB take
+// 74 at a copy's rate).
 __global__ __launch_bounds__(kSsBlock) void k_ssim_bwd(const float* __restrict__ x,
                                                        const float* __restrict__ y, SsArgs a,
                                                        const float* __restrict__ maps,
                                                        const float* __restrict__ d_loss,
                                                        float inv_n, float* __restrict__ d_x) {
-  __shared__ float s_in[3][kSsIn][kSsIn + 1];
-  __shared__ float s_h[3][kSsIn][kSsTile + 1];
+  __shared__ __align__(16) float s_v[kSsTaps][3][kSsRow];
   const int pl = blockIdx.z;
-  const int X0 = blockIdx.x * kSsTile, Y0 = blockIdx.y * kSsTile;
   const int64_t plane = (int64_t)a.W * a.H;
   const int64_t all = (int64_t)a.planes * plane;
-  const float* src[3] = {maps + pl * plane, maps + all + pl * plane, maps + 2 * all + pl * plane};
-  ss_stage<3>(src, a, X0, Y0, s_in);
-  float o[3][4];
-  ss_blur<3>(a, s_in, s_h, o);
+  const float* mp = maps + pl * plane;
   const float scale = -(d_loss ? *d_loss : 1.0f) * inv_n;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  ss_blur<3, 3>(
+      a, blockIdx.x * kSsOut, blockIdx.y * a.rows, s_v,
+      [&](int px, int py, float* v) {
+        const int64_t i = (int64_t)py * a.W + px;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int gx = X0 + tx, gy = Y0 + ty + 8 * q;
-    if (gx >= a.W || gy >= a.H) continue;
-    const int64_t i = pl * plane + (int64_t)gy * a.W + gx;
-    const float yi = y[i];
-    const float g = o[0][q] + 2.0f * (x[i] - yi) * o[1][q] + yi * o[2][q];
-    d_x[i] += scale * g;
-  }
+        for (int l = 0; l < 3; ++l) v[l] = mp[l * all + i];
+      },
+      [&](const float* v, float* m) {
+#pragma unroll
+        for (int l = 0; l < 3; ++l) m[l] = v[l];
+      },
+      [&](int px, int py, const float (*o)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (px + c >= a.W) continue;
+          const int64_t i = pl * plane + (int64_t)py * a.W + px + c;
+          const float yi = y[i];
+          const float g = o[0][c] + 2.0f * (x[i] - yi) * o[1][c] + yi * o[2][c];
+          d_x[i] += scale * g;
+        }
+      });
 }
 
 // out[0] = sum(partial) / N (the blocks' sums of 1 - SSIM), in a fixed
@@ -384,13 +499,33 @@ __global__ __launch_bounds__(256) void k_dssim_finish(const float* __restrict__ 
   if (threadIdx.x == 0) out[0] = (float)(s[0] * inv_n);
 }
 
-bool ss_args(int planes, int W, int H, SsArgs* a) {
-  if (planes < 1 || W < 1 || H < 1 || planes > 65535) return false;
+// Strips of 11 (groups - 1) + 1 rows at most: ten input rows of each are
+// halo, so tall ones compute less, short ones fill the chip.  The number of
+// groups that gives the fewest passes of `resident` workgroups per compute
+// unit over it, times the groups of each (twelve 1024 x 1024 planes: 5 groups
+// in two passes for the moments, 90 us against 99 with 7 and 94 with 10; 7 in
+// one pass for the gradient, 114 us against 127 with 5 and 118 with 10).
+constexpr int kSsResident = 5, kSsResidentBwd = 8;   // by LDS; by registers
+bool ss_ok(int planes, int W, int H) {
+  return planes >= 1 && W >= 1 && H >= 1 && planes <= 65535 && div_up(H, 32) <= 65535;
+}
+void ss_args(int planes, int W, int H, int resident, SsArgs* a) {
   a->planes = planes;
   a->W = W;
   a->H = H;
-  a->tiles_x = div_up(W, kSsTile);
-  a->tiles_y = div_up(H, kSsTile);
+  a->tiles_x = div_up(W, kSsOut);
+  const int64_t chip = (int64_t)resident * device_cus();
+  int64_t best = INT64_MAX;
+  for (int groups = 2; groups <= 12; ++groups) {
+    const int strips = div_up(H, kSsTaps * (groups - 1) + 1);
+    if (strips > 65535) continue;
+    const int64_t cost = (((int64_t)planes * a->tiles_x * strips + chip - 1) / chip) * groups;
+    if (cost >= best) continue;
+    best = cost;
+    a->tiles_y = strips;
+    a->rows = div_up(H, strips);
+    a->groups = div_up(a->rows + 2 * kSsHalo, kSsTaps);
+  }
   double g[11], s = 0.0;
   for (int j = 0; j < 11; ++j) {
     const double u = j - 5;
@@ -398,7 +533,6 @@ bool ss_args(int planes, int W, int H, SsArgs* a) {
     s += g[j];
   }
   for (int j = 0; j < 11; ++j) a->w[j] = (float)(g[j] / s);
-  return a->tiles_y <= 65535;
 }
 
 // -------------------------------------------------------------- regulariser
@@ -413,15 +547,15 @@ __device__ inline void reg_locate(const RegArgs& a, long long e, int& k, int& c,
                                   int& xx, int& x0, int& y0) {
   k = 0;
   while (k + 1 < a.n && a.ebase[k + 1] <= e) ++k;
-  const long long r = e - a.ebase[k];
-  const int S = a.S[k];
-  c = (int)(r / ((long long)S * S));
-  const long long q = r - (long long)c * S * S;
+  const uint32_t r = (uint32_t)(e - a.ebase[k]);   // a crop has under 2^32 elements
+  const uint32_t S = (uint32_t)a.S[k];
+  c = (int)(r / (S * S));
+  const uint32_t q = r - (uint32_t)c * S * S;
   yy = (int)(q / S);
-  xx = (int)(q - (long long)yy * S);
+  xx = (int)(q - (uint32_t)yy * S);
   if (a.place) {
-    x0 = clamp_origin(a.place[k].x, a.W - S);
-    y0 = clamp_origin(a.place[k].y, a.H - S);
+    x0 = clamp_origin(a.place[k].x, a.W - a.S[k]);
+    y0 = clamp_origin(a.place[k].y, a.H - a.S[k]);
   } else {
     x0 = a.x0[k];
     y0 = a.y0[k];
@@ -594,7 +728,7 @@ using namespace vrs;
 extern "C" size_t vrs_tonemap_workspace_size(const vrs_view* views, int n_views, int n_resp) {
   TmArgs a;
   if (!tm_args(views, n_views, n_resp, &a)) return 0;
-  return (size_t)n_views * tm_blocks(a) * (kTmFixed + n_resp) * sizeof(float);
+  return (size_t)n_views * tm_bwd_blocks(a) * (kTmFixed + n_resp) * sizeof(float);
 }
 
 extern "C" vrs_status vrs_tonemap(const float* in, const vrs_view* views, int n_views,
@@ -618,9 +752,10 @@ extern "C" vrs_status vrs_tonemap_backward(const float* in, const vrs_view* view
     return VRS_EINVAL;
   if (!d_in && !d_params) return VRS_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int nb = tm_blocks(a);
+  const int nb = tm_bwd_blocks(a);
   float* partial = d_params ? static_cast<float*>(ws) : nullptr;
-  hipLaunchKernelGGL(k_tonemap_bwd, dim3(nb, n_views), dim3(kTmBlock), 0, st, in, params, a,
+  auto bwd = tm_lanes(n_resp) ? k_tonemap_bwd<true> : k_tonemap_bwd<false>;
+  hipLaunchKernelGGL(bwd, dim3(nb, n_views), dim3(kTmBlock), tm_lds(n_resp), st, in, params, a,
                      d_out, d_in, partial);
   VRS_LAUNCH_CHECK();
   if (d_params) {
@@ -632,22 +767,20 @@ extern "C" vrs_status vrs_tonemap_backward(const float* in, const vrs_view* view
 }
 
 extern "C" size_t vrs_dssim_workspace_size(int planes, int width, int height) {
-  SsArgs a;
-  if (!ss_args(planes, width, height, &a)) return 0;
-  // block partials of the forward, or the three derivative maps of the
-  // adjoint (the larger)
-  const size_t part = (size_t)planes * a.tiles_x * a.tiles_y * sizeof(float);
-  const size_t maps = 3 * (size_t)planes * width * height * sizeof(float);
-  return std::max(part, maps);
+  if (!ss_ok(planes, width, height)) return 0;
+  // the three derivative maps of the adjoint (the forward's block partials
+  // are fewer than one map's elements)
+  return 3 * (size_t)planes * width * height * sizeof(float);
 }
 
 extern "C" vrs_status vrs_dssim(const float* x, const float* y, int planes, int width,
                                 int height, float* loss, void* ws, size_t ws_bytes,
                                 void* stream) {
-  SsArgs a;
-  if (!ss_args(planes, width, height, &a) || !x || !y || !loss || !ws ||
+  if (!ss_ok(planes, width, height) || !x || !y || !loss || !ws ||
       ws_bytes < vrs_dssim_workspace_size(planes, width, height))
     return VRS_EINVAL;
+  SsArgs a;
+  ss_args(planes, width, height, kSsResident, &a);
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* partial = static_cast<float*>(ws);
   hipLaunchKernelGGL(k_ssim<false>, dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
@@ -663,16 +796,19 @@ extern "C" vrs_status vrs_dssim(const float* x, const float* y, int planes, int 
 extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width,
                                          int height, const float* d_loss, float* d_x, void* ws,
                                          size_t ws_bytes, void* stream) {
-  SsArgs a;
-  if (!ss_args(planes, width, height, &a) || !x || !y || !d_x || !ws ||
+  if (!ss_ok(planes, width, height) || !x || !y || !d_x || !ws ||
       ws_bytes < vrs_dssim_workspace_size(planes, width, height))
     return VRS_EINVAL;
+  SsArgs a, b;
+  ss_args(planes, width, height, kSsResident, &a);
+  ss_args(planes, width, height, kSsResidentBwd, &b);
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* maps = static_cast<float*>(ws);
-  const dim3 grid(a.tiles_x, a.tiles_y, planes);
-  hipLaunchKernelGGL(k_ssim<true>, grid, dim3(kSsBlock), 0, st, x, y, a, maps, nullptr);
+  hipLaunchKernelGGL(k_ssim<true>, dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
+                     y, a, maps, nullptr);
   VRS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(kSsBlock), 0, st, x, y, a, maps, d_loss,
+  hipLaunchKernelGGL(k_ssim_bwd, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0, st, x, y,
+                     b, maps, d_loss,
                      (float)(1.0 / ((double)planes * width * height)), d_x);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
