@@ -250,8 +250,9 @@ __device__ inline uint64_t bin_lane_mask(const uint64_t* R, const uint64_t* X, i
   uint64_t a = R[0], b = X[0];
 #pragma unroll
   for (int k = 1; k < kSuper; ++k) {
-    a = r == k ? R[k] : a;
-    b = c == k ? X[k] : b;
+    const uint64_t rk = R[k], xk = X[k];   // values: a choice of addresses would need memory
+    a = r == k ? rk : a;
+    b = c == k ? xk : b;
   }
   return a & b;
 }
