@@ -17,9 +17,12 @@
 namespace vrs {
 
 // Per (view, Gaussian): with s the pixel's gradient with respect to the
-// exponent and d = mean - pixel centre, the sums of s, s dx, s dy, s dx^2,
-// s dx dy, s dy^2, and the gradients of r, g, b and z.  k_gs_project_bwd
-// turns the moments into the gradients of position, conic and opacity.
+// exponent -d^T Q d / 2 (Q the conic), d = mean - pixel centre and u =
+// -log2(e) Q d, the sums of s, s ux, s uy, s ux^2, s ux uy, s uy^2, and the
+// gradients of r, g, b and z.  The position's gradient is a multiple of the
+// sum of s u and the screen covariance's of s u u^T, so k_gs_project_bwd only
+// scales them; sums of s d and s d d^T would still have to go through Q, which
+// loses digits where Q is ill conditioned (thin Gaussians).
 constexpr int kG2d = 10;
 
 // Two values' sums over lane pairs 32 (16) lanes apart, in one register:
@@ -61,7 +64,7 @@ __device__ inline float row_sum(float v) {
 // instruction.  T / (1 - alpha) is the hardware reciprocal with its remainder
 // put back (1 - alpha is in [0.01, 1], so no scaling is needed).
 // 1M Gaussians, four 1024 x 1024 views, tile 16: 3574 us with ten reductions,
-// ten atomics and all records of a tile per 64 pixels, 469 us now.
+// ten atomics and all records of a tile per 64 pixels, 477 us now.
 template <int TILE, bool DEPTH>
 __global__ __launch_bounds__(64) void k_gs_blend_bwd(
     const uint32_t* __restrict__ order, const uint2* __restrict__ ranges,
@@ -180,13 +183,15 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
       T = Tb;
       // a clamped alpha carries nothing to the exponent or the opacity
       const float s = oe < aclamp ? (Tb * diff) * al : 0.0f;
-      const float sx = s * dx, sy = s * dy;
-      // values 0..9 = s, s dx, s dy, s dx^2, s dx dy, s dy^2, r, g, b, z.
+      const float hx = ka.z * dx;
+      const float ux = fmaf(ka.w, dy, hx + hx), uy = fmaf(kb.x + kb.x, dy, ka.w * dx);
+      const float sx = s * ux, sy = s * uy;
+      // values 0..9 = s, s ux, s uy, s ux^2, s ux uy, s uy^2, r, g, b, z.
       // After the exchanges over 32 and 16 lanes, rows 0..3 of q0 hold the
       // sums of values 0, 2, 1, 3, of q1 those of 4, 6, 5, 7, of q2 8 and 9
       // in rows 0 and 2; lane 0 of each row takes q0, lane 1 q1, lane 2 q2.
-      const float p0 = pair_sum32(s, sx), p1 = pair_sum32(sy, sx * dx);
-      const float p2 = pair_sum32(sx * dy, sy * dy), p3 = pair_sum32(w * g0, w * g1);
+      const float p0 = pair_sum32(s, sx), p1 = pair_sum32(sy, sx * ux);
+      const float p2 = pair_sum32(sx * uy, sy * uy), p3 = pair_sum32(w * g0, w * g1);
       const float p4 = pair_sum32(w * g2, DEPTH ? w * gd : 0.0f);
       const float q0 = row_sum(pair_sum16(p0, p1)), q1 = row_sum(pair_sum16(p2, p3));
       const float q2 = row_sum(pair_sum16(p4, 0.0f));
@@ -293,21 +298,14 @@ __global__ __launch_bounds__(256) void k_gs_project_bwd(
     const KView& cv = views.v[v];
     Geom g;
     if (!gs_geom32(cv, mx, my, mz, S6, o.lowpass, o.extent, g)) continue;
-    // conic (A, B, C) = inverse of [[a, b], [b, c]]
-    const float inv = 1.0f / g.det;
-    const float A = g.c * inv, B = -g.b * inv, C = g.a * inv;
-    // exponent -(A dx^2 + C dy^2) / 2 - B dx dy, alpha = opacity e^exponent
-    const float gpx = -(A * G[1] + B * G[2]), gpy = -(C * G[2] + B * G[1]);
-    const float gA = -0.5f * G[3], gB = -G[4], gC = -0.5f * G[5], gz = G[9];
+    // exponent -d^T Q d / 2, alpha = opacity e^exponent: dL/dd = -s Q d and,
+    // with dQ = -Q dSigma Q, dL/dSigma = s (Q d) (Q d)^T / 2; u = -log2(e) Q d
+    constexpr float kLn2 = 0.69314718055994531f;
+    const float gpx = kLn2 * G[1], gpy = kLn2 * G[2], gz = G[9];
     if (op != 0.0f) dopa += G[0] / op;
-    // H = -Q G Q with G = [[gA, gB/2], [gB/2, gC]], Q = [[A, B], [B, C]]
-    const float G00 = gA, G01 = 0.5f * gB, G11 = gC;
-    const float QG00 = A * G00 + B * G01, QG01 = A * G01 + B * G11;
-    const float QG10 = B * G00 + C * G01, QG11 = B * G01 + C * G11;
-    const float H00 = -(QG00 * A + QG01 * B), H01 = -(QG00 * B + QG01 * C);
-    const float H11 = -(QG10 * B + QG11 * C);
     // dL/dSigma2D as a full symmetric matrix Gs
-    const float Gs[2][2] = {{H00, H01}, {H01, H11}};
+    constexpr float h = 0.5f * kLn2 * kLn2;
+    const float Gs[2][2] = {{h * G[3], h * G[4]}, {h * G[4], h * G[5]}};
     // dSigma3D = M^T Gs M ; dM = 2 Gs M Sigma
     const float S[3][3] = {{S6[0], S6[1], S6[2]}, {S6[1], S6[3], S6[4]}, {S6[2], S6[4], S6[5]}};
     float GM[2][3];
