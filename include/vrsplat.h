@@ -235,6 +235,14 @@ vrs_status vrs_render_gaussians_backward(const float* mean, const float* cov,
                                          const float* d_rgb, const float* d_depth, float* d_mean,
                                          float* d_cov, float* d_opacity, float* d_sh, void* ws,
                                          size_t ws_bytes, int64_t max_pairs, void* stream);
+/* The same, written instead of accumulated (every element). */
+vrs_status vrs_render_gaussians_backward_write(const float* mean, const float* cov,
+                                         const float* opacity, const float* sh, int sh_degree,
+                                         int64_t n, const vrs_view* views, int n_views,
+                                         const vrs_raster_opts* opts, const float* t_final,
+                                         const float* d_rgb, const float* d_depth, float* d_mean,
+                                         float* d_cov, float* d_opacity, float* d_sh, void* ws,
+                                         size_t ws_bytes, int64_t max_pairs, void* stream);
 
 /* ------------------------------------------------------- tone mapping
  * The combined image mapped to a displayable range by a differentiable
@@ -283,6 +291,10 @@ vrs_status vrs_dssim(const float* x, const float* y, int planes, int width, int 
 /* Adjoint with respect to x: d_x += d_loss * d(D-SSIM)/dx, d_loss a DEVICE
  * float32 scalar (NULL: 1). */
 vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width, int height,
+                              const float* d_loss, float* d_x, void* ws, size_t ws_bytes,
+                              void* stream);
+/* The same, written instead of accumulated. */
+vrs_status vrs_dssim_backward_write(const float* x, const float* y, int planes, int width, int height,
                               const float* d_loss, float* d_x, void* ws, size_t ws_bytes,
                               void* stream);
 
@@ -465,6 +477,13 @@ vrs_status vrs_composite_frame_backward(const float* rgb_periphery, int n_views,
                                         const vrs_crop_place* place, int mode,
                                         float ring, float m, float gamma, const float* d_out,
                                         float* d_rgb_periphery, float* d_fovea, void* stream);
+/* The same, written instead of accumulated (every element). */
+vrs_status vrs_composite_frame_backward_write(const float* rgb_periphery, int n_views, int width,
+                                        int height, const float* fovea_rgb,
+                                        const vrs_crop* crops, int n_crops,
+                                        const vrs_crop_place* place, int mode,
+                                        float ring, float m, float gamma, const float* d_out,
+                                        float* d_rgb_periphery, float* d_fovea, void* stream);
 
 /* --------------------------------------------------------------- loss
  * L1 photometric term of the fitting loss (Sec. 3.5, Eq. 6):
@@ -472,6 +491,10 @@ vrs_status vrs_composite_frame_backward(const float* rgb_periphery, int n_views,
  * d_pred (may be NULL) accumulates scale * sign(pred - target) / n. */
 vrs_status vrs_l1_loss(const float* pred, const float* target, int64_t n, float* loss,
                        float* d_pred, float scale, void* stream);
+/* Its adjoint alone, written: d_pred = d_loss * sign(pred - target) / n, d_loss
+ * a DEVICE float32 scalar (NULL: 1). */
+vrs_status vrs_l1_loss_backward(const float* pred, const float* target, int64_t n,
+                                const float* d_loss, float* d_pred, void* stream);
 
 /* ---------------------------------------------------------- frame plan
  * Everything fixed across the frames of one scene and rig: views, crop

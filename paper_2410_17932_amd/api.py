@@ -111,6 +111,9 @@ SIGNATURES = {
     "vrs_render_gaussians_backward": (_int, [_vp, _vp, _vp, _vp, _int, _i64, _P(View), _int,
                                              _P(RasterOpts), _vp, _vp, _vp, _vp, _vp, _vp,
                                              _vp, _vp, _sz, _i64, _vp]),
+    "vrs_render_gaussians_backward_write": (_int, [_vp, _vp, _vp, _vp, _int, _i64, _P(View), _int,
+                                             _P(RasterOpts), _vp, _vp, _vp, _vp, _vp, _vp,
+                                             _vp, _vp, _sz, _i64, _vp]),
     "vrs_splat_workspace_size": (_sz, [_i64, _int, _P(View), _P(Crop), _int, _int, _i64]),
     "vrs_splat_workspace_layout": (_int, [_i64, _int, _P(View), _P(Crop), _int, _int, _i64,
                                           _P(SplatLayout)]),
@@ -131,7 +134,10 @@ SIGNATURES = {
                                    _flt, _flt, _flt, _vp, _vp]),
     "vrs_composite_frame_backward": (_int, [_vp, _int, _int, _int, _vp, _P(Crop), _int, _vp,
                                             _int, _flt, _flt, _flt, _vp, _vp, _vp, _vp]),
+    "vrs_composite_frame_backward_write": (_int, [_vp, _int, _int, _int, _vp, _P(Crop), _int, _vp,
+                                            _int, _flt, _flt, _flt, _vp, _vp, _vp, _vp]),
     "vrs_l1_loss": (_int, [_vp, _vp, _i64, _vp, _vp, _flt, _vp]),
+    "vrs_l1_loss_backward": (_int, [_vp, _vp, _i64, _vp, _vp, _vp]),
     "vrs_tonemap": (_int, [_vp, _P(View), _int, _vp, _int, _vp, _vp]),
     "vrs_tonemap_workspace_size": (_sz, [_P(View), _int, _int]),
     "vrs_tonemap_backward": (_int, [_vp, _P(View), _int, _vp, _int, _vp, _vp, _vp, _vp, _sz,
@@ -139,6 +145,7 @@ SIGNATURES = {
     "vrs_dssim_workspace_size": (_sz, [_int, _int, _int]),
     "vrs_dssim": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _sz, _vp]),
     "vrs_dssim_backward": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _vp, _sz, _vp]),
+    "vrs_dssim_backward_write": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _vp, _sz, _vp]),
     "vrs_regulariser_workspace_size": (_sz, []),
     "vrs_regulariser": (_int, [_vp, _vp, _int, _int, _int, _P(Crop), _int, _vp, _vp, _vp, _sz,
                                _vp]),
@@ -383,9 +390,12 @@ def render_gaussians(mean, cov, opacity, sh, sh_degree, views, opts, ws: RenderW
 
 
 def render_gaussians_backward(mean, cov, opacity, sh, sh_degree, views, opts, ws, tfinal, d_rgb,
-                              d_depth, d_mean, d_cov, d_opacity, d_sh):
+                              d_depth, d_mean, d_cov, d_opacity, d_sh, accumulate=True):
+    """Gradients added to d_* (accumulate) or written."""
     n = mean.shape[1]
-    code = lib().vrs_render_gaussians_backward(
+    fn = (lib().vrs_render_gaussians_backward if accumulate
+          else lib().vrs_render_gaussians_backward_write)
+    code = fn(
         ptr(mean, torch.float32), ptr(cov, torch.float32), ptr(opacity, torch.float32),
         ptr(sh, torch.float32), sh_degree, n, ws.cviews, len(views), ctypes.byref(opts),
         ptr(tfinal, torch.float32), ptr(d_rgb, torch.float32), ptr(d_depth, torch.float32),
@@ -543,9 +553,13 @@ def composite_frame(periphery, fovea, crops, mode=BLEND_LINEAR, ring=64.0, m=0.7
 
 
 def composite_frame_backward(periphery, fovea, crops, d_out, d_periphery=None, d_fovea=None,
-                             mode=BLEND_LINEAR, ring=64.0, m=0.75, gamma=0.2, place=None):
+                             mode=BLEND_LINEAR, ring=64.0, m=0.75, gamma=0.2, place=None,
+                             accumulate=True):
+    """Gradients added to d_* (accumulate) or written."""
     V, _, H, W = periphery.shape
-    code = lib().vrs_composite_frame_backward(
+    fn = (lib().vrs_composite_frame_backward if accumulate
+          else lib().vrs_composite_frame_backward_write)
+    code = fn(
         ptr(periphery, torch.float32), V, W, H, ptr(fovea, torch.float32), make_crops(crops),
         len(crops), ptr(place, torch.int32), mode, ring, m, gamma, ptr(d_out, torch.float32), ptr(d_periphery),
         ptr(d_fovea), _stream())
@@ -609,11 +623,12 @@ def dssim(x, y, ws: DssimWorkspace, loss=None):
     return loss
 
 
-def dssim_backward(x, y, ws: DssimWorkspace, d_x, d_loss=None):
+def dssim_backward(x, y, ws: DssimWorkspace, d_x, d_loss=None, accumulate=True):
+    """Gradient added to d_x (accumulate) or written."""
     P, H, W = ws.shape
-    _check(lib().vrs_dssim_backward(ptr(x, torch.float32), ptr(y, torch.float32), P, W, H,
-                                    ptr(d_loss, torch.float32), ptr(d_x), ptr(ws.buf),
-                                    ws.buf.numel(), _stream()), "vrs_dssim_backward")
+    fn = lib().vrs_dssim_backward if accumulate else lib().vrs_dssim_backward_write
+    _check(fn(ptr(x, torch.float32), ptr(y, torch.float32), P, W, H, ptr(d_loss, torch.float32),
+              ptr(d_x), ptr(ws.buf), ws.buf.numel(), _stream()), "vrs_dssim_backward")
 
 
 def regulariser(fovea, periphery, crops, place=None, r=None):
@@ -704,3 +719,10 @@ def l1_loss(pred, target, d_pred=None, scale=1.0):
     _check(lib().vrs_l1_loss(ptr(pred, torch.float32), ptr(target, torch.float32), pred.numel(),
                              ptr(loss), ptr(d_pred), scale, _stream()), "vrs_l1_loss")
     return loss
+
+
+def l1_loss_backward(pred, target, d_pred, d_loss=None):
+    """d_pred = d_loss sign(pred - target) / n, written (d_loss: device scalar, None: 1)."""
+    _check(lib().vrs_l1_loss_backward(ptr(pred, torch.float32), ptr(target, torch.float32),
+                                      pred.numel(), ptr(d_loss, torch.float32), ptr(d_pred),
+                                      _stream()), "vrs_l1_loss_backward")

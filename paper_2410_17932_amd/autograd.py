@@ -1,7 +1,8 @@
 """torch.autograd.Function wrappers over the C-ABI, so the Gaussians, the
 neural points and the decoder can be fitted end to end (Sec. 3.5).  Each
-forward and each backward is one call into the HIP library; gradients land
-in fresh zeroed tensors (the library accumulates into them).
+forward and each backward is one call into the HIP library.  Gradients land
+in fresh tensors: written by the library where every element is (most of a
+backward's bytes), else zeroed and accumulated into.
 
 A backward replays what its forward left in the caller's workspace (tile
 lists, stop positions, fragment segments, activations): one forward per
@@ -41,6 +42,7 @@ class RenderGaussians(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, mean, cov, opacity, sh, sh_degree, views, opts, ws):
+        ctx.set_materialize_grads(False)   # an unused depth costs nothing in the backward
         out = api.render_gaussians(mean, cov, opacity, sh, sh_degree, views, opts, ws)
         ctx.save_for_backward(mean, cov, opacity, sh, out["tfinal"])
         ctx.meta = (sh_degree, views, opts, ws, ws.generation)
@@ -52,11 +54,12 @@ class RenderGaussians(torch.autograd.Function):
         mean, cov, op, sh, tf = ctx.saved_tensors
         deg, views, opts, ws, gen = ctx.meta
         _check_generation(ws, gen, "RenderGaussians")
-        g = [torch.zeros_like(t) for t in (mean, cov, op, sh)]
+        g = [torch.empty_like(t) for t in (mean, cov, op, sh)]
         d_rgb = torch.zeros_like(tf).unsqueeze(1).expand(-1, 3, -1, -1).contiguous() \
             if d_rgb is None else d_rgb.contiguous()
         api.render_gaussians_backward(mean, cov, op, sh, deg, views, opts, ws, tf, d_rgb,
-                                      None if d_depth is None else d_depth.contiguous(), *g)
+                                      None if d_depth is None else d_depth.contiguous(), *g,
+                                      accumulate=False)
         return (*g, None, None, None, None)
 
 
@@ -117,8 +120,9 @@ class CompositeFrame(torch.autograd.Function):
     def backward(ctx, d_out):
         P, F = ctx.saved_tensors
         crops, mode, ring, m, gamma = ctx.meta
-        dP, dF = torch.zeros_like(P), torch.zeros_like(F)
-        api.composite_frame_backward(P, F, crops, d_out.contiguous(), dP, dF, mode, ring, m, gamma)
+        dP, dF = torch.empty_like(P), torch.empty_like(F)
+        api.composite_frame_backward(P, F, crops, d_out.contiguous(), dP, dF, mode, ring, m, gamma,
+                                     accumulate=False)
         return dP, dF, None, None, None, None, None
 
 
@@ -131,8 +135,10 @@ class L1Loss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g):
         pred, target = ctx.saved_tensors
-        d = torch.zeros_like(pred)
-        api.l1_loss(pred.contiguous(), target.contiguous(), d_pred=d, scale=float(g))
+        pred = pred.contiguous()
+        d = torch.empty_like(pred)
+        # the loss gradient stays on the device: reading it here would wait for the forward
+        api.l1_loss_backward(pred, target.contiguous(), d, d_loss=g.reshape(1).contiguous())
         return d, None
 
 
@@ -185,8 +191,9 @@ class Dssim(torch.autograd.Function):
         pred, target = ctx.saved_tensors
         H, W = pred.shape[-2:]
         ws = _dssim_ws(pred.numel() // (H * W), W, H, pred.device)
-        d = torch.zeros_like(pred)
-        api.dssim_backward(pred, target, ws, d, d_loss=g.reshape(1).contiguous())
+        d = torch.empty_like(pred)
+        api.dssim_backward(pred, target, ws, d, d_loss=g.reshape(1).contiguous(),
+                           accumulate=False)
         return d, None
 
 

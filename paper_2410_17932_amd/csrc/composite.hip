@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void k_composite4_inplace(CompArgs a, float* i
 // pixel (one thread owns each gradient element, so nothing is atomic).  A
 // pixel under several crops walks those, and recomputes their masks, in both.
 // Four 1024 x 1024 views with a 512 crop each, with the edge term: 48 us and 28
-// us (together 155 with per-pixel chains in scratch memory and 27 atomics per
+// us, 40 and 24 written instead of added (together 155 with per-pixel chains in scratch memory and 27 atomics per
 // edge pixel).
 
 // The crops of view v over pixel (x, y), as bits (of those in `cand`).
@@ -269,7 +269,8 @@ __device__ inline float comp_mask(const CompArgs& a, int k, const float* __restr
 }
 
 // VEC pixels of a row per thread (4 where rows and pointers allow).
-template <int VEC>
+// ADD: added to dP, else written.
+template <int VEC, bool ADD>
 __global__ __launch_bounds__(256) void k_composite_bwd_p(CompArgs a, const float* __restrict__ F,
                                                          const float* __restrict__ dout,
                                                          float* __restrict__ dP) {
@@ -305,11 +306,12 @@ __global__ __launch_bounds__(256) void k_composite_bwd_p(CompArgs a, const float
       float* o = dP + base + c * plane;
       const float* g = dout + base + c * plane;
       if constexpr (VEC == 4) {
-        const float4 d = *reinterpret_cast<const float4*>(o), e = *reinterpret_cast<const float4*>(g);
+        const float4 d = ADD ? *reinterpret_cast<const float4*>(o) : make_float4(0, 0, 0, 0);
+        const float4 e = *reinterpret_cast<const float4*>(g);
         *reinterpret_cast<float4*>(o) = make_float4(fmaf(f[0], e.x, d.x), fmaf(f[1], e.y, d.y),
                                                     fmaf(f[2], e.z, d.z), fmaf(f[3], e.w, d.w));
       } else {
-        *o = fmaf(f[0], *g, *o);
+        *o = fmaf(f[0], *g, ADD ? *o : 0.0f);
       }
     }
   }
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(256) void k_composite_bwd_p(CompArgs a, const float
 // Sobel sums of every pixel with one around, gathered by the pixels it flows
 // into: tap (ox, oy) of pixel p lands on the pixel at p + o clamped into the
 // crop, so a border pixel also takes its own outward taps.
-template <bool EDGE>
+template <bool EDGE, bool ADD>
 __global__ __launch_bounds__(256) void k_composite_bwd_f(CompArgs a, const float* __restrict__ P,
                                                          const float* __restrict__ F,
                                                          const float* __restrict__ dout,
@@ -433,14 +435,15 @@ __global__ __launch_bounds__(256) void k_composite_bwd_f(CompArgs a, const float
   }
   float* o = dF + a.fbase[k] + (long long)ly * S + lx;
 #pragma unroll
-  for (int ch = 0; ch < 3; ++ch) o[ch * fp] += s_d[ch][cy][cx] + e;
+  for (int ch = 0; ch < 3; ++ch) o[ch * fp] = (ADD ? o[ch * fp] : 0.0f) + (s_d[ch][cy][cx] + e);
 }
 
 // L1: block partial sums of |pred - target| atomically added to loss[0]
 // (zeroed by the preceding fill), gradient scale*sign(pred - target)/n.
 // HBM-bound; two workgroups per compute unit, since every one ends with an
 // atomic on the same word (about 11 ns each: 12.6M elements in 4096
-// workgroups took 65 us, 35 now).
+// workgroups took 65 us, 35 now, 26 without
+// the gradient).
 template <int VEC>
 __global__ __launch_bounds__(256) void k_l1(const float* __restrict__ pred,
                                             const float* __restrict__ target, long long n,
@@ -487,6 +490,35 @@ __global__ __launch_bounds__(256) void k_l1(const float* __restrict__ pred,
 }
 
 __global__ void k_zero1(float* p) { *p = 0.0f; }
+
+// The gradient alone, written: d_loss sign(pred - target) / n with d_loss a
+// device scalar, so the caller need not wait for it, and nothing is read back
+// or cleared first (12.6M elements: 24 us; 45 adding
+// to cleared gradients).
+template <int VEC>
+__global__ __launch_bounds__(256) void k_l1_bwd(const float* __restrict__ pred,
+                                                const float* __restrict__ target, long long n,
+                                                const float* __restrict__ d_loss,
+                                                float* __restrict__ dpred) {
+  const float step = (d_loss ? *d_loss : 1.0f) * (1.0f / (float)n);
+  auto one = [&](float p, float t) {
+    const float d = p - t;
+    return d > 0.0f ? step : (d < 0.0f ? -step : 0.0f);
+  };
+  const long long vn = n / VEC;
+  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < vn; i += (long long)gridDim.x * 256) {
+    if constexpr (VEC == 4) {
+      const float4 p = reinterpret_cast<const float4*>(pred)[i];
+      const float4 t = reinterpret_cast<const float4*>(target)[i];
+      reinterpret_cast<float4*>(dpred)[i] =
+          make_float4(one(p.x, t.x), one(p.y, t.y), one(p.z, t.z), one(p.w, t.w));
+    } else {
+      dpred[i] = one(pred[i], target[i]);
+    }
+  }
+  const long long tail = vn * VEC + blockIdx.x * 256LL + threadIdx.x;
+  if (tail < n) dpred[tail] = one(pred[tail], target[tail]);
+}
 
 static bool comp_args(int nv, int W, int H, const vrs_crop* crops, int n_crops, int mode,
                       float ring, float m, float gamma, const vrs_crop_place* place,
@@ -577,7 +609,8 @@ extern "C" vrs_status vrs_composite_frame(const float* rgb_periphery, int n_view
                         mode, ring, m, gamma, out, stream, nullptr);
 }
 
-extern "C" vrs_status vrs_composite_frame_backward(const float* rgb_periphery, int n_views,
+template <bool ADD>
+static vrs_status composite_backward(const float* rgb_periphery, int n_views,
                                                    int width, int height, const float* fovea_rgb,
                                                    const vrs_crop* crops, int n_crops,
                                                    const vrs_crop_place* place, int mode,
@@ -594,27 +627,40 @@ extern "C" vrs_status vrs_composite_frame_backward(const float* rgb_periphery, i
                                           reinterpret_cast<uintptr_t>(d_rgb_periphery)) & 15) == 0;
     const long long per = (long long)width * height / (vec4 ? 4 : 1);
     const dim3 grid((unsigned)std::min<long long>(8192, (per + 255) / 256), n_views);
-    if (vec4)
-      hipLaunchKernelGGL(k_composite_bwd_p<4>, grid, dim3(256), 0, st, a, fovea_rgb, d_out,
-                         d_rgb_periphery);
-    else
-      hipLaunchKernelGGL(k_composite_bwd_p<1>, grid, dim3(256), 0, st, a, fovea_rgb, d_out,
-                         d_rgb_periphery);
+    hipLaunchKernelGGL((vec4 ? k_composite_bwd_p<4, ADD> : k_composite_bwd_p<1, ADD>), grid,
+                       dim3(256), 0, st, a, fovea_rgb, d_out, d_rgb_periphery);
     VRS_LAUNCH_CHECK();
   }
   if (d_fovea && n_crops > 0) {
     int most = 0;
     for (int k = 0; k < n_crops; ++k) most = std::max(most, (crops[k].size + 15) / 16);
     const dim3 grid((unsigned)(most * most), n_crops);
-    if (mode == VRS_BLEND_PAPER && gamma != 0.0f)
-      hipLaunchKernelGGL(k_composite_bwd_f<true>, grid, dim3(256), 0, st, a, rgb_periphery,
-                         fovea_rgb, d_out, d_fovea);
-    else
-      hipLaunchKernelGGL(k_composite_bwd_f<false>, grid, dim3(256), 0, st, a, rgb_periphery,
-                         fovea_rgb, d_out, d_fovea);
+    const bool edge = mode == VRS_BLEND_PAPER && gamma != 0.0f;
+    hipLaunchKernelGGL((edge ? k_composite_bwd_f<true, ADD> : k_composite_bwd_f<false, ADD>), grid,
+                       dim3(256), 0, st, a, rgb_periphery, fovea_rgb, d_out, d_fovea);
     VRS_LAUNCH_CHECK();
   }
   return VRS_OK;
+}
+
+extern "C" vrs_status vrs_composite_frame_backward(const float* rgb_periphery, int n_views,
+                                                   int width, int height, const float* fovea_rgb,
+                                                   const vrs_crop* crops, int n_crops,
+                                                   const vrs_crop_place* place, int mode,
+                                                   float ring, float m, float gamma,
+                                                   const float* d_out, float* d_rgb_periphery,
+                                                   float* d_fovea, void* stream) {
+  return composite_backward<true>(rgb_periphery, n_views, width, height, fovea_rgb, crops, n_crops, place, mode, ring, m, gamma, d_out, d_rgb_periphery, d_fovea, stream);
+}
+
+extern "C" vrs_status vrs_composite_frame_backward_write(const float* rgb_periphery, int n_views,
+                                                   int width, int height, const float* fovea_rgb,
+                                                   const vrs_crop* crops, int n_crops,
+                                                   const vrs_crop_place* place, int mode,
+                                                   float ring, float m, float gamma,
+                                                   const float* d_out, float* d_rgb_periphery,
+                                                   float* d_fovea, void* stream) {
+  return composite_backward<false>(rgb_periphery, n_views, width, height, fovea_rgb, crops, n_crops, place, mode, ring, m, gamma, d_out, d_rgb_periphery, d_fovea, stream);
 }
 
 extern "C" vrs_status vrs_l1_loss(const float* pred, const float* target, int64_t n, float* loss,
@@ -632,6 +678,18 @@ extern "C" vrs_status vrs_l1_loss(const float* pred, const float* target, int64_
   else
     hipLaunchKernelGGL(k_l1<1>, dim3(blocks), dim3(256), 0, st, pred, target, (long long)n, loss,
                        d_pred, scale);
+  VRS_LAUNCH_CHECK();
+  return VRS_OK;
+}
+
+extern "C" vrs_status vrs_l1_loss_backward(const float* pred, const float* target, int64_t n,
+                                           const float* d_loss, float* d_pred, void* stream) {
+  if (!pred || !target || !d_pred || n < 1) return VRS_EINVAL;
+  const bool vec4 = ((reinterpret_cast<uintptr_t>(pred) | reinterpret_cast<uintptr_t>(target) |
+                      reinterpret_cast<uintptr_t>(d_pred)) & 15) == 0;
+  const int blocks = (int)std::min<int64_t>(8192, ((vec4 ? (n + 3) / 4 : n) + 255) / 256);
+  hipLaunchKernelGGL((vec4 ? k_l1_bwd<4> : k_l1_bwd<1>), dim3(blocks), dim3(256), 0,
+                     static_cast<hipStream_t>(stream), pred, target, (long long)n, d_loss, d_pred);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
 }

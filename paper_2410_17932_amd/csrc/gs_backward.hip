@@ -247,10 +247,11 @@ __device__ inline void sh_grad_dir(int deg, float x, float y, float z, const flo
 
 // HBM-bound: each attribute read once for all views (the SH coefficients stay
 // in registers), the gradient planes read and written, 40 B of moments and 12
-// of colour per view.  A Gaussian that no pixel took leaves its gradients
-// untouched.  1M Gaussians of degree 3, four views: 350 us (962 with the coefficients read
-// twice per view under branches).
-template <int DEG>
+// of colour per view.  1M Gaussians of degree 3, four views: 350 us adding
+// to the gradients (962 with the coefficients read twice per view under
+// branches), where a Gaussian that no pixel took leaves them untouched, and
+// 213 us writing them (no read of 232 MB, and none to be cleared before).
+template <int DEG, bool ADD>
 __global__ __launch_bounds__(256) void k_gs_project_bwd(
     const float* __restrict__ mean, const float* __restrict__ cov,
     const float* __restrict__ opacity, const float* __restrict__ sh, int64_t n, KViews views,
@@ -267,7 +268,19 @@ __global__ __launch_bounds__(256) void k_gs_project_bwd(
 #pragma unroll
     for (int q = 0; q < kG2d / 2; ++q) any |= G[q].x != 0.0f || G[q].y != 0.0f;
   }
-  if (!any) return;
+  auto put = [](float& p, float v) { p = ADD ? p + v : v; };
+  if (!any) {
+    if (!ADD) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d_mean[k * n + i] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) d_cov[k * n + i] = 0.0f;
+      d_op[i] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 3 * K; ++k) d_sh[k * n + i] = 0.0f;
+    }
+    return;
+  }
   const float mx = mean[i], my = mean[n + i], mz = mean[2 * n + i];
   float S6[6];
 #pragma unroll
@@ -388,16 +401,15 @@ __global__ __launch_bounds__(256) void k_gs_project_bwd(
     for (int k = 0; k < 3; ++k)
       dm[k] += cv.R[k] * dt[0] + cv.R[3 + k] * dt[1] + cv.R[6 + k] * dt[2] + dmv[k];
   }
-  d_mean[i] += dm[0];
-  d_mean[n + i] += dm[1];
-  d_mean[2 * n + i] += dm[2];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) d_cov[k * n + i] += dcv[k];
-  d_op[i] += dopa;
+  for (int k = 0; k < 3; ++k) put(d_mean[k * n + i], dm[k]);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) put(d_cov[k * n + i], dcv[k]);
+  put(d_op[i], dopa);
 #pragma unroll
   for (int k = 0; k < K; ++k)
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) d_sh[(k * 3 + ch) * n + i] += dshv[k][ch];
+    for (int ch = 0; ch < 3; ++ch) put(d_sh[(k * 3 + ch) * n + i], dshv[k][ch]);
 }
 
 template <int TILE>
@@ -419,8 +431,8 @@ static void launch_blend_bwd(const RenderWs& L, void* ws, int64_t n, const KView
 
 using namespace vrs;
 
-extern "C" vrs_status vrs_render_gaussians_backward(
-    const float* mean, const float* cov, const float* opacity, const float* sh, int sh_degree,
+static vrs_status render_backward(
+    bool add, const float* mean, const float* cov, const float* opacity, const float* sh, int sh_degree,
     int64_t n, const vrs_view* views, int n_views, const vrs_raster_opts* ro,
     const float* t_final, const float* d_rgb, const float* d_depth, float* d_mean, float* d_cov,
     float* d_opacity, float* d_sh, void* ws, size_t ws_bytes, int64_t max_pairs, void* stream) {
@@ -457,11 +469,31 @@ extern "C" vrs_status vrs_render_gaussians_backward(
                        d_opacity, d_sh);
   };
   switch (sh_degree) {
-    case 0: project(k_gs_project_bwd<0>); break;
-    case 1: project(k_gs_project_bwd<1>); break;
-    case 2: project(k_gs_project_bwd<2>); break;
-    default: project(k_gs_project_bwd<3>); break;
+    case 0: add ? project(k_gs_project_bwd<0, true>) : project(k_gs_project_bwd<0, false>); break;
+    case 1: add ? project(k_gs_project_bwd<1, true>) : project(k_gs_project_bwd<1, false>); break;
+    case 2: add ? project(k_gs_project_bwd<2, true>) : project(k_gs_project_bwd<2, false>); break;
+    default: add ? project(k_gs_project_bwd<3, true>) : project(k_gs_project_bwd<3, false>); break;
   }
   VRS_LAUNCH_CHECK();
   return VRS_OK;
+}
+
+extern "C" vrs_status vrs_render_gaussians_backward(
+    const float* mean, const float* cov, const float* opacity, const float* sh, int sh_degree,
+    int64_t n, const vrs_view* views, int n_views, const vrs_raster_opts* ro,
+    const float* t_final, const float* d_rgb, const float* d_depth, float* d_mean, float* d_cov,
+    float* d_opacity, float* d_sh, void* ws, size_t ws_bytes, int64_t max_pairs, void* stream) {
+  return render_backward(true, mean, cov, opacity, sh, sh_degree, n, views, n_views, ro, t_final,
+                         d_rgb, d_depth, d_mean, d_cov, d_opacity, d_sh, ws, ws_bytes, max_pairs,
+                         stream);
+}
+
+extern "C" vrs_status vrs_render_gaussians_backward_write(
+    const float* mean, const float* cov, const float* opacity, const float* sh, int sh_degree,
+    int64_t n, const vrs_view* views, int n_views, const vrs_raster_opts* ro,
+    const float* t_final, const float* d_rgb, const float* d_depth, float* d_mean, float* d_cov,
+    float* d_opacity, float* d_sh, void* ws, size_t ws_bytes, int64_t max_pairs, void* stream) {
+  return render_backward(false, mean, cov, opacity, sh, sh_degree, n, views, n_views, ro, t_final,
+                         d_rgb, d_depth, d_mean, d_cov, d_opacity, d_sh, ws, ws_bytes, max_pairs,
+                         stream);
 }

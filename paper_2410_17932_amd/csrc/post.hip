@@ -446,8 +446,9 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
 
 // d_x += scale (blur(A) + 2 (x - y) blur(B) + y blur(C')), scale =
 // -d_loss / N (the partials' adjoint: A + 2 x B + y C with C = C' - 2B).
-// Twelve 1024 x 1024 planes: 114 us (129 with 32 x 32 tiles; its 350 MB take
+// Twelve 1024 x 1024 planes: 114 us, 93 written (129 with 32 x 32 tiles; its 350 MB take
 // 74 at a copy's rate).
+template <bool ADD>   // else written
 __global__ __launch_bounds__(kSsBlock) void k_ssim_bwd(const float* __restrict__ x,
                                                        const float* __restrict__ y, SsArgs a,
                                                        const float* __restrict__ maps,
@@ -477,7 +478,7 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim_bwd(const float* __restrict__
           const int64_t i = pl * plane + (int64_t)py * a.W + px + c;
           const float yi = y[i];
           const float g = o[0][c] + 2.0f * (x[i] - yi) * o[1][c] + yi * o[2][c];
-          d_x[i] += scale * g;
+          d_x[i] = ADD ? d_x[i] + scale * g : scale * g;
         }
       });
 }
@@ -793,9 +794,10 @@ extern "C" vrs_status vrs_dssim(const float* x, const float* y, int planes, int 
   return VRS_OK;
 }
 
-extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width,
-                                         int height, const float* d_loss, float* d_x, void* ws,
-                                         size_t ws_bytes, void* stream) {
+template <bool ADD>
+static vrs_status dssim_backward(const float* x, const float* y, int planes, int width, int height,
+                                 const float* d_loss, float* d_x, void* ws, size_t ws_bytes,
+                                 void* stream) {
   if (!ss_ok(planes, width, height) || !x || !y || !d_x || !ws ||
       ws_bytes < vrs_dssim_workspace_size(planes, width, height))
     return VRS_EINVAL;
@@ -807,11 +809,23 @@ extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int pla
   hipLaunchKernelGGL(k_ssim<true>, dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
                      y, a, maps, nullptr);
   VRS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ssim_bwd, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0, st, x, y,
+  hipLaunchKernelGGL(k_ssim_bwd<ADD>, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0, st, x, y,
                      b, maps, d_loss,
                      (float)(1.0 / ((double)planes * width * height)), d_x);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
+}
+
+extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width,
+                                         int height, const float* d_loss, float* d_x, void* ws,
+                                         size_t ws_bytes, void* stream) {
+  return dssim_backward<true>(x, y, planes, width, height, d_loss, d_x, ws, ws_bytes, stream);
+}
+
+extern "C" vrs_status vrs_dssim_backward_write(const float* x, const float* y, int planes, int width,
+                                         int height, const float* d_loss, float* d_x, void* ws,
+                                         size_t ws_bytes, void* stream) {
+  return dssim_backward<false>(x, y, planes, width, height, d_loss, d_x, ws, ws_bytes, stream);
 }
 
 extern "C" size_t vrs_regulariser_workspace_size(void) {
