@@ -293,10 +293,16 @@ vrs_status vrs_dssim(const float* x, const float* y, int planes, int width, int 
 vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width, int height,
                               const float* d_loss, float* d_x, void* ws, size_t ws_bytes,
                               void* stream);
-/* The same, written instead of accumulated. */
-vrs_status vrs_dssim_backward_write(const float* x, const float* y, int planes, int width, int height,
-                              const float* d_loss, float* d_x, void* ws, size_t ws_bytes,
-                              void* stream);
+/* D-SSIM with the adjoint's derivative maps from the same pass over x and y:
+ * maps DEVICE memory of vrs_dssim_maps_size bytes, 4-byte aligned, kept for
+ * vrs_dssim_backward_maps, which WRITES what vrs_dssim_backward would add,
+ * from the same x and y. */
+size_t vrs_dssim_maps_size(int planes, int width, int height);
+vrs_status vrs_dssim_forward_maps(const float* x, const float* y, int planes, int width, int height,
+                                  float* loss, void* maps, size_t maps_bytes, void* stream);
+vrs_status vrs_dssim_backward_maps(const float* x, const float* y, int planes, int width,
+                                   int height, const void* maps, size_t maps_bytes,
+                                   const float* d_loss, float* d_x, void* stream);
 
 /* The regulariser of Eq. 7: R = |mean F - mean crop(P)|, the means over
  * every pixel and channel of all crops together: F the decoder output

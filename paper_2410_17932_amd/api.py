@@ -145,7 +145,9 @@ SIGNATURES = {
     "vrs_dssim_workspace_size": (_sz, [_int, _int, _int]),
     "vrs_dssim": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _sz, _vp]),
     "vrs_dssim_backward": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _vp, _sz, _vp]),
-    "vrs_dssim_backward_write": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _vp, _sz, _vp]),
+    "vrs_dssim_maps_size": (_sz, [_int, _int, _int]),
+    "vrs_dssim_forward_maps": (_int, [_vp, _vp, _int, _int, _int, _vp, _vp, _sz, _vp]),
+    "vrs_dssim_backward_maps": (_int, [_vp, _vp, _int, _int, _int, _vp, _sz, _vp, _vp, _vp]),
     "vrs_regulariser_workspace_size": (_sz, []),
     "vrs_regulariser": (_int, [_vp, _vp, _int, _int, _int, _P(Crop), _int, _vp, _vp, _vp, _sz,
                                _vp]),
@@ -623,12 +625,32 @@ def dssim(x, y, ws: DssimWorkspace, loss=None):
     return loss
 
 
-def dssim_backward(x, y, ws: DssimWorkspace, d_x, d_loss=None, accumulate=True):
-    """Gradient added to d_x (accumulate) or written."""
+def dssim_backward(x, y, ws: DssimWorkspace, d_x, d_loss=None):
     P, H, W = ws.shape
-    fn = lib().vrs_dssim_backward if accumulate else lib().vrs_dssim_backward_write
-    _check(fn(ptr(x, torch.float32), ptr(y, torch.float32), P, W, H, ptr(d_loss, torch.float32),
-              ptr(d_x), ptr(ws.buf), ws.buf.numel(), _stream()), "vrs_dssim_backward")
+    _check(lib().vrs_dssim_backward(ptr(x, torch.float32), ptr(y, torch.float32), P, W, H,
+                                    ptr(d_loss, torch.float32), ptr(d_x), ptr(ws.buf),
+                                    ws.buf.numel(), _stream()), "vrs_dssim_backward")
+
+
+def dssim_forward_maps(x, y, planes, width, height):
+    """(loss [1], maps): D-SSIM and, from the same pass, what its backward needs."""
+    size = lib().vrs_dssim_maps_size(planes, width, height)
+    if size == 0:
+        raise VrsError(VRS_EINVAL, "vrs_dssim_maps_size")
+    loss = torch.empty(1, dtype=torch.float32, device=x.device)
+    maps = torch.empty(size, dtype=torch.uint8, device=x.device)
+    _check(lib().vrs_dssim_forward_maps(ptr(x, torch.float32), ptr(y, torch.float32), planes,
+                                        width, height, ptr(loss), ptr(maps), size, _stream()),
+           "vrs_dssim_forward_maps")
+    return loss, maps
+
+
+def dssim_backward_maps(x, y, planes, width, height, maps, d_x, d_loss=None):
+    """d_x written from the forward's maps."""
+    _check(lib().vrs_dssim_backward_maps(ptr(x, torch.float32), ptr(y, torch.float32), planes,
+                                         width, height, ptr(maps), maps.numel(),
+                                         ptr(d_loss, torch.float32), ptr(d_x), _stream()),
+           "vrs_dssim_backward_maps")
 
 
 def regulariser(fovea, periphery, crops, place=None, r=None):

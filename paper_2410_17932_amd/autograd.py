@@ -182,18 +182,22 @@ class Dssim(torch.autograd.Function):
         pred, target = pred.contiguous(), target.contiguous()
         H, W = pred.shape[-2:]
         planes = pred.numel() // (H * W)
-        ws = _dssim_ws(planes, W, H, pred.device)
-        ctx.save_for_backward(pred, target)
-        return api.dssim(pred, target, ws)[0].clone()
+        if not ctx.needs_input_grad[0]:
+            return api.dssim(pred, target, _dssim_ws(planes, W, H, pred.device))[0].clone()
+        # one pass gives the loss and the backward's derivative maps
+        loss, maps = api.dssim_forward_maps(pred, target, planes, W, H)
+        ctx.save_for_backward(pred, target, maps)
+        return loss[0].clone()
 
     @staticmethod
     def backward(ctx, g):
-        pred, target = ctx.saved_tensors
+        if not ctx.needs_input_grad[0]:
+            return None, None
+        pred, target, maps = ctx.saved_tensors
         H, W = pred.shape[-2:]
-        ws = _dssim_ws(pred.numel() // (H * W), W, H, pred.device)
         d = torch.empty_like(pred)
-        api.dssim_backward(pred, target, ws, d, d_loss=g.reshape(1).contiguous(),
-                           accumulate=False)
+        api.dssim_backward_maps(pred, target, pred.numel() // (H * W), W, H, maps, d,
+                                d_loss=g.reshape(1).contiguous())
         return d, None
 
 

@@ -240,8 +240,8 @@ __global__ __launch_bounds__(256) void k_composite4_inplace(CompArgs a, float* i
 // pixel (one thread owns each gradient element, so nothing is atomic).  A
 // pixel under several crops walks those, and recomputes their masks, in both.
 // Four 1024 x 1024 views with a 512 crop each, with the edge term: 48 us and 28
-// us, 40 and 24 written instead of added (together 155 with per-pixel chains in scratch memory and 27 atomics per
-// edge pixel).
+// us, 40 and 24 written instead of added (together 155 with per-pixel chains in
+// scratch memory and 27 atomics per edge pixel).
 
 // The crops of view v over pixel (x, y), as bits (of those in `cand`).
 __device__ inline uint32_t comp_over(const CompArgs& a, int v, int x, int y, uint32_t cand) {
@@ -442,8 +442,7 @@ __global__ __launch_bounds__(256) void k_composite_bwd_f(CompArgs a, const float
 // (zeroed by the preceding fill), gradient scale*sign(pred - target)/n.
 // HBM-bound; two workgroups per compute unit, since every one ends with an
 // atomic on the same word (about 11 ns each: 12.6M elements in 4096
-// workgroups took 65 us, 35 now, 26 without
-// the gradient).
+// workgroups took 65 us, 35 now, 26 without the gradient).
 template <int VEC>
 __global__ __launch_bounds__(256) void k_l1(const float* __restrict__ pred,
                                             const float* __restrict__ target, long long n,

@@ -376,10 +376,10 @@ __device__ inline void ss_blur(const SsArgs& a, int X0, int Y0, float (*s_v)[NM]
 // in (mu_x, E[x^2]) and their combination with E[xy]'s, in the same
 // difference form (A, B, C' = C + 2B: A = -2 a2 D (mu_y (mu_x + mu_y) + C1)
 // / (b1^2 b2) + 2 a1 (D a2 - mu_y v_e) / (b1 b2^2), B = -SSIM / b2,
-// C' = 2 a1 v_e / (b1 b2^2)) to maps [3][planes][H][W]; else the block's sum
+// C' = 2 a1 v_e / (b1 b2^2)) to maps [3][planes][H][W].  SUM: the block's sum
 // of 1 - SSIM to partial[block].  Twelve 1024 x 1024 planes: 89 us,
-// and 116 with the maps (141 and 165 with 32 x 32 tiles).
-template <bool MAPS>
+// 116 the maps, 119 both in one pass (141 and 165 with 32 x 32 tiles).
+template <bool MAPS, bool SUM>
 __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
                                                    const float* __restrict__ y, SsArgs a,
                                                    float* __restrict__ maps,
@@ -425,12 +425,11 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
             maps[o2] = A;
             maps[all + o2] = -s / b2;
             maps[2 * all + o2] = 2.0f * a1 * ve * inv / b2;
-          } else {
-            sum += (b1 * ve + D * D * a2) * inv;
           }
+          if (SUM) sum += (b1 * ve + D * D * a2) * inv;
         }
       });
-  if (!MAPS) {
+  if (SUM) {
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) sum += __shfl_xor(sum, sh, 64);
     if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = sum;
@@ -446,7 +445,7 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
 
 // d_x += scale (blur(A) + 2 (x - y) blur(B) + y blur(C')), scale =
 // -d_loss / N (the partials' adjoint: A + 2 x B + y C with C = C' - 2B).
-// Twelve 1024 x 1024 planes: 114 us, 93 written (129 with 32 x 32 tiles; its 350 MB take
+// Twelve 1024 x 1024 planes: 114 us, 95 written (129 with 32 x 32 tiles; its 350 MB take
 // 74 at a copy's rate).
 template <bool ADD>   // else written
 __global__ __launch_bounds__(kSsBlock) void k_ssim_bwd(const float* __restrict__ x,
@@ -784,7 +783,7 @@ extern "C" vrs_status vrs_dssim(const float* x, const float* y, int planes, int 
   ss_args(planes, width, height, kSsResident, &a);
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* partial = static_cast<float*>(ws);
-  hipLaunchKernelGGL(k_ssim<false>, dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
+  hipLaunchKernelGGL((k_ssim<false, true>), dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
                      y, a, nullptr, partial);
   VRS_LAUNCH_CHECK();
   const int64_t nb = (int64_t)planes * a.tiles_x * a.tiles_y;
@@ -794,10 +793,9 @@ extern "C" vrs_status vrs_dssim(const float* x, const float* y, int planes, int 
   return VRS_OK;
 }
 
-template <bool ADD>
-static vrs_status dssim_backward(const float* x, const float* y, int planes, int width, int height,
-                                 const float* d_loss, float* d_x, void* ws, size_t ws_bytes,
-                                 void* stream) {
+extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width,
+                                         int height, const float* d_loss, float* d_x, void* ws,
+                                         size_t ws_bytes, void* stream) {
   if (!ss_ok(planes, width, height) || !x || !y || !d_x || !ws ||
       ws_bytes < vrs_dssim_workspace_size(planes, width, height))
     return VRS_EINVAL;
@@ -806,26 +804,58 @@ static vrs_status dssim_backward(const float* x, const float* y, int planes, int
   ss_args(planes, width, height, kSsResidentBwd, &b);
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* maps = static_cast<float*>(ws);
-  hipLaunchKernelGGL(k_ssim<true>, dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
+  hipLaunchKernelGGL((k_ssim<true, false>), dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
                      y, a, maps, nullptr);
   VRS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ssim_bwd<ADD>, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0, st, x, y,
+  hipLaunchKernelGGL(k_ssim_bwd<true>, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0, st, x, y,
                      b, maps, d_loss,
                      (float)(1.0 / ((double)planes * width * height)), d_x);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
 }
 
-extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int planes, int width,
-                                         int height, const float* d_loss, float* d_x, void* ws,
-                                         size_t ws_bytes, void* stream) {
-  return dssim_backward<true>(x, y, planes, width, height, d_loss, d_x, ws, ws_bytes, stream);
+extern "C" size_t vrs_dssim_maps_size(int planes, int width, int height) {
+  if (!ss_ok(planes, width, height)) return 0;
+  SsArgs a;
+  ss_args(planes, width, height, kSsResident, &a);
+  return vrs_dssim_workspace_size(planes, width, height) +
+         (size_t)planes * a.tiles_x * a.tiles_y * sizeof(float);
 }
 
-extern "C" vrs_status vrs_dssim_backward_write(const float* x, const float* y, int planes, int width,
-                                         int height, const float* d_loss, float* d_x, void* ws,
-                                         size_t ws_bytes, void* stream) {
-  return dssim_backward<false>(x, y, planes, width, height, d_loss, d_x, ws, ws_bytes, stream);
+extern "C" vrs_status vrs_dssim_forward_maps(const float* x, const float* y, int planes, int width,
+                                             int height, float* loss, void* maps,
+                                             size_t maps_bytes, void* stream) {
+  if (!ss_ok(planes, width, height) || !x || !y || !loss || !maps ||
+      maps_bytes < vrs_dssim_maps_size(planes, width, height))
+    return VRS_EINVAL;
+  SsArgs a;
+  ss_args(planes, width, height, kSsResident, &a);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  float* m = static_cast<float*>(maps);
+  float* partial = m + 3 * (int64_t)planes * width * height;
+  hipLaunchKernelGGL((k_ssim<true, true>), dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0,
+                     st, x, y, a, m, partial);
+  VRS_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_dssim_finish, dim3(1), dim3(256), 0, st, partial,
+                     (int64_t)planes * a.tiles_x * a.tiles_y,
+                     1.0 / ((double)planes * width * height), loss);
+  VRS_LAUNCH_CHECK();
+  return VRS_OK;
+}
+
+extern "C" vrs_status vrs_dssim_backward_maps(const float* x, const float* y, int planes, int width,
+                                              int height, const void* maps, size_t maps_bytes,
+                                              const float* d_loss, float* d_x, void* stream) {
+  if (!ss_ok(planes, width, height) || !x || !y || !d_x || !maps ||
+      maps_bytes < vrs_dssim_maps_size(planes, width, height))
+    return VRS_EINVAL;
+  SsArgs b;
+  ss_args(planes, width, height, kSsResidentBwd, &b);
+  hipLaunchKernelGGL(k_ssim_bwd<false>, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0,
+                     static_cast<hipStream_t>(stream), x, y, b, static_cast<const float*>(maps),
+                     d_loss, (float)(1.0 / ((double)planes * width * height)), d_x);
+  VRS_LAUNCH_CHECK();
+  return VRS_OK;
 }
 
 extern "C" size_t vrs_regulariser_workspace_size(void) {

@@ -72,7 +72,11 @@ def test_loss_gradients_written(n, shift):
     W, H = 67, 31
     a, b = (dev(rng.uniform(size=(3, H, W)), torch.float32) for _ in range(2))
     ws = api.DssimWorkspace(3, W, H)
-    zero, nan = torch.zeros_like(a), _nan(a)
+    zero = torch.zeros_like(a)
     api.dssim_backward(a, b, ws, zero, d_loss=scale)
-    api.dssim_backward(a, b, ws, nan, d_loss=scale, accumulate=False)
+    # the loss and the gradient from one pass's maps
+    loss, maps = api.dssim_forward_maps(a, b, 3, W, H)
+    assert torch.equal(loss, api.dssim(a, b, ws))
+    nan = _nan(a)
+    api.dssim_backward_maps(a, b, 3, W, H, maps, nan, d_loss=scale)
     assert torch.equal(zero, nan)
