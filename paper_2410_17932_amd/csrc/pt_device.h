@@ -63,13 +63,17 @@ __device__ inline bool pt_cull_pixel(const KView& cv, const PtGeom& g, int64_t& 
   pi = (int64_t)Y * cv.W + X;
   return true;
 }
-__device__ inline bool pt_hidden(float tz, float tf, float dep, float cov_min, float slack) {
+// The depth beyond which a pixel hides points (none where its coverage is too
+// low): slack times the mean depth of what covers it.
+__device__ inline float pt_hide_limit(float tf, float dep, float cov_min, float slack) {
 #pragma clang fp contract(off)
   const float A = 1.0f - tf;
-  if (!(A >= cov_min)) return false;
+  if (!(A >= cov_min)) return __builtin_inff();
   const float q = dep / A;
-  const float lim = slack * q;
-  return tz > lim;
+  return slack * q;
+}
+__device__ inline bool pt_hidden(float tz, float tf, float dep, float cov_min, float slack) {
+  return tz > pt_hide_limit(tf, dep, cov_min, slack);
 }
 
 // Layer-l coordinates of the point in a crop with origin (x0, y0) and the

@@ -72,3 +72,37 @@ def test_ordered_splat_past_the_capacity():
     pyr = api.splat_points(dev(p["pos"]), dev(p["radius"]), feat, None, views, crops, L, None, None, ws)
     assert int(ws.status.item()) == api.VRS_ECAPACITY and ws.frag_count() == nf
     assert float(pyr.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("n", [3000, 20001])
+def test_hiding_depths_cull_as_coverage_and_depth(n):
+    """Many points over a small image are culled against one image of hiding
+    depths, stored points with a numbering against coverage and depth: the same
+    lists to the bit, at coverages around the least, zero, infinite and
+    not-a-number depths, and as the reference's."""
+    W, H, L, cov_min, slack = 61, 47, 3, 0.5, 1.05
+    rng = np.random.default_rng(n)
+    views = [synth.pinhole(W, H, 60.0)]
+    crops = [synth.crop_at(0, 30.0, 24.0, 32, W, H)]
+    p = synth.points(rng, n, "uniform", xy=(-0.6, 0.6))
+    tf = rng.choice([0.0, 0.3, 0.5, np.nextafter(np.float32(0.5), np.float32(1)), 0.7, 1.0],
+                    (1, H, W)).astype(np.float32)
+    dep = (rng.uniform(1.5, 6.0, (1, H, W)) * (1 - tf)).astype(np.float32)
+    feat = dev(np.ascontiguousarray(p["feat"]).view(np.int16))
+    V, D = synth.views_array(views), synth.views_dims(views)
+    ci, _ = synth.crops_array(crops)
+    nf = len(oracle.point_frags(p["pos"], p["radius"], V, D, ci, L))
+    def lists(d, ids):
+        ws = api.SplatWorkspace(n, views, crops, L, nf)
+        pyr = api.splat_points(dev(p["pos"]), dev(p["radius"]), feat, None, views, crops, L, dev(d),
+                               dev(tf), ws, cov_min=cov_min, slack=slack, point_ids=ids)
+        assert int(ws.status.item()) == 0
+        return (*ws.lists(), pyr.cpu().numpy())
+    odd = dep.copy()
+    odd.flat[::7], odd.flat[1::11], odd.flat[2::13] = 0.0, np.inf, np.nan
+    for d in (dep, odd):
+        a, b = lists(d, None), lists(d, torch.arange(n, dtype=torch.int32, device="cuda"))
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
+        assert 0 < len(a[0]) < nf
+    off, oids = oracle.point_lists(p["pos"], p["radius"], V, D, ci, L, dep, tf, cov_min, slack)
+    assert np.array_equal(lists(dep, None)[1], oids)
