@@ -81,8 +81,10 @@ class SplatPoints(torch.autograd.Function):
         pos, radius, op = ctx.saved_tensors
         feat_h, views, crops, levels, ws, has_op, gen = ctx.meta
         _check_generation(ws, gen, "SplatPoints")
-        d_pos, d_r = torch.zeros_like(pos), torch.zeros_like(radius)
-        d_feat = torch.zeros((pos.shape[1], 4), device=pos.device)
+        # one fill for the three (few operations: small splats are bound by them)
+        n = pos.shape[1]
+        d_pos, d_r, d_feat = torch.zeros((8, n), device=pos.device, dtype=torch.float32).split((3, 1, 4))
+        d_r, d_feat = d_r.view(radius.shape), d_feat.view(n, 4)
         d_op = torch.zeros_like(op) if has_op else None
         api.splat_points_backward(pos, radius, feat_h, op if has_op else None, views, crops,
                                   levels, d_pyr.contiguous(), ws, d_feat=d_feat, d_pos=d_pos,

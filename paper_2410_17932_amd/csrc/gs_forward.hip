@@ -587,29 +587,31 @@ __global__ __launch_bounds__(64) void k_gs_schedule(
 // cursor + rank.  Nothing is written past the capacity (the lists are then
 // left empty).
 //
-// The entries of as many rounds as the stage holds are laid out tile by tile
-// in LDS first (lane = tile, each lane taking its reaching pairs in order, as
-// pair number | tile << 8), then written by consecutive lanes: a tile's
+// The entries of as many half rounds as the stage holds are laid out tile by
+// tile in LDS first (lane = tile, each lane taking its reaching pairs in order,
+// as pair number | tile << 8), then written by consecutive lanes: a tile's
 // entries are consecutive words, so a store of 64 of them touches a handful of
 // cache lines.  Bound by the instructions of the staging loop.  A store per
-// round and tile, with the lanes that reach it active, took 64 stores a round
-// whatever they held, 16 clocks of address processing each: 2.4M pairs on 137
-// super-tiles (32M entries) 73 us against 56, 8.2M pairs on 256 (87M) 217
-// against 149, 10.8M on 2205 (395M entries, 36 lanes a store) 761 against 745.
-constexpr int kBinStage = 4096;   // a round of 64 pairs on 64 tiles
-__global__ __launch_bounds__(256) void k_gs_bin_scatter(
+// round and tile, with the lanes that reach it active, takes 64 stores a round
+// whatever they hold, 16 clocks of address processing each: 2.4M pairs on 137
+// super-tiles (32M entries) 73 us against 55, 8.2M pairs on 256 (87M) 217
+// against 150.  3072 entries a wave: with 2048 a unit's entries go out in
+// shorter runs (175 us), with 4096 fewer waves fit (152, and the direct form
+// below, which shares the LDS, 10% slower).
+constexpr int kBinStage = 3072;   // at least half a round, 32 pairs, on 64 tiles
+struct BinStage {
+  uint32_t id[4][kBinUnit], base[4][64];
+  uint16_t stage[4][kBinStage];
+};
+__device__ inline void bin_scatter_staged(
     const uint64_t* __restrict__ svals, const uint2* __restrict__ srange,
-    const uint32_t* __restrict__ ubase, const uint32_t* __restrict__ nunits_p, int64_t st_total,
-    const uint32_t* __restrict__ ucnt, const uint32_t* __restrict__ toff,
-    const uint32_t* __restrict__ total_p, int64_t max_pairs, int64_t sxn, int64_t spv,
-    int64_t tiles_x, int64_t tiles_y, uint32_t* __restrict__ ids) {
+    const uint32_t* __restrict__ ubase, uint32_t nunits, int64_t st_total,
+    const uint32_t* __restrict__ ucnt, const uint32_t* __restrict__ toff, int64_t sxn, int64_t spv,
+    int64_t tiles_x, int64_t tiles_y, uint32_t* __restrict__ ids,
+    BinStage& st) {
   static_assert(kBinUnit <= 256, "pair numbers take eight bits");
   constexpr int NR = kBinUnit / 64;
-  __shared__ uint32_t s_id[4][kBinUnit], s_base[4][64];
-  __shared__ uint16_t s_stage[4][kBinStage];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if ((int64_t)*total_p > max_pairs) return;
-  const uint32_t nunits = *nunits_p;
   for (uint32_t u = blockIdx.x * 4u + wave; u < nunits; u += gridDim.x * 4u) {
     uint32_t lo, hi;
     const int64_t s = bin_unit(ubase, st_total, srange, u, &lo, &hi);
@@ -625,16 +627,17 @@ __global__ __launch_bounds__(256) void k_gs_bin_scatter(
       r[k] = j < hi ? svals[j] : 0ull;
     }
     // per round: the pairs reaching lane l's tile, the earlier tiles' entries
-    // and the round's
+    // and the round's, those of the lower 32 pairs in the low half word
     uint64_t M[NR];
     uint32_t excl[NR], tot[NR];
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
-      s_id[wave][64 * k + lane] = (uint32_t)r[k];
+      st.id[wave][64 * k + lane] = (uint32_t)r[k];
       uint64_t R[kSuper], X[kSuper];
       bin_masks((uint32_t)(r[k] >> 32), lo + 64 * k + lane < hi, R, X);
       M[k] = bin_lane_mask(R, X, lane);
-      const uint32_t c = (uint32_t)__popcll(M[k]);
+      const uint32_t c = (uint32_t)__popc((uint32_t)M[k]) |
+                         (uint32_t)__popc((uint32_t)(M[k] >> 32)) << 16;
       uint32_t incl = c;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -644,44 +647,118 @@ __global__ __launch_bounds__(256) void k_gs_bin_scatter(
       excl[k] = incl - c;
       tot[k] = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
-    for (int k0 = 0; k0 < NR;) {   // uniform over the wave, as all below
+    auto half = [](const uint32_t* x, int h) { return h & 1 ? x[h >> 1] >> 16 : x[h >> 1] & 0xffffu; };
+    for (int h0 = 0; h0 < 2 * NR;) {   // uniform over the wave, as all below
       uint32_t sum = 0, first = 0;
-      int k1 = k0;   // rounds [k0, k1)
+      int h1 = h0;   // half rounds [h0, h1)
 #pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        if (k != k1 || sum + tot[k] > kBinStage) continue;
-        sum += tot[k];
-        first += excl[k];
-        ++k1;
+      for (int h = 0; h < 2 * NR; ++h) {
+        if (h != h1 || sum + half(tot, h) > kBinStage) continue;
+        sum += half(tot, h);
+        first += half(excl, h);
+        ++h1;
       }
       uint32_t p = first;
-      s_base[wave][lane] = cursor - first;
+      st.base[wave][lane] = cursor - first;
 #pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        if (k < k0 || k >= k1) continue;
-        uint32_t m = (uint32_t)M[k];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          while (m) {
-            const uint32_t b = (uint32_t)__builtin_ctz(m);
-            m &= m - 1;
-            s_stage[wave][p++] = (uint16_t)((64 * k + 32 * h + b) | (uint32_t)lane << 8);
-          }
-          m = (uint32_t)(M[k] >> 32);
+      for (int h = 0; h < 2 * NR; ++h) {
+        if (h < h0 || h >= h1) continue;
+        uint32_t m = (uint32_t)(M[h >> 1] >> (32 * (h & 1)));
+        while (m) {
+          const uint32_t b = (uint32_t)__builtin_ctz(m);
+          m &= m - 1;
+          st.stage[wave][p++] = (uint16_t)((32 * h + b) | (uint32_t)lane << 8);
         }
       }
       cursor += p - first;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       for (uint32_t i = lane; i < sum; i += 64) {
-        const uint32_t e = s_stage[wave][i];
-        ids[s_base[wave][e >> 8] + i] = s_id[wave][e & 255u];
+        const uint32_t e = st.stage[wave][i];
+        ids[st.base[wave][e >> 8] + i] = st.id[wave][e & 255u];
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();   // LDS is rewritten by the next rounds
-      k0 = k1;
+      h0 = h1;
     }
   }
+}
+
+// The other way: per round and tile one store by the lanes whose pairs reach it.
+// su: the wave's copy of its unit's pairs (a lane reads back what it wrote).
+__device__ inline void bin_scatter_direct(
+    const uint64_t* __restrict__ svals, const uint2* __restrict__ srange,
+    const uint32_t* __restrict__ ubase, uint32_t nunits, int64_t st_total,
+    const uint32_t* __restrict__ ucnt, const uint32_t* __restrict__ toff, int64_t sxn, int64_t spv,
+    int64_t tiles_x, int64_t tiles_y, uint32_t* __restrict__ ids,
+    uint64_t* su) {
+  const int lane = threadIdx.x & 63;
+  for (uint32_t u = blockIdx.x * 4u + (threadIdx.x >> 6); u < nunits; u += gridDim.x * 4u) {
+    uint32_t lo, hi;
+    const int64_t s = bin_unit(ubase, st_total, srange, u, &lo, &hi);
+    int64_t t;
+    uint32_t cursor = 0;
+    if (bin_tile(s, lane, sxn, spv, tiles_x, tiles_y, &t))
+      cursor = toff[t] + ucnt[(int64_t)u * 64 + lane];
+    // Every load of the unit in flight at once, then parked in LDS.  A load
+    // issued inside the round loop would have to complete before the next
+    // round, and the loads and stores of one wave share a single in-order
+    // completion counter: that wait would drain the round's 64 stores too.
+    {
+      uint64_t r[kBinUnit / 64];
+#pragma unroll
+      for (int k = 0; k < kBinUnit / 64; ++k) {
+        const uint32_t j = lo + 64 * k + lane;
+        r[k] = j < hi ? svals[j] : 0ull;
+      }
+#pragma unroll
+      for (int k = 0; k < kBinUnit / 64; ++k) su[64 * k + lane] = r[k];
+    }
+    for (uint32_t i = lo, k = 0; i < hi; i += 64, ++k) {
+      const uint64_t cur = su[64 * k + lane];
+      const uint32_t gi = (uint32_t)cur;
+      uint64_t R[kSuper], X[kSuper];
+      bin_masks((uint32_t)(cur >> 32), i + lane < hi, R, X);
+#pragma unroll
+      for (int l = 0; l < 64; ++l) {
+        // the lanes reaching tile l are those of M (a wave-uniform mask, the
+        // store's execution mask): the rank is a bit count
+        const uint64_t M = R[l >> 3] & X[l & 7];
+        const uint32_t at_l = (uint32_t)__builtin_amdgcn_readlane((int)cursor, l);
+        if (__builtin_amdgcn_inverse_ballot_w64(M))
+          ids[at_l + __builtin_amdgcn_mbcnt_hi((uint32_t)(M >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)M, 0u))] = gi;
+      }
+      cursor += bin_lane_count(R, X, lane);
+    }
+  }
+}
+
+// Direct up to kBinDirect units (one round of the chip's waves, where a unit's
+// own time is what counts and the staging's loops take longer than 64 stores a
+// round: 4000 units with 11M tile entries 25 us, 27 staged; half as many 18 and
+// 24; twice as many 56 and 46), and where a unit holds under four entries per
+// pair (most of the 64 stores are then skipped: at 2.5 entries per pair, 4M
+// pairs, 56 us and 62 staged; at 4 73 and 62; at 10 211 and 147).
+constexpr uint32_t kBinDirect = 4096, kBinSparse = 4 * kBinUnit;
+__global__ __launch_bounds__(256) void k_gs_bin_scatter(
+    const uint64_t* __restrict__ svals, const uint2* __restrict__ srange,
+    const uint32_t* __restrict__ ubase, const uint32_t* __restrict__ nunits_p, int64_t st_total,
+    const uint32_t* __restrict__ ucnt, const uint32_t* __restrict__ toff,
+    const uint32_t* __restrict__ total_p, int64_t max_pairs, int64_t sxn, int64_t spv,
+    int64_t tiles_x, int64_t tiles_y, uint32_t* __restrict__ ids) {
+  __shared__ union {
+    BinStage staged;
+    uint64_t direct[4][kBinUnit];
+  } sh;
+  if ((int64_t)*total_p > max_pairs) return;
+  const uint32_t nunits = *nunits_p;
+  if (nunits <= kBinDirect || *total_p < (uint64_t)kBinSparse * nunits)
+    bin_scatter_direct(svals, srange, ubase, nunits, st_total, ucnt, toff, sxn, spv, tiles_x,
+                       tiles_y, ids, sh.direct[threadIdx.x >> 6]);
+  else
+    bin_scatter_staged(svals, srange, ubase, nunits, st_total, ucnt, toff, sxn, spv, tiles_x,
+                       tiles_y, ids, sh.staged);
 }
 
 }  // namespace vrs

@@ -363,6 +363,9 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
   extern __shared__ __align__(16) char s_dyn[];
   const int nv = views.n;
   uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_dyn);   // [round][view][tid]
+  // and the depths, where there is room for them
+  constexpr bool DEPTHS = kSelBlock <= 256;
+  float* s_zd = reinterpret_cast<float*>(s_dyn) + kSelRounds * nv * kSelBlock;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int e = tid; e < NSLOT; e += kSelBlock) {
     s_mask[e] = 0;
@@ -398,6 +401,9 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
     px[j] = py[j] = pz[j] = pr[j] = 0.0f;
     if (pin[j]) { px[j] = pos[i]; py[j] = pos[np + i]; pz[j] = pos[2 * np + i]; pr[j] = radius[i]; }
   }
+  // one source or the other without a branch between the loads
+  const float* __restrict__ under_t = hide ? hide : tfinal;
+  const float* __restrict__ under_d = hide ? hide : depth;
   for (int v = 0; v < nv; ++v) {
     const KView& cv = views.v[v];
     const bool vm = (a.view_mask >> v) & 1u;
@@ -419,8 +425,8 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
         int64_t pi;
         cull[j] = ok[j] && tfinal && pt_cull_pixel(cv, g, pi);
         if (cull[j]) {   // T' and depth, or the pixel's hiding depth
-          tf[j] = hide ? hide[v * plane + pi] : tfinal[v * plane + pi];
-          dp[j] = hide ? 0.0f : depth[v * plane + pi];
+          tf[j] = under_t[v * plane + pi];
+          dp[j] = under_d[v * plane + pi];
         }
       }
     }
@@ -444,6 +450,7 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
         }
       }
       s_cnt[(j * nv + v) * kSelBlock + tid] = cnt | bucket << 16;
+      if (DEPTHS) s_zd[(j * nv + v) * kSelBlock + tid] = tz[j];
       const uint64_t m = __ballot(cnt != 0);
       if (m) {   // the slot's fragment total
         uint32_t fs = cnt;
@@ -519,9 +526,15 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
           (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
       const uint32_t p = base + s_pre[slot] + below;
       const uint32_t fo = fbase + s_fpre[slot] + fi - cnt;
-      PtGeom g;   // its depth again: cheaper than a place for every (view, point)
-      pt_geom32(views.v[v], pos[i], pos[np + i], pos[2 * np + i], radius[i], a.levels, g);
-      surv[p] = make_uint4((uint32_t)(v * np + i), __float_as_uint(g.t[2]), fo, cw);
+      float z;
+      if constexpr (DEPTHS) {
+        z = s_zd[(j * nv + v) * kSelBlock + tid];
+      } else {
+        PtGeom g;
+        pt_geom32(views.v[v], pos[i], pos[np + i], pos[2 * np + i], radius[i], a.levels, g);
+        z = g.t[2];
+      }
+      surv[p] = make_uint4((uint32_t)(v * np + i), __float_as_uint(z), fo, cw);
       // the emission chunks whose first fragment is one of this survivor's
       for (uint64_t c = ((uint64_t)fo + kEmitFrags - 1) / kEmitFrags;
            c * kEmitFrags < (uint64_t)fo + cnt && c * kEmitFrags < (uint64_t)max_frags; ++c)
@@ -1313,13 +1326,15 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
     return VRS_OK;
   }
   uint32_t* live = at<uint32_t>(ws, L.live);
-  // without the cull every workgroup has survivors, and what it waits for is
-  // its atomic on their one counter (about 11 ns each): half as many of them
-  // (5M points: 97 -> 72 us).  With it the reads under the points bound it
-  // (two 2016 x 2240 views: 62 us, 65 with 512).
-  const int sel_block = t_final ? 256 : 512;
+  // Without the cull every workgroup has survivors, and what many of them wait
+  // for is their atomic on the one counter (about 11 ns each): half as many of
+  // them (5M points: 97 -> 72 us).  With it the reads under the points bound it
+  // (two 2016 x 2240 views: 62 us, 65 with 512), and under 1M points too few
+  // workgroups would be left.
+  const bool wide = !t_final && np >= (int64_t(1) << 20);
+  const int sel_block = wide ? 512 : 256;
   const int sel_parts = div_up(np, sel_block * kSelRounds);
-  const size_t sel_lds = (size_t)kSelRounds * n_views * sel_block * 4;
+  const size_t sel_lds = (size_t)kSelRounds * n_views * 256 * 8;   // (counts alone with 512)
   uint32_t* grid = at<uint32_t>(ws, L.grid);
   // Points in no spatial order read T' and depth from a cache line each.  One
   // image of the depths that hide points halves those reads; it costs 12 bytes
@@ -1344,7 +1359,7 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
     VRS_LAUNCH_CHECK();
   }
   // survivors with their fragment offsets (compaction order), then emission
-  auto select = t_final ? k_pt_select<256> : k_pt_select<512>;
+  auto select = wide ? k_pt_select<512> : k_pt_select<256>;
   hipLaunchKernelGGL(select, dim3(sel_parts), dim3(sel_block), sel_lds, st, pos, radius, np, kv, kc,
                      a, depth, t_final, hide, grid, L.gx, L.gy, at<uint4>(ws, L.surv),
                      at<uint64_t>(ws, L.ctr), at<uint32_t>(ws, L.chunk_first), max_frags,
