@@ -852,8 +852,9 @@ __global__ __launch_bounds__(kEmitBlock) void k_pt_emit(
 // Each fragment's record (point index, depth key, weight, pixel) to its
 // segment place (checked against the segment, so an unresolved place can
 // never write outside it).  The place replaces the fragment's slot and, once
-// the fragment is ranked, its final place the record's pixel: the adjoint's
-// way from a point's fragments to the sorted lists.
+// the fragment is ranked, its final place goes to the depth keys' array (free
+// by then), by place: the adjoint's way from a point's fragments to the sorted
+// lists.
 __global__ __launch_bounds__(256) void k_pt_scatter(const uint32_t* __restrict__ fkey,
                                                     const uint64_t* __restrict__ fval,
                                                     const uint32_t* __restrict__ fdep,
@@ -882,7 +883,8 @@ __global__ __launch_bounds__(256) void k_pt_scatter(const uint32_t* __restrict__
 // Consecutive places share segments, so the lanes of a segment read the
 // same records; places go in reverse, so that the long segments of each
 // crop's coarse layers start early.
-__global__ __launch_bounds__(256) void k_pt_rank(uint4* seg,
+__global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
+                                                 uint32_t* __restrict__ fin,
                                                  const uint32_t* __restrict__ poff,
                                                  const uint32_t* __restrict__ total_p,
                                                  int64_t max_frags, int64_t pix_total,
@@ -931,7 +933,7 @@ __global__ __launch_bounds__(256) void k_pt_rank(uint4* seg,
     }
     okey[start + rank] = rec.w;
     oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
-    seg[total - 1 - sr].w = start + rank;   // read by this thread alone
+    fin[total - 1 - sr] = start + rank;
   }
 }
 
@@ -997,12 +999,14 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
 // segment and k_pt_blend walks a segment in one thread, so both grow with
 // the list length: 5M points under one 512 crop (27M fragments, lists to
 // 2000) took 7.4 + 0.95 ms.  Here a wave takes each pixel, and the workgroup
-// together those with more than 64 fragments: they are ranked through 1024
+// together those with more than 256 fragments: they are ranked through 1024
 // depth buckets (count, scan, place, then a comparison within the bucket
-// alone), then each wave composites its pixel: the lanes gather 64 fragments'
+// alone; up to 64 a lane's one fragment against all, up to 256 four), then each
+// wave composites its pixel: the lanes gather 64 fragments'
 // weights and features at a time, and the sums run over them one by one in
 // list order, a channel per lane (the same operations in the same order as
-// k_pt_blend, so the results are the same to the bit): 0.93 ms.
+// k_pt_blend, so the results are the same to the bit): 0.96 ms, of which the
+// records, the lists and 8-byte features from scattered lines are most.
 //
 // It takes the splats that counted over kRsDense fragments per layer pixel;
 // the count is on the device, so where the capacity allows that many all three
@@ -1010,10 +1014,72 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
 // whole splat, this kernel against the two: 435 us against 325 at 6.6
 // fragments per pixel, 622 against 704 at 13, 3.2 ms against 11.8 at 77 (a
 // wave per pixel idles on short lists).
+constexpr uint32_t kRsWave = 256;   // fragments that one wave ranks
 constexpr int kRsCap = 4096, kRsBuckets = 1024, kRsPix = 4;   // pixels per workgroup, one wave each
 
+// A list of at most 64 R fragments ranked by one wave, R per lane in registers,
+// each compared with all of them by broadcast.  Beyond one fragment per lane
+// the ranks' sum tells whether any depths are equal (each equal pair is
+// missing from it); those take the points' own order.
+template <int R>
+__device__ inline void rs_rank_wave(const uint4* __restrict__ seg, uint32_t start, int n,
+                                    uint32_t pixel, uint32_t* __restrict__ fin,
+                                    const uint32_t* __restrict__ ids, uint32_t* okey,
+                                    uint64_t* oval, int lane) {
+  uint4 rec[R];
+  uint32_t rank[R], sum = 0, same = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    rec[r] = lane + 64 * r < n ? seg[start + lane + 64 * r] : make_uint4(0, 0, 0, 0);
+    rank[r] = 0;
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int m = min(64, n - 64 * q);
+    for (int j = 0; j < m; ++j) {
+      const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)rec[q].y, j);
+#pragma unroll
+      for (int r = 0; r < R; ++r) rank[r] += d < rec[r].y ? 1u : 0u;
+      if (R == 1) same += d == rec[0].y ? 1u : 0u;
+    }
+  }
+  bool ties;
+  if (R == 1) {
+    ties = __ballot(lane < n && same > 1) != 0;
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum += lane + 64 * r < n ? rank[r] : 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += (uint32_t)__shfl_xor((int)sum, o, 64);
+    ties = __builtin_amdgcn_readfirstlane((int)sum) != n * (n - 1) / 2;
+  }
+  if (ties) {
+    uint32_t own[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) own[r] = ids && lane + 64 * r < n ? ids[rec[r].x] : rec[r].x;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int m = min(64, n - 64 * q);
+      for (int j = 0; j < m; ++j) {
+        const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)rec[q].y, j);
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)own[q], j);
+#pragma unroll
+        for (int r = 0; r < R; ++r) rank[r] += d == rec[r].y && o < own[r] ? 1u : 0u;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (lane + 64 * r >= n) continue;
+    okey[start + rank[r]] = pixel;
+    oval[start + rank[r]] = ((uint64_t)rec[r].z << 32) | rec[r].x;
+    fin[start + lane + 64 * r] = start + rank[r];
+  }
+}
+
 __global__ __launch_bounds__(256) void k_pt_resolve(
-    uint4* seg, const uint32_t* __restrict__ poff,
+    const uint4* __restrict__ seg, uint32_t* __restrict__ fin,
+    const uint32_t* __restrict__ poff,
     const uint32_t* __restrict__ total_p, int64_t max_frags, int64_t pix_total,
     const uint32_t* __restrict__ ids, const uint16_t* __restrict__ feat,
     const float* __restrict__ opacity, int64_t np, uint32_t* __restrict__ okey,
@@ -1035,33 +1101,17 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
       nw = poff[kw + 1] - start_w;
     }
     if (lane == 0) s_n[wave] = nw;
-    if (nw <= 64 && lane < (int)nw) {
-      // one fragment per lane, ranked against each other in registers
-      const uint4 rec = seg[start_w + lane];
-      uint32_t rank = 0, same = 0;
-      for (uint32_t j = 0; j < nw; ++j) {
-        const uint32_t d = __builtin_amdgcn_readlane(rec.y, j);
-        rank += d < rec.y ? 1u : 0u;
-        same += d == rec.y ? 1u : 0u;
-      }
-      if (__ballot(same > 1)) {   // equal depths: the points' own order
-        const uint32_t own = ids ? ids[rec.x] : rec.x;
-        for (uint32_t j = 0; j < nw; ++j)
-          rank += (uint32_t)__builtin_amdgcn_readlane(rec.y, j) == rec.y &&
-                          (uint32_t)__builtin_amdgcn_readlane(own, j) < own
-                      ? 1u : 0u;
-      }
-      okey[start_w + rank] = (uint32_t)kw;
-      oval[start_w + rank] = ((uint64_t)rec.z << 32) | rec.x;
-      seg[start_w + lane].w = start_w + rank;
-    }
+    // (uniform over the wave)
+    if (nw <= 64) rs_rank_wave<1>(seg, start_w, (int)nw, (uint32_t)kw, fin, ids, okey, oval, lane);
+    else if (nw <= 128) rs_rank_wave<2>(seg, start_w, (int)nw, (uint32_t)kw, fin, ids, okey, oval, lane);
+    else if (nw <= kRsWave) rs_rank_wave<4>(seg, start_w, (int)nw, (uint32_t)kw, fin, ids, okey, oval, lane);
     __syncthreads();
     for (int w = 0; w < kRsPix; ++w) {
       const uint32_t n = s_n[w];
-      if (n <= 64) continue;   // uniform over the workgroup
+      if (n <= kRsWave) continue;   // uniform over the workgroup
       const int64_t k = k0 + w;
       const uint32_t start = poff[k];
-      uint4* sg = seg + start;
+      const uint4* sg = seg + start;
       // range of the depth keys
       uint32_t lo = ~0u, hi = 0u;
       for (uint32_t i = tid; i < n; i += 256) {
@@ -1159,7 +1209,7 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
             }
             okey[start + rank] = (uint32_t)k;
             oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
-            sg[(uint32_t)e].w = start + rank;
+            fin[start + (uint32_t)e] = start + rank;
           }
         } else {
           // one bucket beyond the LDS (thousands of nearly equal depths)
@@ -1174,7 +1224,7 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
             }
             okey[start + rank] = (uint32_t)k;
             oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
-            sg[i].w = start + rank;
+            fin[start + i] = start + rank;
           }
         }
         __syncthreads();
@@ -1407,13 +1457,15 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
   // unit, what the LDS holds), short ones by a thread per fragment and pixel
   if (max_frags > kRsDense * L.pix_total) {
     const unsigned rb = (unsigned)std::min<int64_t>(4 * device_cus(), div_up(L.pix_total, kRsPix));
-    hipLaunchKernelGGL(k_pt_resolve, dim3(rb), dim3(256), 0, st, at<uint4>(ws, L.seg), poff,
+    hipLaunchKernelGGL(k_pt_resolve, dim3(rb), dim3(256), 0, st, at<uint4>(ws, L.seg),
+                       at<uint32_t>(ws, L.fdep), poff,
                        frag_count, max_frags, L.pix_total, point_ids, feat, opacity, np,
                        at<uint32_t>(ws, L.fkey1), at<uint64_t>(ws, L.fval1),
                        reinterpret_cast<float4*>(pyramid));
     VRS_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(k_pt_rank, dim3(fb), dim3(256), 0, st, at<uint4>(ws, L.seg), poff,
+  hipLaunchKernelGGL(k_pt_rank, dim3(fb), dim3(256), 0, st, at<uint4>(ws, L.seg),
+                     at<uint32_t>(ws, L.fdep), poff,
                      frag_count, max_frags, L.pix_total, point_ids, at<uint32_t>(ws, L.fkey1),
                      at<uint64_t>(ws, L.fval1));
   VRS_LAUNCH_CHECK();
@@ -1553,7 +1605,7 @@ __global__ __launch_bounds__(256) void k_pt_scan_bwd(
 // A quad of lanes per survivor walks its crops and layers as the emission
 // did, a lane per footprint target, so that the target's fragment is the next
 // of the survivor's in emission order; its place in the sorted lists is
-// fslot -> seg.w.  The quad's sums go out once per survivor (two atomic
+// fslot -> fin.  The quad's sums go out once per survivor (two atomic
 // instructions) instead of eight scattered atomics per fragment, which bound
 // the per-fragment form (726 us against 91).
 // res: each sorted fragment's alpha T and alpha gradient.
@@ -1568,7 +1620,7 @@ __global__ __launch_bounds__(256) void k_pt_blend_bwd(
     const uint4* __restrict__ surv1, const uint4* __restrict__ surv2, int64_t pix_total,
     const uint32_t* __restrict__ live_p, const uint32_t* __restrict__ total_p, int64_t max_frags,
     const uint32_t* __restrict__ fslot,
-    const uint4* __restrict__ seg, const float* __restrict__ pos,
+    const uint32_t* __restrict__ fin, const float* __restrict__ pos,
     const float* __restrict__ radius, const float* __restrict__ opacity, int64_t np, KViews views,
     KCrops crops, PtArgs a, const uint32_t* __restrict__ grid, int gx, int gy,
     const float4* __restrict__ dpyr, const float2* __restrict__ res, float* __restrict__ d_feat,
@@ -1621,9 +1673,9 @@ __global__ __launch_bounds__(256) void k_pt_blend_bwd(
           if ((dx ? x1 : x0) && (dy ? y1 : y0)) {
             const int64_t e = at + (dy && y0 ? nx : 0) + (dx && x0 ? 1 : 0);
             const uint32_t place = e < total ? fslot[e] : ~0u;
-            const uint32_t fin = place < total ? seg[place].w : ~0u;
-            if (fin < total) {
-              const float2 r = res[fin];
+            const uint32_t at_list = place < total ? fin[place] : ~0u;
+            if (at_list < total) {
+              const float2 r = res[at_list];
               const float4 gp = dpyr[lb + (iy + dy) * Sl + ix + dx];
               df[0] = fmaf(r.x, gp.x, df[0]);
               df[1] = fmaf(r.x, gp.y, df[1]);
@@ -1716,7 +1768,7 @@ extern "C" vrs_status vrs_splat_points_backward(const float* pos, const float* r
   hipLaunchKernelGGL(k_pt_blend_bwd, dim3(bb), dim3(256), 0, st, at<uint4>(ws, L.surv),
                      L.surv2 ? at<uint4>(ws, L.surv2) : nullptr, L.pix_total,
                      at<uint32_t>(ws, L.live), at<uint32_t>(ws, L.frag_count), max_frags,
-                     at<uint32_t>(ws, L.fslot), at<uint4>(ws, L.seg), pos, radius, opacity, np, kv,
+                     at<uint32_t>(ws, L.fslot), at<uint32_t>(ws, L.fdep), pos, radius, opacity, np, kv,
                      kc, a, at<uint32_t>(ws, L.grid), L.gx, L.gy,
                      reinterpret_cast<const float4*>(d_pyramid), res, d_feat, d_pos, d_radius,
                      d_opacity);

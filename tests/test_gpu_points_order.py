@@ -106,3 +106,34 @@ def test_hiding_depths_cull_as_coverage_and_depth(n):
         assert 0 < len(a[0]) < nf
     off, oids = oracle.point_lists(p["pos"], p["radius"], V, D, ci, L, dep, tf, cov_min, slack)
     assert np.array_equal(lists(dep, None)[1], oids)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 255, 256, 257])
+def test_dense_list_lengths(n):
+    """Lists of exactly n fragments (points one behind the other, few distinct
+    depths, a numbering), dense through a far longer list elsewhere in the crop."""
+    W, H, L, far = 64, 48, 3, 1500
+    rng = np.random.default_rng(n)
+    views = [synth.pinhole(W, H, 60.0)]
+    crops = [synth.crop_at(0, 32.0, 24.0, 16, W, H)]
+    z = np.concatenate([rng.choice([2.0, 2.5, 3.0], n), rng.uniform(2.0, 4.0, far)])
+    at = np.where(np.arange(n + far) < n, -4.3, 4.6) / 60.0   # pixels right of the axis at z = 1
+    p = synth.points(rng, n + far, "uniform", xy=(-0.1, 0.1))
+    p["pos"] = np.stack([at * z, at * z * 0.7, z]).astype(np.float32)
+    p["radius"] = (0.004 * z).astype(np.float32)
+    V, D = synth.views_array(views), synth.views_dims(views)
+    ci, _ = synth.crops_array(crops)
+    off, oids = oracle.point_lists(p["pos"], p["radius"], V, D, ci, L, None, None)
+    pyr_o = oracle.splat_points(p["pos"], p["radius"], p["feat"], V, D, ci, L, None, None)
+    assert n in np.diff(off) and len(oids) > 12 * len(pyr_o)
+    perm = rng.permutation(n + far)
+    stored = lambda a: dev(np.ascontiguousarray(a[..., perm]))
+    ws = api.SplatWorkspace(n + far, views, crops, L, len(oids))
+    pyr = api.splat_points(stored(p["pos"]), stored(p["radius"]),
+                           dev(np.ascontiguousarray(p["feat"][perm]).view(np.int16)), None, views,
+                           crops, L, None, None, ws, point_ids=dev(perm.astype(np.int32)))
+    assert int(ws.status.item()) == 0
+    keys, ids = ws.lists()
+    assert np.array_equal(np.bincount(keys, minlength=len(off) - 1), np.diff(off))
+    assert np.array_equal(perm[ids], oids)
+    assert np.abs(pyr.cpu().numpy() - pyr_o).max() <= 1e-4
