@@ -871,15 +871,17 @@ vrs_status render_impl(const float* mean, const float* cov, const float* opacity
     trace_end(tr, VRS_TRACE_GS_PREPROCESS, st);
     trace_begin(tr, VRS_TRACE_GS_DEPTH_SORT, st);
     bool d1 = false;
+    SortScan scan = {at<uint32_t>(ws, L.soffs), super_count, false};
     // the last pass also lays the super-tile counts out in depth order
     VRS_HIP_CHECK(radix_sort_u32(at<uint32_t>(ws, L.dkey0), at<uint32_t>(ws, L.dval0),
                                  at<uint32_t>(ws, L.dkey1), at<uint32_t>(ws, L.dval1), nullptr, vn,
                                  32, L.radix, at<void>(ws, L.sort_tmp), dev_status, st, &d1,
-                                 at<uint32_t>(ws, L.nsup), at<uint32_t>(ws, L.nsorted), true));
+                                 at<uint32_t>(ws, L.nsup), at<uint32_t>(ws, L.nsorted), true, &scan));
     const uint32_t* sorted_e = at<uint32_t>(ws, d1 ? L.dval1 : L.dval0);
-    VRS_HIP_CHECK(exclusive_scan_u32(at<uint32_t>(ws, L.nsorted), nullptr,
-                                     at<uint32_t>(ws, L.soffs), super_count, nullptr, vn,
-                                     at<void>(ws, L.scan_tmp), dev_status, st, true));
+    if (!scan.done)
+      VRS_HIP_CHECK(exclusive_scan_u32(at<uint32_t>(ws, L.nsorted), nullptr,
+                                       at<uint32_t>(ws, L.soffs), super_count, nullptr, vn,
+                                       at<void>(ws, L.scan_tmp), dev_status, st, true));
     trace_end(tr, VRS_TRACE_GS_DEPTH_SORT, st);
     trace_begin(tr, VRS_TRACE_GS_EMIT, st);
     hipLaunchKernelGGL(k_gs_emit_super, dim3(div_up(vn, kEmitBlock)), dim3(kEmitBlock), 0, st,

@@ -120,11 +120,18 @@ size_t sort_tmp_bytes(int64_t n_max, int key_bits, int radix_bits);
 // carried into the sorted order without a pass of its own).  iota: the
 // values are the items' input positions, not read from v0 (v0 is still the
 // buffer of the even passes' output).
+// scan (with gather): where the one-workgroup form runs, the gathered words'
+// exclusive scan goes to dst and their sum to total, and done is set; else the
+// caller scans.
+struct SortScan {
+  uint32_t *dst, *total;
+  bool done;
+};
 hipError_t radix_sort_u32(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
                           const uint32_t* n_dev, int64_t n_max, int key_bits, int radix_bits,
                           void* tmp, int32_t* status, hipStream_t st, bool* result_in_1,
                           const uint32_t* gather_src = nullptr, uint32_t* gather_dst = nullptr,
-                          bool iota = false);
+                          bool iota = false, SortScan* scan = nullptr);
 hipError_t radix_sort_u64(uint32_t* k0, uint64_t* v0, uint32_t* k1, uint64_t* v1,
                           const uint32_t* n_dev, int64_t n_max, int key_bits, int radix_bits,
                           void* tmp, int32_t* status, hipStream_t st, bool* result_in_1);
