@@ -340,7 +340,8 @@ __device__ inline uint32_t pt_targets_over(const PtGeom& g, int v, uint32_t cand
 // its atomics, so workgroups are kept large.
 constexpr int kSelRounds = 4;
 
-template <int kSelBlock>
+// ORD: a survivor also carries its screen bucket.
+template <int kSelBlock, bool ORD>
 __global__ __launch_bounds__(kSelBlock) void k_pt_select(
     const float* __restrict__ pos, const float* __restrict__ radius, int64_t np, KViews views,
     KCrops crops, PtArgs a, const float* __restrict__ depth, const float* __restrict__ tfinal,
@@ -376,13 +377,14 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
     s_oy[tid] = crop_y0(crops, tid);
     s_cv[tid] = crops.c[tid].view;
     s_cs[tid] = crops.c[tid].size;
-    int ob = 0;
-    if (a.ord_side)
+    if (ORD) {
+      int ob = 0;
       for (int k = 0; k < tid; ++k) {
         const int t = (crops.c[k].size + a.ord_side - 1) / a.ord_side;
         ob += t * t;
       }
-    s_ob[tid] = ob;
+      s_ob[tid] = ob;
+    }
   }
   __syncthreads();
   const int64_t part = blockIdx.x;
@@ -438,7 +440,7 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
         PtGeom g;   // recomputed for the few points the cull keeps
         pt_geom32(cv, px[j], py[j], pz[j], pr[j], a.levels, g);
         cnt = pt_targets_over(g, v, cand[j], a.levels, s_cv, s_cs, s_ox, s_oy);
-        if (a.ord_side && cnt) {   // its place on the first of its view's candidate crops
+        if (ORD && cnt) {   // its place on the first of its view's candidate crops
           uint32_t cm = cand[j];
           while (s_cv[__builtin_ctz(cm)] != v) cm &= cm - 1;
           const int k = __builtin_ctz(cm);
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
           bucket = (uint32_t)(s_ob[k] + by * t + bx);
         }
       }
-      s_cnt[(j * nv + v) * kSelBlock + tid] = cnt | bucket << 16;
+      s_cnt[(j * nv + v) * kSelBlock + tid] = ORD ? cnt | bucket << 16 : cnt;
       if (DEPTHS) s_zd[(j * nv + v) * kSelBlock + tid] = tz[j];
       const uint64_t m = __ballot(cnt != 0);
       if (m) {   // the slot's fragment total
@@ -514,7 +516,7 @@ __global__ __launch_bounds__(kSelBlock) void k_pt_select(
       const int slot = (v * kSelRounds + j) * NW + wave;
       const uint64_t m = s_mask[slot];
       if (!m) continue;   // uniform
-      const uint32_t cw = s_cnt[(j * nv + v) * kSelBlock + tid], cnt = cw & 0xffffu;
+      const uint32_t cw = s_cnt[(j * nv + v) * kSelBlock + tid], cnt = ORD ? cw & 0xffffu : cw;
       uint32_t fi = cnt;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -1409,7 +1411,8 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
     VRS_LAUNCH_CHECK();
   }
   // survivors with their fragment offsets (compaction order), then emission
-  auto select = wide ? k_pt_select<512> : k_pt_select<256>;
+  auto select = a.ord_side ? (wide ? k_pt_select<512, true> : k_pt_select<256, true>)
+                           : (wide ? k_pt_select<512, false> : k_pt_select<256, false>);
   hipLaunchKernelGGL(select, dim3(sel_parts), dim3(sel_block), sel_lds, st, pos, radius, np, kv, kc,
                      a, depth, t_final, hide, grid, L.gx, L.gy, at<uint4>(ws, L.surv),
                      at<uint64_t>(ws, L.ctr), at<uint32_t>(ws, L.chunk_first), max_frags,
