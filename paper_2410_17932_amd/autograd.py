@@ -21,6 +21,15 @@ def _check_generation(ws, gen, what):
                            f"call (use one workspace per forward kept for backward)")
 
 
+def _written(t, count):
+    """An empty gradient of t whose first `count` elements the library writes;
+    what t holds beyond them took no part, and its gradient is zero."""
+    g = torch.empty_like(t)
+    if t.numel() > count:
+        g.view(-1)[count:].zero_()
+    return g
+
+
 class BakeGaussians(torch.autograd.Function):
     @staticmethod
     def forward(ctx, logscale, quat, logit):
@@ -54,7 +63,9 @@ class RenderGaussians(torch.autograd.Function):
         mean, cov, op, sh, tf = ctx.saved_tensors
         deg, views, opts, ws, gen = ctx.meta
         _check_generation(ws, gen, "RenderGaussians")
-        g = [torch.empty_like(t) for t in (mean, cov, op, sh)]
+        n = mean.shape[1]
+        g = [_written(t, k * n) for t, k in
+             ((mean, 3), (cov, 6), (op, 1), (sh, 3 * (deg + 1) ** 2))]
         d_rgb = torch.zeros_like(tf).unsqueeze(1).expand(-1, 3, -1, -1).contiguous() \
             if d_rgb is None else d_rgb.contiguous()
         api.render_gaussians_backward(mean, cov, op, sh, deg, views, opts, ws, tf, d_rgb,
@@ -122,7 +133,8 @@ class CompositeFrame(torch.autograd.Function):
     def backward(ctx, d_out):
         P, F = ctx.saved_tensors
         crops, mode, ring, m, gamma = ctx.meta
-        dP, dF = torch.empty_like(P), torch.empty_like(F)
+        V, _, H, W = P.shape
+        dP, dF = _written(P, 3 * V * H * W), _written(F, api.fovea_elements(crops))
         api.composite_frame_backward(P, F, crops, d_out.contiguous(), dP, dF, mode, ring, m, gamma,
                                      accumulate=False)
         return dP, dF, None, None, None, None, None
