@@ -18,8 +18,8 @@ namespace vrs {
 
 // Per (view, Gaussian): with s the pixel's gradient with respect to the
 // exponent -d^T Q d / 2 (Q the conic), d = mean - pixel centre and u =
-// -log2(e) Q d, the sums of s, s ux, s uy, s ux^2, s ux uy, s uy^2, and the
-// gradients of r, g, b and z.  The position's gradient is a multiple of the
+// -log2(e) Q d, the gradient of the opacity and the sums of s ux, s uy, s
+// ux^2, s ux uy, s uy^2, and the gradients of r, g, b and z.  The position's gradient is a multiple of the
 // sum of s u and the screen covariance's of s u u^T, so k_gs_project_bwd only
 // scales them; sums of s d and s d d^T would still have to go through Q, which
 // loses digits where Q is ill conditioned (thin Gaussians).
@@ -181,16 +181,19 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
       const float diff = G - A;
       A = fmaf(al, diff, A);
       T = Tb;
-      // a clamped alpha carries nothing to the exponent or the opacity
-      const float s = oe < aclamp ? (Tb * diff) * al : 0.0f;
+      // to the opacity and, times it, to the exponent (not by a division of the
+      // latter: an opacity of 0 has a gradient where alpha_min is 0); a clamped
+      // alpha carries nothing to either
+      const float go = oe < aclamp && lane_in(ok) ? (Tb * diff) * e : 0.0f;
+      const float s = go * kb.y;
       const float hx = ka.z * dx;
       const float ux = fmaf(ka.w, dy, hx + hx), uy = fmaf(kb.x + kb.x, dy, ka.w * dx);
       const float sx = s * ux, sy = s * uy;
-      // values 0..9 = s, s ux, s uy, s ux^2, s ux uy, s uy^2, r, g, b, z.
+      // values 0..9 = opacity, s ux, s uy, s ux^2, s ux uy, s uy^2, r, g, b, z.
       // After the exchanges over 32 and 16 lanes, rows 0..3 of q0 hold the
       // sums of values 0, 2, 1, 3, of q1 those of 4, 6, 5, 7, of q2 8 and 9
       // in rows 0 and 2; lane 0 of each row takes q0, lane 1 q1, lane 2 q2.
-      const float p0 = pair_sum32(s, sx), p1 = pair_sum32(sy, sx * ux);
+      const float p0 = pair_sum32(go, sx), p1 = pair_sum32(sy, sx * ux);
       const float p2 = pair_sum32(sx * uy, sy * uy), p3 = pair_sum32(w * g0, w * g1);
       const float p4 = pair_sum32(w * g2, DEPTH ? w * gd : 0.0f);
       const float q0 = row_sum(pair_sum16(p0, p1)), q1 = row_sum(pair_sum16(p2, p3));
@@ -254,10 +257,9 @@ __device__ inline void sh_grad_dir(int deg, float x, float y, float z, const flo
 template <int DEG, bool ADD>
 __global__ __launch_bounds__(256) void k_gs_project_bwd(
     const float* __restrict__ mean, const float* __restrict__ cov,
-    const float* __restrict__ opacity, const float* __restrict__ sh, int64_t n, KViews views,
-    GsOpt o, const float4* __restrict__ rec, const float* __restrict__ g2d,
-    float* __restrict__ d_mean, float* __restrict__ d_cov, float* __restrict__ d_op,
-    float* __restrict__ d_sh) {
+    const float* __restrict__ sh, int64_t n, KViews views, GsOpt o,
+    const float4* __restrict__ rec, const float* __restrict__ g2d, float* __restrict__ d_mean,
+    float* __restrict__ d_cov, float* __restrict__ d_op, float* __restrict__ d_sh) {
   constexpr int K = (DEG + 1) * (DEG + 1);
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -285,7 +287,6 @@ __global__ __launch_bounds__(256) void k_gs_project_bwd(
   float S6[6];
 #pragma unroll
   for (int k = 0; k < 6; ++k) S6[k] = cov[k * n + i];
-  const float op = opacity[i];
   float coef[K][3];
 #pragma unroll
   for (int k = 0; k < K; ++k)
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(256) void k_gs_project_bwd(
     // with dQ = -Q dSigma Q, dL/dSigma = s (Q d) (Q d)^T / 2; u = -log2(e) Q d
     constexpr float kLn2 = 0.69314718055994531f;
     const float gpx = kLn2 * G[1], gpy = kLn2 * G[2], gz = G[9];
-    if (op != 0.0f) dopa += G[0] / op;
+    dopa += G[0];
     // dL/dSigma2D as a full symmetric matrix Gs
     constexpr float h = 0.5f * kLn2 * kLn2;
     const float Gs[2][2] = {{h * G[3], h * G[4]}, {h * G[4], h * G[5]}};
@@ -464,7 +465,7 @@ static vrs_status render_backward(
   }
   VRS_LAUNCH_CHECK();
   auto project = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(div_up(n, 256)), dim3(256), 0, st, mean, cov, opacity, sh, n,
+    hipLaunchKernelGGL(kernel, dim3(div_up(n, 256)), dim3(256), 0, st, mean, cov, sh, n,
                        kv, o, at<float4>(ws, L.rec), at<float>(ws, L.g2d), d_mean, d_cov,
                        d_opacity, d_sh);
   };
