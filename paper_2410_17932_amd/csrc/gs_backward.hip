@@ -56,8 +56,9 @@ __device__ inline float row_sum(float v) {
 // tiles hold long lists, by the walk's length: four pixels per lane share the
 // reduction and the atomics but were slower at every size measured (2330
 // against 2099 us below, 1955 against 817 at 256 x 256).  What keeps it there:
-// a pixel that does not take the entry has alpha 0, which leaves all of its
-// sums as they are (one select); the colour behind an entry is needed only
+// a pixel that does not take the entry has alpha 0, which leaves its sums as
+// they are but for values that 0 does not cancel (see the record loop); the
+// colour behind an entry is needed only
 // through its product with the pixel's gradient, one running sum instead of
 // four; and the ten sums are reduced together, halving the registers at each
 // exchange (28 instructions instead of 120), into ten lanes' one atomic
@@ -97,6 +98,7 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
     g1 = d_rgb[rp + plane];
     g2 = d_rgb[rp + 2 * plane];
     if (DEPTH) gd = d_depth[pix];
+    if (last == 0) g0 = g1 = g2 = gd = 0.0f;   // no entries: the pixel may hold anything
   }
   // the pixel's gradient times the colour behind the entry reached so far
   float A = g0 * o.bg[0] + g1 * o.bg[1] + g2 * o.bg[2];
@@ -105,6 +107,9 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
   for (int sh = 32; sh > 0; sh >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, sh, 64));
   const uint32_t stop = (uint32_t)__builtin_amdgcn_readfirstlane((int)most);
   if (stop == 0) return;
+  // pixels whose gradient 0 does not cancel
+  const bool wild = wave_mask(!(fabsf(g0) < INFINITY && fabsf(g1) < INFINITY &&
+                                fabsf(g2) < INFINITY && fabsf(gd) < INFINITY)) != 0;
   const float aclamp = o.aclamp, amin = o.amin, inv_amin = 1.0f / amin;
   const float xc = (float)px + 0.5f, yc = (float)py + 0.5f;
   const int64_t vn = (int64_t)v * n;
@@ -130,6 +135,10 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
     s_b[lane] = b;
     s_c[lane] = c;
     s_id[lane] = id;
+    // records whose products 0 may not cancel: a conic that is not finite or
+    // overflows times a distance, an opacity that is not finite
+    const float size = (fabsf(a.z) + fabsf(a.w)) + (fabsf(b.x) + fabsf(b.y));
+    const uint64_t odd = wild ? ~0ull : wave_mask(!(size < 1.0e28f));
     uint64_t m;
     {
       const uint32_t lo = __float_as_uint(b.z), hi = __float_as_uint(b.w);
@@ -170,7 +179,8 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
                           wave_mask((uint32_t)(py - ry0) <= (uint32_t)((int)(hi >> 16) - ry0)) &
                           wave_mask(al0 >= amin) & wave_mask(pos < last);
       if (ok == 0) continue;
-      const float al = lane_in(ok) ? al0 : 0.0f;
+      const bool in = lane_in(ok);
+      const float al = in ? al0 : 0.0f;
       const float d = 1.0f - al;
       const float r = __builtin_amdgcn_rcpf(d);
       const float t = T * r;
@@ -179,12 +189,12 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
       float G = fmaf(g2, kc.z, fmaf(g1, kc.y, g0 * kc.x));
       if (DEPTH) G = fmaf(gd, kc.w, G);
       const float diff = G - A;
-      A = fmaf(al, diff, A);
+      A = in ? fmaf(al, diff, A) : A;   // (the colour may not be finite)
       T = Tb;
       // to the opacity and, times it, to the exponent (not by a division of the
       // latter: an opacity of 0 has a gradient where alpha_min is 0); a clamped
       // alpha carries nothing to either
-      const float go = oe < aclamp && lane_in(ok) ? (Tb * diff) * e : 0.0f;
+      const float go = in && oe < aclamp ? (Tb * diff) * e : 0.0f;
       const float s = go * kb.y;
       const float hx = ka.z * dx;
       const float ux = fmaf(ka.w, dy, hx + hx), uy = fmaf(kb.x + kb.x, dy, ka.w * dx);
@@ -193,9 +203,14 @@ __global__ __launch_bounds__(64) void k_gs_blend_bwd(
       // After the exchanges over 32 and 16 lanes, rows 0..3 of q0 hold the
       // sums of values 0, 2, 1, 3, of q1 those of 4, 6, 5, 7, of q2 8 and 9
       // in rows 0 and 2; lane 0 of each row takes q0, lane 1 q1, lane 2 q2.
-      const float p0 = pair_sum32(go, sx), p1 = pair_sum32(sy, sx * ux);
-      const float p2 = pair_sum32(sx * uy, sy * uy), p3 = pair_sum32(w * g0, w * g1);
-      const float p4 = pair_sum32(w * g2, DEPTH ? w * gd : 0.0f);
+      float x[10] = {go,      sx,     sy,     sx * ux, sx * uy,
+                     sy * uy, w * g0, w * g1, w * g2,  DEPTH ? w * gd : 0.0f};
+      if ((odd >> k) & 1)   // uniform
+#pragma unroll
+        for (int i = 0; i < 10; ++i) x[i] = in ? x[i] : 0.0f;
+      const float p0 = pair_sum32(x[0], x[1]), p1 = pair_sum32(x[2], x[3]);
+      const float p2 = pair_sum32(x[4], x[5]), p3 = pair_sum32(x[6], x[7]);
+      const float p4 = pair_sum32(x[8], x[9]);
       const float q0 = row_sum(pair_sum16(p0, p1)), q1 = row_sum(pair_sum16(p2, p3));
       const float q2 = row_sum(pair_sum16(p4, 0.0f));
       const float val = l15 == 0 ? q0 : (l15 == 1 ? q1 : q2);
