@@ -1251,7 +1251,8 @@ __global__ __launch_bounds__(256) void k_dec_wgrad(DecLevel d, const float* __re
     __syncthreads();
     // upsampled channels, four per item: loads without branches (clamped
     // places, the weights of pixels outside the layer zero), so that several
-    // items' loads are in flight
+    // items' loads are in flight; 64-bit offsets (a 64-wide level of more than
+    // 5792 pixels a side passes 2^31 elements)
     constexpr int KG = 4 * (NT - 1);
     if (KG > 0) {
       const int Sn = S >> 1;
@@ -1266,10 +1267,10 @@ __global__ __launch_bounds__(256) void k_dec_wgrad(DecLevel d, const float* __re
         const int y0 = min(max(ya, 0), Sn - 1), y1 = min(max(ya + 1, 0), Sn - 1);
         const int x0 = min(max(xa, 0), Sn - 1), x1 = min(max(xa + 1, 0), Sn - 1);
         typedef T v4t __attribute__((ext_vector_type(4)));
-        const v4t a00 = *reinterpret_cast<const v4t*>(h + (y0 * Sn + x0) * (KG * 4) + n);
-        const v4t a01 = *reinterpret_cast<const v4t*>(h + (y0 * Sn + x1) * (KG * 4) + n);
-        const v4t a10 = *reinterpret_cast<const v4t*>(h + (y1 * Sn + x0) * (KG * 4) + n);
-        const v4t a11 = *reinterpret_cast<const v4t*>(h + (y1 * Sn + x1) * (KG * 4) + n);
+        const v4t a00 = *reinterpret_cast<const v4t*>(h + (long long)(y0 * Sn + x0) * (KG * 4) + n);
+        const v4t a01 = *reinterpret_cast<const v4t*>(h + (long long)(y0 * Sn + x1) * (KG * 4) + n);
+        const v4t a10 = *reinterpret_cast<const v4t*>(h + (long long)(y1 * Sn + x0) * (KG * 4) + n);
+        const v4t a11 = *reinterpret_cast<const v4t*>(h + (long long)(y1 * Sn + x1) * (KG * 4) + n);
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
