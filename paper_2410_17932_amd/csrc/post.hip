@@ -541,18 +541,27 @@ struct RegArgs {
   int view[VRS_MAX_CROPS], x0[VRS_MAX_CROPS], y0[VRS_MAX_CROPS], S[VRS_MAX_CROPS];
   long long fbase[VRS_MAX_CROPS], ebase[VRS_MAX_CROPS + 1];   // fovea offsets, element prefix
   const int4* place;
+  int wide;   // a crop of 2^32 elements or more
 };
 
 __device__ inline void reg_locate(const RegArgs& a, long long e, int& k, int& c, int& yy,
                                   int& xx, int& x0, int& y0) {
   k = 0;
   while (k + 1 < a.n && a.ebase[k + 1] <= e) ++k;
-  const uint32_t r = (uint32_t)(e - a.ebase[k]);   // a crop has under 2^32 elements
+  const long long r = e - a.ebase[k];
   const uint32_t S = (uint32_t)a.S[k];
-  c = (int)(r / (S * S));
-  const uint32_t q = r - (uint32_t)c * S * S;
-  yy = (int)(q / S);
-  xx = (int)(q - (uint32_t)yy * S);
+  if (a.wide) {
+    const long long plane = (long long)S * S;
+    c = (int)(r / plane);
+    const long long q = r - c * plane;
+    yy = (int)(q / S);
+    xx = (int)(q - (long long)yy * S);
+  } else {   // 32-bit divisions
+    c = (int)((uint32_t)r / (S * S));
+    const uint32_t q = (uint32_t)r - (uint32_t)c * S * S;
+    yy = (int)(q / S);
+    xx = (int)(q - (uint32_t)yy * S);
+  }
   if (a.place) {
     x0 = clamp_origin(a.place[k].x, a.W - a.S[k]);
     y0 = clamp_origin(a.place[k].y, a.H - a.S[k]);
@@ -657,6 +666,7 @@ bool reg_args(int nv, int W, int H, const vrs_crop* crops, int n, const vrs_crop
   a->W = W;
   a->H = H;
   a->place = reinterpret_cast<const int4*>(place);
+  a->wide = 0;
   long long fb = 0;
   a->ebase[0] = 0;
   for (int k = 0; k < n; ++k) {
@@ -668,6 +678,7 @@ bool reg_args(int nv, int W, int H, const vrs_crop* crops, int n, const vrs_crop
     a->y0[k] = c.y0;
     a->S[k] = c.size;
     a->fbase[k] = fb;
+    if ((3LL * c.size * c.size) >> 32) a->wide = 1;
     fb += 3LL * c.size * c.size;
     a->ebase[k + 1] = fb;
   }
