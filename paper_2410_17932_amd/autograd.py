@@ -92,11 +92,11 @@ class SplatPoints(torch.autograd.Function):
         pos, radius, op = ctx.saved_tensors
         feat_h, views, crops, levels, ws, has_op, gen = ctx.meta
         _check_generation(ws, gen, "SplatPoints")
-        # one fill for the three (few operations: small splats are bound by them)
-        n = pos.shape[1]
-        d_pos, d_r, d_feat = torch.zeros((8, n), device=pos.device, dtype=torch.float32).split((3, 1, 4))
-        d_r, d_feat = d_r.view(radius.shape), d_feat.view(n, 4)
-        d_op = torch.zeros_like(op) if has_op else None
+        d_pos, d_r = torch.empty_like(pos), torch.empty_like(radius)
+        d_feat = torch.empty((pos.shape[1], 4), device=pos.device, dtype=torch.float32)
+        d_op = torch.empty_like(op) if has_op else None
+        # one fill for all (few operations: small splats are bound by them)
+        torch._foreach_zero_([t for t in (d_pos, d_r, d_feat, d_op) if t is not None])
         api.splat_points_backward(pos, radius, feat_h, op if has_op else None, views, crops,
                                   levels, d_pyr.contiguous(), ws, d_feat=d_feat, d_pos=d_pos,
                                   d_radius=d_r, d_opacity=d_op)
