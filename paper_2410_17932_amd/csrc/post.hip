@@ -541,16 +541,19 @@ struct RegArgs {
   int view[VRS_MAX_CROPS], x0[VRS_MAX_CROPS], y0[VRS_MAX_CROPS], S[VRS_MAX_CROPS];
   long long fbase[VRS_MAX_CROPS], ebase[VRS_MAX_CROPS + 1];   // fovea offsets, element prefix
   const int4* place;
-  int wide;   // a crop of 2^32 elements or more
+  bool wide;   // a crop of 2^32 elements or more
 };
 
+// WIDE: 64-bit divisions (as a branch in the one kernel they cost a whole
+// objective of four 1024 x 1024 views 8 us).
+template <bool WIDE>
 __device__ inline void reg_locate(const RegArgs& a, long long e, int& k, int& c, int& yy,
                                   int& xx, int& x0, int& y0) {
   k = 0;
   while (k + 1 < a.n && a.ebase[k + 1] <= e) ++k;
   const long long r = e - a.ebase[k];
   const uint32_t S = (uint32_t)a.S[k];
-  if (a.wide) {
+  if (WIDE) {
     const long long plane = (long long)S * S;
     c = (int)(r / plane);
     const long long q = r - c * plane;
@@ -573,6 +576,7 @@ __device__ inline void reg_locate(const RegArgs& a, long long e, int& k, int& c,
 
 constexpr int kRegBlock = 256, kRegBlocks = 1024;
 
+template <bool WIDE>
 __global__ __launch_bounds__(kRegBlock) void k_reg_sums(const float* __restrict__ fovea,
                                                         const float* __restrict__ rgb, RegArgs a,
                                                         double* __restrict__ partial) {
@@ -583,7 +587,7 @@ __global__ __launch_bounds__(kRegBlock) void k_reg_sums(const float* __restrict_
   for (long long e = blockIdx.x * (long long)kRegBlock + threadIdx.x; e < total;
        e += (long long)gridDim.x * kRegBlock) {
     int k, c, yy, xx, x0, y0;
-    reg_locate(a, e, k, c, yy, xx, x0, y0);
+    reg_locate<WIDE>(a, e, k, c, yy, xx, x0, y0);
     const int S = a.S[k];
     sf += (double)fovea[a.fbase[k] + ((long long)c * S + yy) * S + xx];
     sp += (double)rgb[((int64_t)a.view[k] * 3 + c) * plane + (int64_t)(y0 + yy) * a.W + x0 + xx];
@@ -635,6 +639,7 @@ __global__ __launch_bounds__(256) void k_reg_finish(const double* __restrict__ p
 }
 
 // dF += g, dP -= g over the crops, g = d_r sign(diff) / count.
+template <bool WIDE>
 __global__ __launch_bounds__(kRegBlock) void k_reg_bwd(RegArgs a, const float* __restrict__ r,
                                                        const float* __restrict__ d_r,
                                                        float inv_cnt, float* __restrict__ d_fovea,
@@ -648,7 +653,7 @@ __global__ __launch_bounds__(kRegBlock) void k_reg_bwd(RegArgs a, const float* _
   for (long long e = blockIdx.x * (long long)kRegBlock + threadIdx.x; e < total;
        e += (long long)gridDim.x * kRegBlock) {
     int k, c, yy, xx, x0, y0;
-    reg_locate(a, e, k, c, yy, xx, x0, y0);
+    reg_locate<WIDE>(a, e, k, c, yy, xx, x0, y0);
     const int S = a.S[k];
     if (d_fovea) d_fovea[a.fbase[k] + ((long long)c * S + yy) * S + xx] += g;
     if (d_rgb)
@@ -666,7 +671,7 @@ bool reg_args(int nv, int W, int H, const vrs_crop* crops, int n, const vrs_crop
   a->W = W;
   a->H = H;
   a->place = reinterpret_cast<const int4*>(place);
-  a->wide = 0;
+  a->wide = false;
   long long fb = 0;
   a->ebase[0] = 0;
   for (int k = 0; k < n; ++k) {
@@ -678,7 +683,7 @@ bool reg_args(int nv, int W, int H, const vrs_crop* crops, int n, const vrs_crop
     a->y0[k] = c.y0;
     a->S[k] = c.size;
     a->fbase[k] = fb;
-    if ((3LL * c.size * c.size) >> 32) a->wide = 1;
+    if ((3LL * c.size * c.size) >> 32) a->wide = true;
     fb += 3LL * c.size * c.size;
     a->ebase[k + 1] = fb;
   }
@@ -884,7 +889,8 @@ extern "C" vrs_status vrs_regulariser(const float* fovea_rgb, const float* rgb, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int nb = std::max(1, std::min(kRegBlocks, div_up(a.ebase[n_crops], kRegBlock)));
   double* partial = static_cast<double*>(ws);
-  hipLaunchKernelGGL(k_reg_sums, dim3(nb), dim3(kRegBlock), 0, st, fovea_rgb, rgb, a, partial);
+  hipLaunchKernelGGL((a.wide ? k_reg_sums<true> : k_reg_sums<false>), dim3(nb), dim3(kRegBlock), 0,
+                     st, fovea_rgb, rgb, a, partial);
   VRS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_reg_finish, dim3(1), dim3(256), 0, st, partial, nb,
                      1.0 / (double)a.ebase[n_crops], r);
@@ -902,7 +908,8 @@ extern "C" vrs_status vrs_regulariser_backward(int n_views, int width, int heigh
   if (!d_fovea && !d_rgb) return VRS_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int nb = std::max(1, std::min(kRegBlocks, div_up(a.ebase[n_crops], kRegBlock)));
-  hipLaunchKernelGGL(k_reg_bwd, dim3(nb), dim3(kRegBlock), 0, st, a, r, d_r,
+  hipLaunchKernelGGL((a.wide ? k_reg_bwd<true> : k_reg_bwd<false>), dim3(nb), dim3(kRegBlock), 0,
+                     st, a, r, d_r,
                      (float)(1.0 / (double)a.ebase[n_crops]), d_fovea, d_rgb);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
