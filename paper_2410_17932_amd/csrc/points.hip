@@ -1504,9 +1504,9 @@ namespace vrs {
 // its alpha's is T (G - A), T the transmittance before it.  T is a prefix
 // product of 1 - alpha over the pixel's list and A a suffix composition of
 // A -> alpha G + (1 - alpha) A, so 16 lanes take a pixel and scan 16 fragments
-// at a time (row shifts); a fully opaque fragment (alpha >= 1) cuts both.  The
-// second kernel gathers a point's fragments and carries them into the point.
-// Both are latency-bound.  Fitting workload (2M points, four 512 crops): one
+// at a time (row shifts); a fully opaque fragment (alpha >= 1) cuts both, also
+// where what lies behind it is not finite.  The second kernel gathers a point's
+// fragments and carries them into the point.  Both are latency-bound.  Fitting workload (2M points, four 512 crops): one
 // thread walking each list took 864 us, the two take 165.
 constexpr int kPbLanes = 16;
 
@@ -1587,19 +1587,22 @@ __global__ __launch_bounds__(256) void k_pt_scan_bwd(
         }
         // suffix compositions of A -> b + a A over the row: row_shl 1, 2, 4, 8
         float a = om, b = al * G;
-        b = fmaf(a, row_shift<0x101>(b, 0.0f), b);
+        auto over = [&](float behind) { return a == 0.0f ? b : fmaf(a, behind, b); };
+        b = over(row_shift<0x101>(b, 0.0f));
         a *= row_shift<0x101>(a, 1.0f);
-        b = fmaf(a, row_shift<0x102>(b, 0.0f), b);
+        b = over(row_shift<0x102>(b, 0.0f));
         a *= row_shift<0x102>(a, 1.0f);
-        b = fmaf(a, row_shift<0x104>(b, 0.0f), b);
+        b = over(row_shift<0x104>(b, 0.0f));
         a *= row_shift<0x104>(a, 1.0f);
-        b = fmaf(a, row_shift<0x108>(b, 0.0f), b);
+        b = over(row_shift<0x108>(b, 0.0f));
         a *= row_shift<0x108>(a, 1.0f);
-        const float here = fmaf(a, Aend, b);   // A before the lane's fragment
+        const float here = over(Aend);   // A before the lane's fragment
         const float A = row_shift<0x101>(here, Aend);
         Aend = __shfl(here, 0, kPbLanes);
         const int j = c * kPbLanes + li;
-        if (j < n) res[start + j] = make_float2(al * Tb, Tb * (G - A));
+        // (behind an opaque fragment: nothing, whatever G and A are)
+        if (j < n)
+          res[start + j] = Tb == 0.0f ? make_float2(0.0f, 0.0f) : make_float2(al * Tb, Tb * (G - A));
       }
     }
   }
@@ -1679,7 +1682,9 @@ __global__ __launch_bounds__(256) void k_pt_blend_bwd(
             const uint32_t at_list = place < total ? fin[place] : ~0u;
             if (at_list < total) {
               const float2 r = res[at_list];
-              const float4 gp = dpyr[lb + (iy + dy) * Sl + ix + dx];
+              float4 gp = dpyr[lb + (iy + dy) * Sl + ix + dx];
+              // (a fragment that is not seen takes nothing, whatever the pixel's gradient)
+              if (r.x == 0.0f && r.y == 0.0f) gp = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
               df[0] = fmaf(r.x, gp.x, df[0]);
               df[1] = fmaf(r.x, gp.y, df[1]);
               df[2] = fmaf(r.x, gp.z, df[2]);
