@@ -427,10 +427,11 @@ __global__ __launch_bounds__(kZsBlock) void k_gs_tile_zsort(
 }
 
 // A lane's pending contributions in registers: 64-bit words (key bits << 32 |
-// list position), ascending, empty slots at the end.  Only positive finite
-// keys enter, so a word read as a double is positive and orders as it does as
-// an integer, and a comparator is one v_min_f64 and one v_max_f64; empty
-// slots hold +infinity (above every such word).
+// list position), ascending, empty slots at the end.  Only finite keys other
+// than zero enter, so a word read as a double is finite and orders by its key
+// (a float's high bits order as the float does in a double too, of either
+// sign; equal keys stand side by side), and a comparator is one v_min_f64 and
+// one v_max_f64; empty slots hold +infinity (above every such word).
 constexpr uint32_t kPxEmptyHi = 0x7ff00000u;
 __device__ inline double px_word(uint32_t hi, uint32_t lo) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
@@ -560,7 +561,7 @@ __global__ __launch_bounds__(PxCfg<TILE>::BLOCK) void k_gs_blend_px(
       uint32_t oldest = ~0u;
 #pragma unroll
       for (int q = 0; q < K; ++q)
-        oldest = px_hi(win[q]) < kPxEmptyHi ? min(oldest, px_lo(win[q])) : oldest;
+        oldest = px_hi(win[q]) != kPxEmptyHi ? min(oldest, px_lo(win[q])) : oldest;
       if (alive && nwin > 0 && oldest + RING < (b0 - begin) + BLOCK) {
         inexact = true;
         alive = false;
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(PxCfg<TILE>::BLOCK) void k_gs_blend_px(
           float num, den;
           pix_numden(s_q0[k], s_q1[k], make_float4(s_q2[k], 0, 0, 0), ur, vr, num, den);
           const float z = num / den;
-          if (z > 0.0f && z < INFINITY) {
+          if (z != 0.0f && fabsf(z) < INFINITY) {
             s_newz[wave][nnew][lane] = z;
             s_newk[wave][nnew][lane] = (uint8_t)k;
             ++nnew;
@@ -704,12 +705,15 @@ __global__ __launch_bounds__(PxCfg<TILE>::BLOCK) void k_gs_blend_px(
         nnew = 0;
       }
       // ---- blend the entries below the bound, in order
-      const uint32_t lim = bound & 0x80000000u ? min(bound & 0x7fffffffu, kPxEmptyHi) : 0u;
+      // (no bound, an image below the infinities', is a NaN: nothing goes; past
+      // the list, or next to nothing but NaN keys, everything but the empty
+      // slots, whose keys read as NaN)
+      const float lim = bound >= 0xff800000u ? INFINITY : ord2f(bound);
       bool released = false;
       static_while<0, K>([&](auto index) __attribute__((always_inline)) {
         constexpr int i = decltype(index)::value;
         const uint32_t zb = px_hi(win[i]);
-        const bool go = alive && zb < lim;
+        const bool go = alive && __uint_as_float(zb) < lim;
         if (!__ballot(go)) return false;
         released = true;
         if (go) {
