@@ -238,7 +238,9 @@ __global__ __launch_bounds__(256) void k_composite4_inplace(CompArgs a, float* i
 // In PAPER mode dc_k also flows into F_k through the Sobel edge term.  Two
 // kernels: the periphery's gradient per view pixel, and each crop's per crop
 // pixel (one thread owns each gradient element, so nothing is atomic).  A
-// pixel under several crops walks those, and recomputes their masks, in both.
+// pixel under several crops walks those, and recomputes their masks, in both;
+// where many crops lie over one another, with the edge term, k_composite_bwd
+// walks each view pixel's chain once instead (see kCompChain).
 // Four 1024 x 1024 views with a 512 crop each, with the edge term: 48 us and 28
 // us, 40 and 24 written instead of added (together 155 with per-pixel chains in
 // scratch memory and 27 atomics per edge pixel).
@@ -438,6 +440,134 @@ __global__ __launch_bounds__(256) void k_composite_bwd_f(CompArgs a, const float
   for (int ch = 0; ch < 3; ++ch) o[ch * fp] = (ADD ? o[ch * fp] : 0.0f) + (s_d[ch][cy][cx] + e);
 }
 
+// The adjoint per view pixel: the crop chain is replayed forward to recover the
+// intermediate images (each crop's mask computed once), then walked backwards.
+// In PAPER mode the edge term is scattered to the 3x3 neighbourhood with
+// atomics.
+__global__ __launch_bounds__(256) void k_composite_bwd(CompArgs a, const float* __restrict__ P,
+                                                       const float* __restrict__ F,
+                                                       const float* __restrict__ dout,
+                                                       float* __restrict__ dP,
+                                                       float* __restrict__ dF) {
+  const long long plane = (long long)a.W * a.H;
+  const long long total = plane * a.nv;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
+       i += (long long)gridDim.x * blockDim.x) {
+    const int v = (int)(i / plane);
+    const long long pi = i - v * plane;
+    const int y = (int)(pi / a.W), x = (int)(pi - (long long)y * a.W);
+    const long long base = (long long)v * 3 * plane + pi;
+    int ks[VRS_MAX_CROPS];
+    int nk = 0;
+    for (int k = 0; k < a.n_crops; ++k) {
+      if (a.view[k] != v) continue;
+      const int lx = x - cx0(a, k), ly = y - cy0(a, k);
+      if (lx < 0 || ly < 0 || lx >= a.S[k] || ly >= a.S[k]) continue;
+      ks[nk++] = k;
+    }
+    float g0 = dout[base], g1 = dout[base + plane], g2 = dout[base + 2 * plane];
+    if (nk > 0) {
+      // forward replay: o_j = image after crop j
+      float o[VRS_MAX_CROPS + 1][3];
+      float cs[VRS_MAX_CROPS], us[VRS_MAX_CROPS], gxs[VRS_MAX_CROPS], gys[VRS_MAX_CROPS];
+      o[0][0] = P[base]; o[0][1] = P[base + plane]; o[0][2] = P[base + 2 * plane];
+      for (int j = 0; j < nk; ++j) {
+        const int k = ks[j], S = a.S[k];
+        const int lx = x - cx0(a, k), ly = y - cy0(a, k);
+        const float* Fk = F + a.fbase[k];
+        cs[j] = blend_mask(a, k, Fk, lx, ly, us[j], gxs[j], gys[j], a.place);
+        const long long fp = (long long)S * S, fo = (long long)ly * S + lx;
+        for (int ch = 0; ch < 3; ++ch)
+          o[j + 1][ch] = (1.0f - cs[j]) * o[j][ch] + cs[j] * Fk[ch * fp + fo];
+      }
+      for (int j = nk - 1; j >= 0; --j) {
+        const int k = ks[j], S = a.S[k];
+        const int lx = x - cx0(a, k), ly = y - cy0(a, k);
+        const float* Fk = F + a.fbase[k];
+        const long long fp = (long long)S * S, fo = (long long)ly * S + lx;
+        const float c = cs[j];
+        const float f0 = Fk[fo], f1 = Fk[fp + fo], f2 = Fk[2 * fp + fo];
+        const float dc = g0 * (f0 - o[j][0]) + g1 * (f1 - o[j][1]) + g2 * (f2 - o[j][2]);
+        if (dF) {
+          float* dFk = dF + a.fbase[k];
+          if (a.mode == VRS_BLEND_PAPER) {
+            // neighbours scatter into this crop pixel too (edge term)
+            atomicAdd(&dFk[fo], c * g0);
+            atomicAdd(&dFk[fp + fo], c * g1);
+            atomicAdd(&dFk[2 * fp + fo], c * g2);
+          } else {
+            dFk[fo] += c * g0;
+            dFk[fp + fo] += c * g1;
+            dFk[2 * fp + fo] += c * g2;
+          }
+          const float u = us[j];
+          if (a.mode == VRS_BLEND_PAPER && u > 0.0f && u < 1.0f) {
+            // c = 1 - S2(u), u = fp + gamma |grad|/4
+            const float mag = sqrtf(gxs[j] * gxs[j] + gys[j] * gys[j]);
+            if (mag > 0.0f) {
+              const float dfe = -smootherstep_d(u) * a.gamma * dc;
+              const float s = dfe * 0.25f / mag / 3.0f;  // d|g|/dg = g/|g|; gray = mean/3
+              const float wx = s * gxs[j], wy = s * gys[j];
+              // Sobel taps: gx weights (+1,+2,+1 on x+1; -1,-2,-1 on x-1),
+              // gy weights (+1,+2,+1 on y+1; -1,-2,-1 on y-1)
+              for (int oy = -1; oy <= 1; ++oy)
+                for (int ox = -1; ox <= 1; ++ox) {
+                  const float kx = (float)ox * (oy == 0 ? 2.0f : 1.0f);
+                  const float ky = (float)oy * (ox == 0 ? 2.0f : 1.0f);
+                  const float wgt = kx * wx + ky * wy;
+                  if (wgt == 0.0f) continue;
+                  int sx = lx + ox, sy = ly + oy;
+                  sx = sx < 0 ? 0 : (sx > S - 1 ? S - 1 : sx);
+                  sy = sy < 0 ? 0 : (sy > S - 1 ? S - 1 : sy);
+                  const long long so = (long long)sy * S + sx;
+                  atomicAdd(&dFk[so], wgt);
+                  atomicAdd(&dFk[fp + so], wgt);
+                  atomicAdd(&dFk[2 * fp + so], wgt);
+                }
+            }
+          }
+        }
+        g0 *= 1.0f - c;
+        g1 *= 1.0f - c;
+        g2 *= 1.0f - c;
+      }
+    }
+    if (dP) {
+      dP[base] += g0;
+      dP[base + plane] += g1;
+      dP[base + 2 * plane] += g2;
+    }
+  }
+}
+
+// The mean number of other crops over a crop's pixel.  k_composite_bwd_f computes
+// all of their masks again for each crop, each a Sobel of 24 reads, so it grows
+// with the square of the crops over one another; k_composite_bwd pays atomics
+// and per-crop arrays in scratch, but each mask once.  One 1024 x 1024 view, 512
+// crops over one another, with the edge term, the two kernels against
+// k_composite_bwd: 2 crops 52 us and 58, 4 124 and 97, 8 366 and 175, 32 4357
+// and 639 (without it the two are faster throughout).  Origins read on the
+// device are not known here: such crops are taken to lie over one another.
+constexpr double kCompChain = 1.5;
+static double comp_overlap(const vrs_crop* crops, int n, bool placed) {
+  double area = 0.0, over = 0.0;
+  for (int k = 0; k < n; ++k) {
+    const vrs_crop& c = crops[k];
+    area += (double)c.size * c.size;
+    for (int q = 0; q < n; ++q) {
+      const vrs_crop& d = crops[q];
+      if (q == k || d.view != c.view) continue;
+      double w = std::min(c.size, d.size), h = w;
+      if (!placed) {
+        w = std::min(c.x0 + c.size, d.x0 + d.size) - std::max(c.x0, d.x0);
+        h = std::min(c.y0 + c.size, d.y0 + d.size) - std::max(c.y0, d.y0);
+      }
+      if (w > 0.0 && h > 0.0) over += w * h;
+    }
+  }
+  return area > 0.0 ? over / area : 0.0;
+}
+
 // L1: block partial sums of |pred - target| atomically added to loss[0]
 // (zeroed by the preceding fill), gradient scale*sign(pred - target)/n.
 // HBM-bound; two workgroups per compute unit, since every one ends with an
@@ -621,6 +751,22 @@ static vrs_status composite_backward(const float* rgb_periphery, int n_views,
     return VRS_EINVAL;
   if (!rgb_periphery || !d_out || (n_crops > 0 && !fovea_rgb)) return VRS_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const bool edge = mode == VRS_BLEND_PAPER && gamma != 0.0f;
+  if (d_fovea && edge && comp_overlap(crops, n_crops, place != nullptr) > kCompChain) {
+    const long long total = (long long)width * height * n_views;
+    if (!ADD) {
+      if (d_rgb_periphery)
+        VRS_HIP_CHECK(fill_u32(reinterpret_cast<uint32_t*>(d_rgb_periphery), 0u, 3 * total, st));
+      int64_t n = 0;
+      for (int k = 0; k < n_crops; ++k) n += (int64_t)3 * crops[k].size * crops[k].size;
+      VRS_HIP_CHECK(fill_u32(reinterpret_cast<uint32_t*>(d_fovea), 0u, n, st));
+    }
+    const int blocks = (int)std::min<long long>(16384, (total + 255) / 256);
+    hipLaunchKernelGGL(k_composite_bwd, dim3(blocks), dim3(256), 0, st, a, rgb_periphery,
+                       fovea_rgb, d_out, d_rgb_periphery, d_fovea);
+    VRS_LAUNCH_CHECK();
+    return VRS_OK;
+  }
   if (d_rgb_periphery) {
     const bool vec4 = width % 4 == 0 && ((reinterpret_cast<uintptr_t>(d_out) |
                                           reinterpret_cast<uintptr_t>(d_rgb_periphery)) & 15) == 0;
@@ -634,7 +780,6 @@ static vrs_status composite_backward(const float* rgb_periphery, int n_views,
     int most = 0;
     for (int k = 0; k < n_crops; ++k) most = std::max(most, (crops[k].size + 15) / 16);
     const dim3 grid((unsigned)(most * most), n_crops);
-    const bool edge = mode == VRS_BLEND_PAPER && gamma != 0.0f;
     hipLaunchKernelGGL((edge ? k_composite_bwd_f<true, ADD> : k_composite_bwd_f<false, ADD>), grid,
                        dim3(256), 0, st, a, rgb_periphery, fovea_rgb, d_out, d_fovea);
     VRS_LAUNCH_CHECK();
