@@ -38,6 +38,7 @@ namespace vrs {
 struct SplatWs {
   size_t surv, ctr, live, frag_count,   // survivors: (entry, depth key, fragment offset,
                                         // fragments | bucket << 16)
+      left,
       chunk_first,                 // per emission chunk: the survivor holding its first fragment
       fkey0, fval0, fdep, fslot,   // fragments in emission order, place in segment
       seg,                         // (point index, depth key, weight, pixel) per segment place
@@ -57,6 +58,9 @@ constexpr int kEmitFrags = 1024;
 // Fragments per layer pixel above which lists are dense: survivors are put
 // in screen order before the emission and k_pt_resolve ranks and blends.
 constexpr int64_t kRsDense = 12;
+// Per-pixel mark (in place of its fragment count) of a list that k_pt_resolve
+// leaves to k_pt_rank and k_pt_blend.
+constexpr uint32_t kRsLeft = 0xffffffffu;
 // Screen buckets of dense survivors, and those counted per workgroup.
 constexpr int kOrdBuckets = 2048, kOrdBlock = 512;
 
@@ -87,9 +91,10 @@ static bool splat_layout(int64_t np, int nv, int W, int H, const vrs_crop* crops
   const int64_t pt = std::max<int64_t>(L->pix_total, 1);
   Carver c;
   L->surv = c.take(vn * 16);
-  L->ctr = c.take(8);   // survivors in the low word, fragments in the high word
+  L->ctr = c.take(12);   // survivors in the low word, fragments in the high word,
   L->live = L->ctr;
   L->frag_count = L->ctr + 4;
+  L->left = L->ctr + 8;   // then the pixels that k_pt_resolve leaves to rank and blend
   L->chunk_first = c.take((mf / kEmitFrags + 2) * 4);
   L->fkey0 = c.take(mf * 4);
   L->fval0 = c.take(mf * 8);
@@ -270,7 +275,10 @@ __global__ void k_pt_prep(uint32_t* __restrict__ pcnt, int64_t pix_total,
   for (int64_t q = gt; q < pix_total / 4; q += stride) p4[q] = make_uint4(0u, 0u, 0u, 0u);
   for (int64_t i = (pix_total & ~int64_t(3)) + gt; i < pix_total; i += stride) pcnt[i] = 0u;
   for (int64_t i = gt; i < scan_words; i += stride) scan_tmp[i] = 0u;
-  if (gt == 0) *ctr = 0ull;
+  if (gt == 0) {
+    ctr[0] = 0ull;
+    *reinterpret_cast<uint32_t*>(ctr + 1) = 0u;
+  }
   for (int64_t i = gt; i < cells; i += stride)
     pt_cropgrid_cell(crops, levels, gx, gy, i, s_ox, s_oy, grid);
   if (hide)
@@ -890,16 +898,21 @@ __global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
                                                  const uint32_t* __restrict__ poff,
                                                  const uint32_t* __restrict__ total_p,
                                                  int64_t max_frags, int64_t pix_total,
+                                                 const uint32_t* __restrict__ left_p,
+                                                 const uint32_t* __restrict__ pcnt,
                                                  const uint32_t* __restrict__ ids,
                                                  uint32_t* __restrict__ okey,
                                                  uint64_t* __restrict__ oval) {
+  const uint32_t left = *left_p;   // (read with the count: most workgroups only leave)
   const int64_t total = *total_p;
-  if (total > max_frags || total > kRsDense * pix_total) return;
+  const bool dense = total > kRsDense * pix_total;   // only what k_pt_resolve left
+  if (total > max_frags || (dense && left == 0)) return;
   const uint64_t* key = reinterpret_cast<const uint64_t*>(seg);   // depth key << 32 | index
   for (int64_t sr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; sr < total;
        sr += (int64_t)gridDim.x * blockDim.x) {
     const uint4 rec = seg[total - 1 - sr];
     if (rec.w >= pix_total) continue;   // every place is filled; never taken
+    if (dense && pcnt[rec.w] != kRsLeft) continue;
     const uint64_t own = ((uint64_t)rec.y << 32) | rec.x;
     const uint32_t start = poff[rec.w], n = poff[rec.w + 1] - start;
     uint32_t rank = 0;
@@ -948,15 +961,21 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
                                                   const uint32_t* __restrict__ poff,
                                                   const uint32_t* __restrict__ total_p,
                                                   int64_t max_frags,
+                                                  const uint32_t* __restrict__ left_p,
+                                                  const uint32_t* __restrict__ pcnt,
                                                   const uint16_t* __restrict__ feat,
                                                   const float* __restrict__ opacity, int64_t np,
                                                   int64_t pix_total, float4* __restrict__ pyr) {
-  // dense lists are k_pt_resolve's (launched wherever the capacity allows them)
-  if (min((int64_t)*total_p, max_frags) > kRsDense * pix_total) return;
+  // dense lists are k_pt_resolve's (launched wherever the capacity allows
+  // them) but for those it left
+  const uint32_t left = *left_p;
+  const bool dense = min((int64_t)*total_p, max_frags) > kRsDense * pix_total;
+  if (dense && left == 0) return;
   const bool over = (int64_t)*total_p > max_frags;
   for (int64_t kr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; kr < pix_total;
        kr += (int64_t)gridDim.x * blockDim.x) {
     const int64_t k = pix_total - 1 - kr;
+    if (dense && pcnt[k] != kRsLeft) continue;
     float T = 1.0f;
     float4 F = make_float4(0, 0, 0, 0);
     const uint32_t start = over ? 0u : poff[k], n = over ? 0u : poff[k + 1] - start;
@@ -1003,8 +1022,9 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
 // 2000) took 7.4 + 0.95 ms.  Here a wave takes each pixel, and the workgroup
 // together those with more than 256 fragments: they are ranked through 1024
 // depth buckets (count, scan, place, then a comparison within the bucket
-// alone; up to 64 a lane's one fragment against all, up to 256 four), then each
-// wave composites its pixel: the lanes gather 64 fragments'
+// alone; up to 64 a lane's one fragment against all, up to 256 four; a bucket
+// beyond the LDS leaves its pixel to k_pt_rank and k_pt_blend), then each wave
+// composites its pixel: the lanes gather 64 fragments'
 // weights and features at a time, and the sums run over them one by one in
 // list order, a channel per lane (the same operations in the same order as
 // k_pt_blend, so the results are the same to the bit): 0.96 ms, of which the
@@ -1083,16 +1103,21 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
     const uint4* __restrict__ seg, uint32_t* __restrict__ fin,
     const uint32_t* __restrict__ poff,
     const uint32_t* __restrict__ total_p, int64_t max_frags, int64_t pix_total,
+    uint32_t* __restrict__ left, uint32_t* __restrict__ pcnt,
     const uint32_t* __restrict__ ids, const uint16_t* __restrict__ feat,
     const float* __restrict__ opacity, int64_t np, uint32_t* __restrict__ okey,
     uint64_t* oval, float4* __restrict__ pyr) {
   __shared__ __align__(16) uint64_t s_key[kRsCap];      // (depth key << 32 | segment place), by bucket
   __shared__ uint32_t s_cur[kRsBuckets];   // bucket starts, advanced to their ends by the placing
-  __shared__ uint32_t s_n[kRsPix], s_w[4], s_v[4];
+  __shared__ uint32_t s_n[kRsPix], s_left[kRsPix], s_w[4], s_v[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t total = *total_p;
   if (total <= kRsDense * pix_total) return;
   const bool over = total > max_frags;
+  // most fragments that a workgroup compares with one another: what the LDS
+  // holds (a bucket of 4096 takes it about 0.5 ms), less where there are fewer
+  // pixels than workgroups and that would be the launch's time
+  const uint32_t bucket_cap = pix_total < 1024 ? 512 : kRsCap;
   // pixels in reverse: the coarse layers' long lists start early
   for (int64_t k0 = pix_total - kRsPix * ((int64_t)blockIdx.x + 1); k0 > -kRsPix;
        k0 -= kRsPix * (int64_t)gridDim.x) {
@@ -1102,7 +1127,10 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
       start_w = poff[kw];
       nw = poff[kw + 1] - start_w;
     }
-    if (lane == 0) s_n[wave] = nw;
+    if (lane == 0) {
+      s_n[wave] = nw;
+      s_left[wave] = 0u;
+    }
     // (uniform over the wave)
     if (nw <= 64) rs_rank_wave<1>(seg, start_w, (int)nw, (uint32_t)kw, fin, ids, okey, oval, lane);
     else if (nw <= 128) rs_rank_wave<2>(seg, start_w, (int)nw, (uint32_t)kw, fin, ids, okey, oval, lane);
@@ -1141,21 +1169,34 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
       };
       for (uint32_t i = tid; i < n; i += 256) atomicAdd(&s_cur[bucket(sg[i].y)], 1u);
       __syncthreads();
+      bool wide;
       // exclusive scan of the counts, four buckets per thread
       {
-        uint32_t c[4], sum = 0;
+        uint32_t c[4], sum = 0, most = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           c[q] = s_cur[tid * 4 + q];
           sum += c[q];
+          most = max(most, c[q]);
         }
+        if (n > bucket_cap && __syncthreads_or(most > bucket_cap)) {
+          // thousands of nearly equal depths: one workgroup would compare each
+          // with all, so the pixel is left to the kernels that share it out
+          if (tid == 0) {
+            pcnt[k] = kRsLeft;
+            s_left[w] = 1u;
+            atomicAdd(left, 1u);
+          }
+          continue;
+        }
+        // large buckets: equal depths may be many (see below)
+        wide = __syncthreads_or(most >= (n <= kRsCap ? 64u : 1024u)) != 0;   // s_w is read above
         uint32_t inc = sum;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
           const uint32_t t = (uint32_t)__shfl_up((int)inc, o, 64);
           if (lane >= o) inc += t;
         }
-        __syncthreads();   // s_w is read above
         if (lane == 63) s_w[wave] = inc;
         __syncthreads();
         uint32_t base = inc - sum;
@@ -1168,7 +1209,11 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
       }
       __syncthreads();
       // buckets [b0, b1) whose fragments fit the LDS at a time: all of them
-      // for segments up to kRsCap
+      // for segments up to kRsCap.  A fragment is compared with its bucket's;
+      // where buckets are small its equals (rare) are looked up one by one, where
+      // they are large every word holds the tie's order and every group walks
+      // the segment again (4M points of one depth, one 512 crop: 7.7 ms, 7.8 with
+      // a numbering; 24.5 and 142 by lookups)
       uint32_t done = 0;   // fragments of the buckets before b0
       for (int b0 = 0; b0 < kRsBuckets && done < n;) {
         int b1 = kRsBuckets;
@@ -1185,7 +1230,38 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
         }
         const uint32_t cnt = (b1 < kRsBuckets ? s_cur[b1] : n) - done;
         __syncthreads();   // b1's start is read before any placing moves a cursor
-        if (cnt <= kRsCap) {
+        auto put = [&](const uint4& rec, uint32_t i, uint32_t rank) {
+          okey[start + rank] = (uint32_t)k;
+          oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
+          fin[start + i] = start + rank;
+        };
+        auto own_id = [&](uint32_t x) { return ids ? ids[x] : x; };
+        // the words of a key's bucket
+        auto span = [&](int b, uint32_t& first, uint32_t& last) {
+          first = b == b0 ? 0u : s_cur[b - 1] - done;
+          last = s_cur[b] - done;
+        };
+        if (wide) {
+          // words of the points' own order, and the fragments by place
+          for (uint32_t i = tid; i < n; i += 256) {
+            const uint4 rec = sg[i];
+            const int b = bucket(rec.y);
+            if (b >= b0 && b < b1)
+              s_key[atomicAdd(&s_cur[b], 1u) - done] = ((uint64_t)rec.y << 32) | own_id(rec.x);
+          }
+          __syncthreads();
+          for (uint32_t i = tid; i < n; i += 256) {
+            const uint4 rec = sg[i];
+            const int b = bucket(rec.y);
+            if (b < b0 || b >= b1) continue;
+            const uint64_t own = ((uint64_t)rec.y << 32) | own_id(rec.x);
+            uint32_t first, last;
+            span(b, first, last);
+            uint32_t rank = first;
+            for (uint32_t q = first; q < last; ++q) rank += s_key[q] < own ? 1u : 0u;
+            put(rec, i, done + rank);
+          }
+        } else {
           for (uint32_t i = tid; i < n; i += 256) {
             const uint32_t d = sg[i].y;
             const int b = bucket(d);
@@ -1196,37 +1272,18 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
           for (uint32_t p = tid; p < cnt; p += 256) {
             const uint64_t e = s_key[p];
             const uint32_t d = (uint32_t)(e >> 32);
-            const int b = bucket(d);
-            const uint32_t first = b == b0 ? 0u : s_cur[b - 1] - done, last = s_cur[b] - done;
             const uint4 rec = sg[(uint32_t)e];
-            uint32_t rank = done + first;
+            uint32_t first, last;
+            span(bucket(d), first, last);
+            uint32_t rank = first;
             for (uint32_t q = first; q < last; ++q) {
               const uint64_t f = s_key[q];
               const uint32_t df = (uint32_t)(f >> 32);
               rank += df < d ? 1u : 0u;
-              if (df == d && q != p) {   // equal depths: the points' own order
-                const uint32_t x = sg[(uint32_t)f].x;
-                rank += (ids ? ids[x] : x) < (ids ? ids[rec.x] : rec.x) ? 1u : 0u;
-              }
+              if (df == d && q != p)   // equal depths: the points' own order
+                rank += own_id(sg[(uint32_t)f].x) < own_id(rec.x) ? 1u : 0u;
             }
-            okey[start + rank] = (uint32_t)k;
-            oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
-            fin[start + (uint32_t)e] = start + rank;
-          }
-        } else {
-          // one bucket beyond the LDS (thousands of nearly equal depths)
-          for (uint32_t i = tid; i < n; i += 256) {
-            const uint4 rec = sg[i];
-            if (bucket(rec.y) != b0) continue;
-            uint32_t rank = done;
-            for (uint32_t j = 0; j < n; ++j) {
-              const uint4 o = sg[j];
-              if (o.y > rec.y || bucket(o.y) != b0 || j == i) continue;
-              rank += o.y < rec.y || (ids ? ids[o.x] : o.x) < (ids ? ids[rec.x] : rec.x) ? 1u : 0u;
-            }
-            okey[start + rank] = (uint32_t)k;
-            oval[start + rank] = ((uint64_t)rec.z << 32) | rec.x;
-            fin[start + i] = start + rank;
+            put(rec, (uint32_t)e, done + rank);
           }
         }
         __syncthreads();
@@ -1235,6 +1292,8 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
       }
     }
     __syncthreads();   // the sorted lists are written, s_key is free
+    const bool skip = s_left[wave] != 0u;
+    if (skip) nw = 0;
     // weights, 1 - weights and four features of 64 fragments, per wave
     float* st = reinterpret_cast<float*>(s_key) + wave * (6 * 64);
     const uint64_t* list = oval + start_w;
@@ -1279,7 +1338,7 @@ __global__ __launch_bounds__(256) void k_pt_resolve(
       }
       __builtin_amdgcn_wave_barrier();   // read before the next batch's stores
     }
-    if (lane < 4 && kw >= 0) reinterpret_cast<float*>(pyr + kw)[lane] = F;
+    if (lane < 4 && kw >= 0 && !skip) reinterpret_cast<float*>(pyr + kw)[lane] = F;
     __syncthreads();   // the shared words are reused by the next pixels
   }
 }
@@ -1462,20 +1521,21 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
     const unsigned rb = (unsigned)std::min<int64_t>(4 * device_cus(), div_up(L.pix_total, kRsPix));
     hipLaunchKernelGGL(k_pt_resolve, dim3(rb), dim3(256), 0, st, at<uint4>(ws, L.seg),
                        at<uint32_t>(ws, L.fdep), poff,
-                       frag_count, max_frags, L.pix_total, point_ids, feat, opacity, np,
-                       at<uint32_t>(ws, L.fkey1), at<uint64_t>(ws, L.fval1),
+                       frag_count, max_frags, L.pix_total, at<uint32_t>(ws, L.left), pcnt,
+                       point_ids, feat, opacity, np, at<uint32_t>(ws, L.fkey1), at<uint64_t>(ws, L.fval1),
                        reinterpret_cast<float4*>(pyramid));
     VRS_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(k_pt_rank, dim3(fb), dim3(256), 0, st, at<uint4>(ws, L.seg),
                      at<uint32_t>(ws, L.fdep), poff,
-                     frag_count, max_frags, L.pix_total, point_ids, at<uint32_t>(ws, L.fkey1),
+                     frag_count, max_frags, L.pix_total, at<uint32_t>(ws, L.left), pcnt, point_ids,
+                     at<uint32_t>(ws, L.fkey1),
                      at<uint64_t>(ws, L.fval1));
   VRS_LAUNCH_CHECK();
   const unsigned pb = (unsigned)std::min<int64_t>(8192, std::max<int64_t>(1, div_up(L.pix_total, 256)));
   hipLaunchKernelGGL(k_pt_blend, dim3(pb), dim3(256), 0, st, at<uint64_t>(ws, L.fval1), poff,
-                     frag_count, max_frags, feat, opacity, np, L.pix_total,
-                     reinterpret_cast<float4*>(pyramid));
+                     frag_count, max_frags, at<uint32_t>(ws, L.left), pcnt, feat, opacity, np,
+                     L.pix_total, reinterpret_cast<float4*>(pyramid));
   VRS_LAUNCH_CHECK();
   trace_end(tr, VRS_TRACE_SPLAT, st);
   return VRS_OK;
