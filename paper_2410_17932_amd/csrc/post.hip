@@ -289,6 +289,7 @@ struct SsArgs {
   int planes, W, H;
   int tiles_x, tiles_y;
   int rows, groups;   // output rows per workgroup; input row groups of kSsTaps
+  bool tile;          // 32 x 32 tiles (small images) instead of strips
   float w[kSsTaps];   // the window's 1-D taps, rounded from double precision
 };
 
@@ -367,7 +368,7 @@ __device__ inline void ss_blur(const SsArgs& a, int X0, int Y0, float (*s_v)[NM]
   }
 }
 
-// SSIM from five blurred moments of x, y and e = x - y (mu_x, mu_y, E[xy],
+// One pixel's SSIM from five blurred moments of x, y and e = x - y (mu_x, mu_y, E[xy],
 // D = mu_e, E[e^2]; s_xy is taken from E[xy] itself, since a difference of
 // larger moments would lose it where either image is dark).  With a1 = 2 mu_x
 // mu_y + C1, a2 = 2 s_xy + C2, b1 = a1 + D^2 (= mu_x^2 + mu_y^2 + C1), b2 = a2
@@ -379,6 +380,53 @@ __device__ inline void ss_blur(const SsArgs& a, int X0, int Y0, float (*s_v)[NM]
 // C' = 2 a1 v_e / (b1 b2^2)) to maps [3][planes][H][W].  SUM: the block's sum
 // of 1 - SSIM to partial[block].  Twelve 1024 x 1024 planes: 89 us,
 // 116 the maps, 119 both in one pass (141 and 165 with 32 x 32 tiles).
+// (No contraction beyond the fused operations written, so that every variant
+// gives the same bits.)
+struct SsPoint {
+  float my, mxy, D, ve, a1, a2, b1, b2, inv;
+  __device__ SsPoint(float mx, float my_, float exy, float D_, float ee) : my(my_), D(D_) {
+#pragma clang fp contract(off)
+    const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
+    mxy = mx + my;
+    const float sxy = fmaf(-mx, my, exy);
+    ve = fmaf(-D, D, ee);
+    a1 = fmaf(2.0f * mx, my, C1);
+    a2 = fmaf(2.0f, sxy, C2);
+    b1 = fmaf(D, D, a1);
+    b2 = a2 + ve;
+    inv = 1.0f / (b1 * b2);
+  }
+  __device__ float loss() const {
+#pragma clang fp contract(off)
+    return fmaf(b1, ve, D * D * a2) * inv;
+  }
+  __device__ void maps(float* __restrict__ m, int64_t at, int64_t all) const {
+#pragma clang fp contract(off)
+    const float C1 = 0.01f * 0.01f;
+    const float s = a1 * a2 * inv;
+    const float u = -2.0f * a2 * D * fmaf(my, mxy, C1) * inv / b1;
+    const float v = 2.0f * a1 * fmaf(D, a2, -(my * ve)) * inv;
+    m[at] = u + v / b2;
+    m[all + at] = -s / b2;
+    m[2 * all + at] = 2.0f * a1 * ve * inv / b2;
+  }
+};
+
+// The workgroup's sum to partial[its place].
+template <int BLOCK>
+__device__ inline void ss_block_sum(const SsArgs& a, float sum, float* s_red,
+                                    float* __restrict__ partial) {
+#pragma unroll
+  for (int sh = 32; sh > 0; sh >>= 1) sum += __shfl_xor(sum, sh, 64);
+  if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.0f;
+    for (int w = 0; w < BLOCK / 64; ++w) t += s_red[w];
+    partial[((int64_t)blockIdx.z * a.tiles_y + blockIdx.y) * a.tiles_x + blockIdx.x] = t;
+  }
+}
+
 template <bool MAPS, bool SUM>
 __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
                                                    const float* __restrict__ y, SsArgs a,
@@ -389,7 +437,6 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
   const int pl = blockIdx.z;
   const int64_t plane = (int64_t)a.W * a.H;
   const float *xp = x + pl * plane, *yp = y + pl * plane;
-  const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
   float sum = 0.0f;
   ss_blur<5, 2>(
       a, blockIdx.x * kSsOut, blockIdx.y * a.rows, s_v,
@@ -410,37 +457,13 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim(const float* __restrict__ x,
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           if (px + c >= a.W) continue;
-          const float mx = o[0][c], my = o[1][c], D = o[3][c];
-          const float sxy = o[2][c] - mx * my;
-          const float ve = o[4][c] - D * D;
-          const float a1 = 2.0f * mx * my + C1, a2 = 2.0f * sxy + C2;
-          const float b1 = a1 + D * D, b2 = a2 + ve;
-          const float inv = 1.0f / (b1 * b2);
-          if (MAPS) {
-            const float s = a1 * a2 * inv;
-            const float A = -2.0f * a2 * D * (my * (mx + my) + C1) * inv / b1 +
-                            2.0f * a1 * (D * a2 - my * ve) * inv / b2;
-            const int64_t o2 = pl * plane + (int64_t)py * a.W + px + c;
-            const int64_t all = (int64_t)a.planes * plane;
-            maps[o2] = A;
-            maps[all + o2] = -s / b2;
-            maps[2 * all + o2] = 2.0f * a1 * ve * inv / b2;
-          }
-          if (SUM) sum += (b1 * ve + D * D * a2) * inv;
+          const SsPoint v(o[0][c], o[1][c], o[2][c], o[3][c], o[4][c]);
+          if (MAPS)
+            v.maps(maps, pl * plane + (int64_t)py * a.W + px + c, (int64_t)a.planes * plane);
+          if (SUM) sum += v.loss();
         }
       });
-  if (SUM) {
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) sum += __shfl_xor(sum, sh, 64);
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float t = 0.0f;
-      for (int w = 0; w < kSsBlock / 64; ++w) t += s_red[w];
-      const int64_t b = ((int64_t)pl * a.tiles_y + blockIdx.y) * a.tiles_x + blockIdx.x;
-      partial[b] = t;
-    }
-  }
+  if (SUM) ss_block_sum<kSsBlock>(a, sum, s_red, partial);
 }
 
 // d_x += scale (blur(A) + 2 (x - y) blur(B) + y blur(C')), scale =
@@ -482,6 +505,115 @@ __global__ __launch_bounds__(kSsBlock) void k_ssim_bwd(const float* __restrict__
       });
 }
 
+// The same over 32 x 32 tiles, both passes through LDS: every thread of a
+// small image's workgroup has work, and one is done in fewer steps (see
+// ss_tiles for where).
+constexpr int kStTile = 32, kStIn = kStTile + 2 * kSsHalo, kStBlock = 256;
+
+// NM planes' halo tiles (zero outside the image) to LDS.
+template <int NM>
+__device__ inline void st_stage(const float* const src[NM], const SsArgs& a, int X0, int Y0,
+                                float (*in)[kStIn][kStIn + 1]) {
+  for (int i = threadIdx.x; i < kStIn * kStIn; i += kStBlock) {
+    const int r = i / kStIn, c = i - r * kStIn;
+    const int y = Y0 + r - kSsHalo, x = X0 + c - kSsHalo;
+    const bool ok = x >= 0 && x < a.W && y >= 0 && y < a.H;
+#pragma unroll
+    for (int m = 0; m < NM; ++m) in[m][r][c] = ok ? src[m][(int64_t)y * a.W + x] : 0.0f;
+  }
+  __syncthreads();
+}
+// Vertical pass: thread (tx, ty) the rows ty + 8 q of column tx.
+template <int NM>
+__device__ inline void st_column(const SsArgs& a, float (*h)[kStIn][kStTile + 1], int tx, int r,
+                                 float o[NM]) {
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    float s = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kSsTaps; ++j) s = fmaf(a.w[j], h[m][r + j][tx], s);
+    o[m] = s;
+  }
+}
+
+template <bool MAPS, bool SUM>
+__global__ __launch_bounds__(kStBlock) void k_ssim_tile(const float* __restrict__ x,
+                                                        const float* __restrict__ y, SsArgs a,
+                                                        float* __restrict__ maps,
+                                                        float* __restrict__ partial) {
+  __shared__ float s_in[2][kStIn][kStIn + 1];
+  __shared__ float s_h[5][kStIn][kStTile + 1];
+  __shared__ float s_red[kStBlock / 64];
+  const int pl = blockIdx.z, X0 = blockIdx.x * kStTile, Y0 = blockIdx.y * kStTile;
+  const int64_t plane = (int64_t)a.W * a.H;
+  const float* src[2] = {x + pl * plane, y + pl * plane};
+  st_stage<2>(src, a, X0, Y0, s_in);
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int r = ty; r < kStIn; r += 8) {
+    float h[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < kSsTaps; ++j) {
+      const float w = a.w[j], u = s_in[0][r][tx + j], v = s_in[1][r][tx + j], e = u - v;
+      h[0] = fmaf(w, u, h[0]);
+      h[1] = fmaf(w, v, h[1]);
+      h[2] = fmaf(w, u * v, h[2]);
+      h[3] = fmaf(w, e, h[3]);
+      h[4] = fmaf(w, e * e, h[4]);
+    }
+#pragma unroll
+    for (int m = 0; m < 5; ++m) s_h[m][r][tx] = h[m];
+  }
+  __syncthreads();
+  float sum = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = ty + 8 * q, px = X0 + tx, py = Y0 + r;
+    float o[5];
+    st_column<5>(a, s_h, tx, r, o);
+    if (px >= a.W || py >= a.H) continue;
+    const SsPoint v(o[0], o[1], o[2], o[3], o[4]);
+    if (MAPS) v.maps(maps, pl * plane + (int64_t)py * a.W + px, (int64_t)a.planes * plane);
+    if (SUM) sum += v.loss();
+  }
+  if (SUM) ss_block_sum<kStBlock>(a, sum, s_red, partial);
+}
+
+template <bool ADD>
+__global__ __launch_bounds__(kStBlock) void k_ssim_bwd_tile(const float* __restrict__ x,
+                                                            const float* __restrict__ y, SsArgs a,
+                                                            const float* __restrict__ maps,
+                                                            const float* __restrict__ d_loss,
+                                                            float inv_n, float* __restrict__ d_x) {
+  __shared__ float s_in[3][kStIn][kStIn + 1];
+  __shared__ float s_h[3][kStIn][kStTile + 1];
+  const int pl = blockIdx.z, X0 = blockIdx.x * kStTile, Y0 = blockIdx.y * kStTile;
+  const int64_t plane = (int64_t)a.W * a.H, all = (int64_t)a.planes * plane;
+  const float* src[3] = {maps + pl * plane, maps + all + pl * plane, maps + 2 * all + pl * plane};
+  st_stage<3>(src, a, X0, Y0, s_in);
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int r = ty; r < kStIn; r += 8)
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      float s = 0.0f;
+#pragma unroll
+      for (int j = 0; j < kSsTaps; ++j) s = fmaf(a.w[j], s_in[m][r][tx + j], s);
+      s_h[m][r][tx] = s;
+    }
+  __syncthreads();
+  const float scale = -(d_loss ? *d_loss : 1.0f) * inv_n;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = ty + 8 * q, px = X0 + tx, py = Y0 + r;
+    float o[3];
+    st_column<3>(a, s_h, tx, r, o);
+    if (px >= a.W || py >= a.H) continue;
+    const int64_t i = pl * plane + (int64_t)py * a.W + px;
+    const float yi = y[i];
+    const float g = o[0] + 2.0f * (x[i] - yi) * o[1] + yi * o[2];
+    d_x[i] = ADD ? d_x[i] + scale * g : scale * g;
+  }
+}
+
 // out[0] = sum(partial) / N (the blocks' sums of 1 - SSIM), in a fixed
 // order.
 __global__ __launch_bounds__(256) void k_dssim_finish(const float* __restrict__ partial,
@@ -509,10 +641,21 @@ constexpr int kSsResident = 5, kSsResidentBwd = 8;   // by LDS; by registers
 bool ss_ok(int planes, int W, int H) {
   return planes >= 1 && W >= 1 && H >= 1 && planes <= 65535 && div_up(H, 32) <= 65535;
 }
+// Tiles where there are few of them (a strip's workgroup takes as many steps
+// however small the image) or the strips' columns would be over a fifth idle:
+// loss and adjoint 15 + 30 us with strips and 12 + 24 with tiles for three 512 x
+// 512 planes, 16 + 25 and 12 + 14 for 300 of 32 x 32, 46 + 93 and 40 + 71 for 192
+// of 128 x 128 (55 % used), but 31 + 64 and 39 + 69 for twelve of 512 x 512, 30 +
+// 62 and 47 + 84 for thirty of 1024 x 100 (86 %).
+bool ss_tiles(int planes, int W, int H) {
+  const int64_t tiles = (int64_t)planes * div_up(W, kStTile) * div_up(H, kStTile);
+  return tiles < 2048 || 5 * (int64_t)W < 4 * (int64_t)kSsOut * div_up(W, kSsOut);
+}
 void ss_args(int planes, int W, int H, int resident, SsArgs* a) {
   a->planes = planes;
   a->W = W;
   a->H = H;
+  a->tile = ss_tiles(planes, W, H);
   a->tiles_x = div_up(W, kSsOut);
   const int64_t chip = (int64_t)resident * device_cus();
   int64_t best = INT64_MAX;
@@ -526,6 +669,10 @@ void ss_args(int planes, int W, int H, int resident, SsArgs* a) {
     a->rows = div_up(H, strips);
     a->groups = div_up(a->rows + 2 * kSsHalo, kSsTaps);
   }
+  if (a->tile) {
+    a->tiles_x = div_up(W, kStTile);
+    a->tiles_y = div_up(H, kStTile);
+  }
   double g[11], s = 0.0;
   for (int j = 0; j < 11; ++j) {
     const double u = j - 5;
@@ -533,6 +680,28 @@ void ss_args(int planes, int W, int H, int resident, SsArgs* a) {
     s += g[j];
   }
   for (int j = 0; j < 11; ++j) a->w[j] = (float)(g[j] / s);
+}
+
+template <bool MAPS, bool SUM>
+void launch_ssim(const SsArgs& a, const float* x, const float* y, float* maps, float* partial,
+                 hipStream_t st) {
+  const dim3 grid(a.tiles_x, a.tiles_y, a.planes);
+  if (a.tile)
+    hipLaunchKernelGGL((k_ssim_tile<MAPS, SUM>), grid, dim3(kStBlock), 0, st, x, y, a, maps, partial);
+  else
+    hipLaunchKernelGGL((k_ssim<MAPS, SUM>), grid, dim3(kSsBlock), 0, st, x, y, a, maps, partial);
+}
+template <bool ADD>
+void launch_ssim_bwd(const SsArgs& a, const float* x, const float* y, const float* maps,
+                     const float* d_loss, float* d_x, hipStream_t st) {
+  const dim3 grid(a.tiles_x, a.tiles_y, a.planes);
+  const float inv_n = (float)(1.0 / ((double)a.planes * a.W * a.H));
+  if (a.tile)
+    hipLaunchKernelGGL(k_ssim_bwd_tile<ADD>, grid, dim3(kStBlock), 0, st, x, y, a, maps, d_loss,
+                       inv_n, d_x);
+  else
+    hipLaunchKernelGGL(k_ssim_bwd<ADD>, grid, dim3(kSsBlock), 0, st, x, y, a, maps, d_loss, inv_n,
+                       d_x);
 }
 
 // -------------------------------------------------------------- regulariser
@@ -799,8 +968,7 @@ extern "C" vrs_status vrs_dssim(const float* x, const float* y, int planes, int 
   ss_args(planes, width, height, kSsResident, &a);
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* partial = static_cast<float*>(ws);
-  hipLaunchKernelGGL((k_ssim<false, true>), dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
-                     y, a, nullptr, partial);
+  launch_ssim<false, true>(a, x, y, nullptr, partial, st);
   VRS_LAUNCH_CHECK();
   const int64_t nb = (int64_t)planes * a.tiles_x * a.tiles_y;
   hipLaunchKernelGGL(k_dssim_finish, dim3(1), dim3(256), 0, st, partial, nb,
@@ -820,12 +988,9 @@ extern "C" vrs_status vrs_dssim_backward(const float* x, const float* y, int pla
   ss_args(planes, width, height, kSsResidentBwd, &b);
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* maps = static_cast<float*>(ws);
-  hipLaunchKernelGGL((k_ssim<true, false>), dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0, st, x,
-                     y, a, maps, nullptr);
+  launch_ssim<true, false>(a, x, y, maps, nullptr, st);
   VRS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_ssim_bwd<true>, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0, st, x, y,
-                     b, maps, d_loss,
-                     (float)(1.0 / ((double)planes * width * height)), d_x);
+  launch_ssim_bwd<true>(b, x, y, maps, d_loss, d_x, st);
   VRS_LAUNCH_CHECK();
   return VRS_OK;
 }
@@ -849,8 +1014,7 @@ extern "C" vrs_status vrs_dssim_forward_maps(const float* x, const float* y, int
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* m = static_cast<float*>(maps);
   float* partial = m + 3 * (int64_t)planes * width * height;
-  hipLaunchKernelGGL((k_ssim<true, true>), dim3(a.tiles_x, a.tiles_y, planes), dim3(kSsBlock), 0,
-                     st, x, y, a, m, partial);
+  launch_ssim<true, true>(a, x, y, m, partial, st);
   VRS_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_dssim_finish, dim3(1), dim3(256), 0, st, partial,
                      (int64_t)planes * a.tiles_x * a.tiles_y,
@@ -867,9 +1031,8 @@ extern "C" vrs_status vrs_dssim_backward_maps(const float* x, const float* y, in
     return VRS_EINVAL;
   SsArgs b;
   ss_args(planes, width, height, kSsResidentBwd, &b);
-  hipLaunchKernelGGL(k_ssim_bwd<false>, dim3(b.tiles_x, b.tiles_y, planes), dim3(kSsBlock), 0,
-                     static_cast<hipStream_t>(stream), x, y, b, static_cast<const float*>(maps),
-                     d_loss, (float)(1.0 / ((double)planes * width * height)), d_x);
+  launch_ssim_bwd<false>(b, x, y, static_cast<const float*>(maps), d_loss, d_x,
+                         static_cast<hipStream_t>(stream));
   VRS_LAUNCH_CHECK();
   return VRS_OK;
 }
