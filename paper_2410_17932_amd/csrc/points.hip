@@ -45,7 +45,8 @@ struct SplatWs {
       fkey1, fval1,                // fragments in blend order
       pcnt, poff,                  // per layer pixel: fragment count, segment offsets [P + 1]
       surv2, ord_hist,             // dense lists: survivors by bucket (0: none), the buckets' counts
-      hide,                        // per view pixel: depth that hides points (0: none kept)
+      hide,                        // per view pixel: depth that hides points (0: none kept),
+                               // over the fragments
       grid, scan_tmp, total;
   int ord_parts;
   int gx, gy;   // crop-lookup grid cells per view row / column
@@ -96,13 +97,6 @@ static bool splat_layout(int64_t np, int nv, int W, int H, const vrs_crop* crops
   L->frag_count = L->ctr + 4;
   L->left = L->ctr + 8;   // then the pixels that k_pt_resolve leaves to rank and blend
   L->chunk_first = c.take((mf / kEmitFrags + 2) * 4);
-  L->fkey0 = c.take(mf * 4);
-  L->fval0 = c.take(mf * 8);
-  L->fdep = c.take(mf * 4);
-  L->fslot = c.take(mf * 4);
-  L->seg = c.take(mf * 16);
-  L->fkey1 = c.take(mf * 4);
-  L->fval1 = c.take(mf * 8);
   L->pcnt = c.take(pt * 4);
   L->poff = c.take((pt + 1) * 4);
   L->surv2 = L->ord_hist = 0;
@@ -113,15 +107,28 @@ static bool splat_layout(int64_t np, int nv, int W, int H, const vrs_crop* crops
     L->surv2 = c.take(most * 16);
     L->ord_hist = c.take(((size_t)L->ord_parts + 1) * kOrdBuckets * 8);
   }
+  L->grid = c.take((size_t)nv * L->gx * L->gy * 4);
+  L->scan_tmp = c.take(scan_tmp_bytes(pt));
+  L->fkey0 = c.take(mf * 4);
+  L->fval0 = c.take(mf * 8);
+  L->fdep = c.take(mf * 4);
+  L->fslot = c.take(mf * 4);
+  L->seg = c.take(mf * 16);
+  L->fkey1 = c.take(mf * 4);
+  L->fval1 = c.take(mf * 8);
   {
-    // pairs that look a pixel up, about, against four pixels of the image
+    // pairs that look a pixel up, about, against four pixels of the image; the
+    // selection is done with it when the first fragment is written, so it lies
+    // over the fragments
     double area = 0.0;
     for (int k = 0; k < n_crops; ++k) area += (double)crops[k].size * crops[k].size;
     const double pixels = (double)nv * W * H;
-    L->hide = (double)L->vn * area * 4.0 >= pixels * pixels ? c.take((size_t)pixels * 4) : 0;
+    L->hide = 0;
+    if ((double)L->vn * area * 4.0 >= pixels * pixels) {
+      L->hide = L->fkey0;
+      c.off = std::max(c.off, L->hide + (size_t)pixels * 4);
+    }
   }
-  L->grid = c.take((size_t)nv * L->gx * L->gy * 4);
-  L->scan_tmp = c.take(scan_tmp_bytes(pt));
   L->total = c.off;
   return true;
 }
