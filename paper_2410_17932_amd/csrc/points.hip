@@ -900,6 +900,8 @@ __global__ __launch_bounds__(256) void k_pt_scatter(const uint32_t* __restrict__
 // Consecutive places share segments, so the lanes of a segment read the
 // same records; places go in reverse, so that the long segments of each
 // crop's coarse layers start early.
+// DENSE: the capacity allows dense lists; then only what k_pt_resolve left.
+template <bool DENSE>
 __global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
                                                  uint32_t* __restrict__ fin,
                                                  const uint32_t* __restrict__ poff,
@@ -910,9 +912,9 @@ __global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
                                                  const uint32_t* __restrict__ ids,
                                                  uint32_t* __restrict__ okey,
                                                  uint64_t* __restrict__ oval) {
-  const uint32_t left = *left_p;   // (read with the count: most workgroups only leave)
+  const uint32_t left = DENSE ? *left_p : 0u;   // (read with the count: most workgroups only leave)
   const int64_t total = *total_p;
-  const bool dense = total > kRsDense * pix_total;   // only what k_pt_resolve left
+  const bool dense = DENSE && total > kRsDense * pix_total;
   if (total > max_frags || (dense && left == 0)) return;
   const uint64_t* key = reinterpret_cast<const uint64_t*>(seg);   // depth key << 32 | index
   for (int64_t sr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; sr < total;
@@ -964,6 +966,7 @@ __global__ __launch_bounds__(256) void k_pt_rank(const uint4* __restrict__ seg,
 // Pixels go in reverse pyramid order: each crop's coarse layers (the long
 // lists) come after its finest layer in the pyramid, so in reverse the
 // long lists start early and the finest layers' short lists fill the end.
+template <bool DENSE>   // as k_pt_rank
 __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ fval,
                                                   const uint32_t* __restrict__ poff,
                                                   const uint32_t* __restrict__ total_p,
@@ -975,8 +978,8 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
                                                   int64_t pix_total, float4* __restrict__ pyr) {
   // dense lists are k_pt_resolve's (launched wherever the capacity allows
   // them) but for those it left
-  const uint32_t left = *left_p;
-  const bool dense = min((int64_t)*total_p, max_frags) > kRsDense * pix_total;
+  const uint32_t left = DENSE ? *left_p : 0u;
+  const bool dense = DENSE && min((int64_t)*total_p, max_frags) > kRsDense * pix_total;
   if (dense && left == 0) return;
   const bool over = (int64_t)*total_p > max_frags;
   for (int64_t kr = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; kr < pix_total;
@@ -1524,7 +1527,8 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
   VRS_LAUNCH_CHECK();
   // long lists are ranked and blended together (four workgroups per compute
   // unit, what the LDS holds), short ones by a thread per fragment and pixel
-  if (max_frags > kRsDense * L.pix_total) {
+  const bool dense = max_frags > kRsDense * L.pix_total;
+  if (dense) {
     const unsigned rb = (unsigned)std::min<int64_t>(4 * device_cus(), div_up(L.pix_total, kRsPix));
     hipLaunchKernelGGL(k_pt_resolve, dim3(rb), dim3(256), 0, st, at<uint4>(ws, L.seg),
                        at<uint32_t>(ws, L.fdep), poff,
@@ -1533,14 +1537,14 @@ vrs_status splat_impl(const float* pos, const float* radius, const uint16_t* fea
                        reinterpret_cast<float4*>(pyramid));
     VRS_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(k_pt_rank, dim3(fb), dim3(256), 0, st, at<uint4>(ws, L.seg),
+  hipLaunchKernelGGL((dense ? k_pt_rank<true> : k_pt_rank<false>), dim3(fb), dim3(256), 0, st, at<uint4>(ws, L.seg),
                      at<uint32_t>(ws, L.fdep), poff,
                      frag_count, max_frags, L.pix_total, at<uint32_t>(ws, L.left), pcnt, point_ids,
                      at<uint32_t>(ws, L.fkey1),
                      at<uint64_t>(ws, L.fval1));
   VRS_LAUNCH_CHECK();
   const unsigned pb = (unsigned)std::min<int64_t>(8192, std::max<int64_t>(1, div_up(L.pix_total, 256)));
-  hipLaunchKernelGGL(k_pt_blend, dim3(pb), dim3(256), 0, st, at<uint64_t>(ws, L.fval1), poff,
+  hipLaunchKernelGGL((dense ? k_pt_blend<true> : k_pt_blend<false>), dim3(pb), dim3(256), 0, st, at<uint64_t>(ws, L.fval1), poff,
                      frag_count, max_frags, at<uint32_t>(ws, L.left), pcnt, feat, opacity, np,
                      L.pix_total, reinterpret_cast<float4*>(pyramid));
   VRS_LAUNCH_CHECK();
