@@ -57,15 +57,15 @@ __device__ inline float row_sum(float v) {
 // reduction and the atomics but were slower at every size measured (2330
 // against 2099 us below, 1955 against 817 at 256 x 256).  What keeps it there:
 // a pixel that does not take the entry has alpha 0, which leaves its sums as
-// they are but for values that 0 does not cancel (see the record loop); the
-// colour behind an entry is needed only
-// through its product with the pixel's gradient, one running sum instead of
-// four; and the ten sums are reduced together, halving the registers at each
-// exchange (28 instructions instead of 120), into ten lanes' one atomic
-// instruction.  T / (1 - alpha) is the hardware reciprocal with its remainder
+// they are, so that only the running sum and the opacity's gradient are selected
+// by the mask (all ten values where a gradient, a conic or an opacity is not
+// finite, which 0 does not cancel); the colour behind an entry is needed only
+// through its product with the pixel's gradient, one running sum instead of four;
+// and the ten sums are reduced together, halving the registers at each exchange
+// (28 instructions instead of 120), into ten lanes' one atomic instruction.  T / (1 - alpha) is the hardware reciprocal with its remainder
 // put back (1 - alpha is in [0.01, 1], so no scaling is needed).
 // 1M Gaussians, four 1024 x 1024 views, tile 16: 3574 us with ten reductions,
-// ten atomics and all records of a tile per 64 pixels, 477 us now.
+// ten atomics and all records of a tile per 64 pixels, 453 us now.
 template <int TILE, bool DEPTH>
 __global__ __launch_bounds__(64) void k_gs_blend_bwd(
     const uint32_t* __restrict__ order, const uint2* __restrict__ ranges,

@@ -173,21 +173,12 @@ __device__ inline float gs_exponent(const float4& a, const float4& b, float dx, 
   return fmaf(dy, fmaf(b.x, dy, R), P);
 }
 
-// Opacity at a pixel centre.  The conic is positive definite (the dilated
-// covariance has a positive determinant), so the exponent is never positive
-// but for rounding within a few units of the last place of zero, at the
-// centre, where the opacity is the Gaussian's own either way: no guard on its
-// sign is taken.  The forward blend evaluates the same operations inline and
-// the backward calls this, so both take the same threshold decisions; e = 2^q
-// is returned for the adjoint.
-__device__ inline float gs_alpha(const float4& a, const float4& b, float xc, float yc,
-                                 float aclamp, float& dx, float& dy, float& e) {
-  dx = a.x - xc;
-  dy = a.y - yc;
-  const float q = gs_exponent(a, b, dx, dy);
-  e = __builtin_amdgcn_exp2f(q);
-  return fminf(b.y * e, aclamp);
-}
+// The opacity at a pixel centre is min(alpha_clamp, opacity 2^q).  The conic is
+// positive definite (the dilated covariance has a positive determinant), so the
+// exponent is never positive but for rounding within a few units of the last
+// place of zero, at the centre, where the opacity is the Gaussian's own either
+// way: no guard on its sign is taken.  The blends and the adjoint evaluate the
+// same operations inline, so all take the same threshold decisions.
 
 // A lane flag as the wave's mask (bit l = lane l) and back: the mask lives
 // in scalar registers and every combination of flags is a scalar operation.

@@ -17,6 +17,8 @@
 //                  the same pass, one 64-bit atomic per workgroup for the
 //                  survivor and fragment bases, and the survivor that opens
 //                  each emission chunk
+//   k_pt_ord_*     where the counted fragments make dense lists: the survivors
+//                  into the order of screen buckets (count, scan, move)
 //   k_pt_emit      one workgroup per chunk of 1024 consecutive fragments,
 //                  one thread per survivor of the chunk: writes its
 //                  fragments (layer pixel, weight | point index, depth key),
@@ -25,8 +27,10 @@
 //   scan           per-pixel counts -> segment offsets
 //   k_pt_scatter   each fragment's record (point index, depth key, weight,
 //                  pixel) to its segment place: no atomics
-//   k_pt_rank      one thread per segment place: the record's rank in its
-//                  segment -> its final place (the lanes of one segment
+//   k_pt_resolve   dense lists: a wave or a workgroup per pixel ranks its
+//                  segment and composites it
+//   k_pt_rank      otherwise, one thread per segment place: the record's rank
+//                  in its segment -> its final place (the lanes of one segment
 //                  read the same records)
 //   k_pt_blend     one thread per layer pixel walks its list front to back
 #include <hip/hip_fp16.h>
@@ -1034,18 +1038,22 @@ __global__ __launch_bounds__(256) void k_pt_blend(const uint64_t* __restrict__ f
 // depth buckets (count, scan, place, then a comparison within the bucket
 // alone; up to 64 a lane's one fragment against all, up to 256 four; a bucket
 // beyond the LDS leaves its pixel to k_pt_rank and k_pt_blend), then each wave
-// composites its pixel: the lanes gather 64 fragments'
-// weights and features at a time, and the sums run over them one by one in
-// list order, a channel per lane (the same operations in the same order as
-// k_pt_blend, so the results are the same to the bit): 0.96 ms, of which the
-// records, the lists and 8-byte features from scattered lines are most.
+// composites its pixel: the lanes gather 64 fragments' weights and features at a
+// time, and the sums run over them one by one in list order, a channel per lane
+// (the same operations in the same order as k_pt_blend, so the results are the
+// same to the bit): 0.97 ms for those 27M, of which the records, the lists and
+// 8-byte features from scattered lines are most.
 //
 // It takes the splats that counted over kRsDense fragments per layer pixel;
 // the count is on the device, so where the capacity allows that many all three
-// kernels are launched and those not meant leave at once.  One 512 crop,
-// whole splat, this kernel against the two: 435 us against 325 at 6.6
-// fragments per pixel, 622 against 704 at 13, 3.2 ms against 11.8 at 77 (a
-// wave per pixel idles on short lists).
+// kernels are launched and those not meant leave at once (9 us for the screen
+// order's and this one).  Whole splat, this way with the screen order against the
+// two kernels: one 512 crop 256 us and 169 at 3.2 fragments per pixel, 328 and 322
+// at 6.3, 399 and 497 at 9.5, 1.94 ms and 10.9 at 76; crops of 64, 128 and 256 59
+// and 55, 74 and 65, 129 and 118 at 8, 61 and 69, 77 and 79, 138 and 144 at 10 (a
+// wave per pixel idles on short lists).  The sides meet at 6.5 for a large crop and
+// at 10 for small ones; the line is above both, as the launches that only leave
+// are an eighth of a small splat's time.
 constexpr uint32_t kRsWave = 256;   // fragments that one wave ranks
 constexpr int kRsCap = 4096, kRsBuckets = 1024, kRsPix = 4;   // pixels per workgroup, one wave each
 

@@ -2,10 +2,11 @@
 // the reading stated in vrsplat.h) and the training objective's kernels
 // (Sec. 3.5, Eqs. 6-7): D-SSIM, the regulariser R, and the Adam step.
 //
-// All of them stream their images once (the SSIM tiles re-read a 5-pixel
+// All of them stream their images once (SSIM's strips and tiles re-read a 5-pixel
 // halo), so each is bound by HBM bandwidth.  Sums over an image are
 // deterministic (per-block partials reduced in a fixed order), except the
-// response-curve gradient, accumulated per block with LDS atomics.
+// gradient of a response curve of more than kTmLaneSamples samples, accumulated
+// per block with LDS atomics.
 #include <cmath>
 
 #include "vrs_common.h"
@@ -275,7 +276,7 @@ int tm_blocks(const TmArgs& a) {
   return std::max(1, std::min(kTmBlocksPerView, div_up((int64_t)a.W * a.H, kTmBlock)));
 }
 // The adjoint ends each workgroup with a reduction of the response columns,
-// so it takes fewer: two per compute unit.
+// so it takes fewer: for one view two per compute unit.
 int tm_bwd_blocks(const TmArgs& a) {
   return std::max(1, std::min(kTmBwdBlocks, div_up((int64_t)a.W * a.H, kTmBlock)));
 }

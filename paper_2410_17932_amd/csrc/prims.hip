@@ -521,8 +521,9 @@ hipError_t radix_sort_r(uint32_t* k0, V* v0, uint32_t* k1, V* v1, const uint32_t
   if (passes == 0 || n_max == 0) return hipSuccess;
   // One workgroup while its passes cost less than the launches they save: four
   // passes over up to 8192 items (a whole small frame, eager: 183 -> 153 us at
-  // 1000, 265 -> 256 at 8000, but 239 -> 258 at 16000), one or two over twice
-  // that.
+  // 1000, 265 -> 256 at 8000, but 239 -> 258 at 16000; a periphery alone, replayed
+  // from a graph: 135 -> 106 at 1000, 251 -> 229 at 4000, 395 -> 390 at 8192), one
+  // or two over twice that.
   if (R == 8 && n_max <= kSmallMax && passes * n_max <= 2 * kSmallMax) {
     hipLaunchKernelGGL(k_sort_small<V>, dim3(1), dim3(kSmallBlock), 0, st, k0,
                        iota ? nullptr : v0, *result_in_1 ? k1 : k0, *result_in_1 ? v1 : v0, n_dev,
